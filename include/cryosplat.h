@@ -457,11 +457,12 @@ int cs_pose_refine(cs_pose_bank *bank, const float *images, const cs_ctf *ctf, i
 /* Particle side of pose scoring, computed once per batch of particles and
  * shared by every search and refinement stage on any bank of the same D:
  * Z = H Y (the image filtered by its own CTF, the matched filter of the
- * image model), the (2r+1)^2 circularly shifted copies of -2 Z (bfloat16),
+ * image model), 2r+1 circularly shifted copies of -2 Z (bfloat16, one per
+ * column offset; a row offset is an address),
  * the energy weights w_f |H^|^2 / D^2 (bfloat16) and ||Y||^2.
  * create: capacity particles of side D (multiple of 16, prime factors 2
  * and 3, <= 512), shift radius 0 <= r <= 4; device memory about
- * capacity * D^2 * (2 (2r+1)^2 + 18) bytes.  load: P <= capacity images
+ * capacity * D^2 * (2 (2r+1)(1 + 2r/D) + 18) bytes.  load: P <= capacity images
  * [P][D][D] with per-particle CTF parameters (ctf NULL = no CTF); filtered
  * (may be NULL) receives Z [P][D][D] FP32; standardized (may be NULL)
  * receives Z standardised per image, (Z - mean) / std as bfloat16 [P][D][D],

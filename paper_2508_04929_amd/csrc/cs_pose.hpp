@@ -8,12 +8,13 @@
 
 namespace cs {
 
-enum { kPoseStore = 0, kPoseScore = 1, kPoseRefine = 2 };
+enum { kPoseStore = 0, kPoseScore = 1 };
 
 // Operands of the pose GEMMs (bfloat16 as raw uint16, K contiguous).
 struct PoseGemmArgs {
-  const unsigned short *A = nullptr;   // rows of length >= K (lda elements apart)
-  int64_t lda = 0;
+  const unsigned short *A = nullptr;   // store: rows lda elements apart; score, refine: the
+  int64_t lda = 0;                     //   shifted copies of k_pose_shifts (D, r, side)
+  int D = 0, r = 0, side = 1;
   const unsigned short *A2 = nullptr;  // refine: second A segment (per particle), k >= ka_split
   int64_t lda2 = 0;
   int ka_split = 0;
@@ -22,7 +23,8 @@ struct PoseGemmArgs {
   const int *cand = nullptr;           // refine: [P][L] bank rows (out of [0, nrows): skipped)
   int L = 0;
   int64_t nrows = 0;                   // refine: rows of B
-  int M = 0, N = 0, K = 0;             // K a multiple of the kernel's K step (32 / 128)
+  int M = 0, N = 0, K = 0;             // K a multiple of 128
+  int t0 = 0;                          // store, score: first 256 x 256 tile of the launch
   int S = 1;                           // shifts per particle
   float *C = nullptr;                  // store: [M][ldc]
   int64_t ldc = 0;

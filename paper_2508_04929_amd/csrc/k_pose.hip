@@ -14,6 +14,7 @@
 // grid and is fused into the K dimension for gathered candidate lists.
 #include <algorithm>
 
+#include "cs_mma.hpp"
 #include "cs_pose.hpp"
 
 namespace cs {
@@ -42,9 +43,13 @@ __device__ __forceinline__ float ord_float(unsigned o) {
 // ---------------------------------------------------------------------------
 // Particle preparation.
 //   k_pose_zpad    (block = particle): -2 Z as bfloat16 rows with wrap padding
-//   k_pose_shifts  (block = (particle, shift s)), from the padded rows:
-//     zs[p][s][i][j] = -2 Z[p][(i - dy) mod D][(j + dx) mod D]   (bfloat16)
-//     shift s = (dy + r)(2r + 1) + (dx + r); 8 outputs (16 bytes) per lane
+//   k_pose_shifts  (block = (particle, column offset dx)), from the padded
+//     rows: one copy per column offset with r wrapped rows above and below,
+//     so that the particle moved by shift s = (dy + r)(2r + 1) + (dx + r),
+//       -2 Z[p][(i - dy) mod D][(j + dx) mod D]   (bfloat16),
+//     is the D^2 consecutive values of copy dx from row r - dy on; 8 outputs
+//     (16 bytes) per lane.  2r + 1 copies instead of (2r + 1)^2: 173 MB
+//     instead of 839 MB for 1,024 particles of 128^2 at r = 2
 //   k_pose_weights (block = particle):
 //     w[p][f] = w_f * table[p][f]^2 * D^2 = w_f |H^(f)|^2 / D^2, zero pad to F8
 //     yy[p]   = sum Y^2
@@ -77,18 +82,18 @@ k_pose_zpad(const float *Z, int D, unsigned short *zb) {
   }
 }
 
-// zs[p][s][i][j] = zb[p][(i - dy) mod D][j + dx + 8]  (block = (particle, shift))
+// zs[p][dx + r][t][j] = zb[p][(t - r) mod D][j + dx + 8], t < D + 2 r (block =
+// (particle, column offset dx))
 __global__ void __launch_bounds__(256)
 k_pose_shifts(const unsigned short *zb, int D, int r, unsigned short *zs) {
-  const int p = blockIdx.x, s = blockIdx.y;
-  const int side = 2 * r + 1, S = side * side, npx = D * D, RS = D + 16;
-  const int dy = s / side - r, dx = s % side - r;
+  const int p = blockIdx.x, dx = (int)blockIdx.y - r;
+  const int side = 2 * r + 1, RS = D + 16, rows = D + 2 * r;
   const unsigned short *zp = zb + (size_t)p * D * RS;
-  uint4 *o = (uint4 *)(zs + ((size_t)p * S + s) * npx);
+  uint4 *o = (uint4 *)(zs + ((size_t)p * side + blockIdx.y) * rows * D);
   const int per_row = D / 8;
-  for (int v = threadIdx.x; v < npx / 8; v += 256) {
-    const int i = v / per_row, j0 = (v - i * per_row) * 8;
-    int si = i - dy;
+  for (int v = threadIdx.x; v < rows * per_row; v += 256) {
+    const int t = v / per_row, j0 = (v - t * per_row) * 8;
+    int si = t - r;
     si += (si < 0) ? D : 0;
     si -= (si >= D) ? D : 0;
     o[v] = load8_at((const unsigned *)(zp + (size_t)si * RS), j0 + dx + 8);
@@ -203,138 +208,165 @@ k_pose_confidence(const unsigned short *bank, int64_t ldb, int64_t boff, int64_t
 }
 
 // ---------------------------------------------------------------------------
-// TN GEMM on MFMA: C[m][n] = sum_k A[m][k] B[n][k], bfloat16 operands with
-// K contiguous, FP32 accumulation (v_mfma_f32_16x16x32_bf16), K a multiple
-// of 32.  256 threads = 4 waves in a WGM x (4 / WGM) arrangement; tiles of
-// BM x BN, K steps of 32 double-buffered through LDS (rows padded to 80 B so
-// that the 16-byte operand reads of 16 lanes hit 64 distinct banks).
+// Grid-search GEMMs: C[m][n] = sum_k A[m][k] B[n][k], bfloat16 operands with K
+// contiguous, FP32 accumulation (v_mfma_f32_16x16x32_bf16, K in order), K a
+// multiple of 64.  NWM x NWN waves, each TI x TJ MFMA tiles; K steps of 64 in
+// two LDS buffers, filled by direct global-to-LDS loads: a step's fragments
+// are read into registers first, then the next step's loads are issued, so
+// they are in flight behind this step's MFMAs and one barrier per step
+// suffices (the buffer they fill was last read before that barrier).  Bound by
+// the matrix cores and, next, by the LDS traffic of the fragments: a wave
+// reads 24 KB for 128 x 64 x 64 products.  The 25,600 x 4,608 x 16,384 product
+// of 1,024 particles takes 3.0 ms (1.29 PFLOP/s; 1.37 in the whole rounds of
+// 256 tiles), against 5.58 ms (690 TFLOP/s) with 128 x 128 tiles staged through
+// registers in steps of 32.
 //
-//   MODE kStore:  C (FP32) = A B^T                        (energy matrix)
-//   MODE kScore:  rows m = p S + s, value = acc + E[p][n] + yy[p];
-//                 per-particle minimum of (value, n S + s) by 64-bit atomicMin
-//   MODE kRefine: block x = particle p, rows s < S, B rows gathered through
-//                 cand[p][n]; A switches at k = ka_split from the shifted
-//                 particle rows to the particle's energy weights (energy fused
-//                 into the contraction); value = acc + yy[p]
+//   MODE kPoseStore:  C (FP32) = A B^T                    (energy matrix)
+//   MODE kPoseScore:  rows m = p S + s, value = acc + yy[p] + E[p][n];
+//                     per-particle minimum of (value, n S + s) by 64-bit
+//                     atomicMin
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int MODE, int kBK>
-__global__ void __launch_bounds__(256) k_pose_gemm(PoseGemmArgs a) {
-  constexpr int kLDK = kBK + 8;   // padded row: 16-lane operand reads hit distinct banks
-  constexpr int KQ = kBK / 8;     // 16-byte loads per row and K step
-  constexpr int WGN = 4 / WGM;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int TI = WTM / 16, TJ = WTN / 16;
-  constexpr int LA = BM * kBK / 8, LB = BN * kBK / 8;  // 16-byte loads per K step
-  constexpr int NA = (LA + 255) / 256, NB = (LB + 255) / 256;
-  static_assert(TI >= 1 && TJ >= 1 && LA % 64 == 0 && LB % 64 == 0, "tile shape");
-  __shared__ unsigned short sA[2][BM][kLDK];
-  __shared__ unsigned short sB[2][BN][kLDK];
 
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wm = (wv / WGN) * WTM, wn = (wv % WGN) * WTN;
+// Row of the shifted copies that holds particle p moved by shift s: a column
+// offset selects the copy, a row offset only its first row (element index).
+__device__ __forceinline__ int64_t shift_row(const PoseGemmArgs &a, int p, int s) {
+  const int dy = s / a.side - a.r, dxi = s % a.side;
+  return (((int64_t)p * a.side + dxi) * (a.D + 2 * a.r) + (a.r - dy)) * a.D;
+}
 
-  int mt, nt, p = 0;
-  if (MODE == kPoseRefine) {
-    p = blockIdx.x;
-    mt = 0;
-    nt = blockIdx.y;
-  } else {
-    // XCD-aware order: consecutive block ids land on different XCDs, so give
-    // each XCD a contiguous range of tiles, grouped 8 row tiles at a time.
-    const int Mt = (a.M + BM - 1) / BM, Nt = (a.N + BN - 1) / BN;
-    const int T = Mt * Nt;
-    int t = blockIdx.x;
-    if ((T & 7) == 0) t = (t & 7) * (T >> 3) + (t >> 3);
-    const int G = 8;
-    const int grp = t / (G * Nt);
-    const int first = grp * G;
-    const int gs = min(Mt - first, G);
-    const int within = t - grp * G * Nt;
-    mt = first + within % gs;
-    nt = within / gs;
+// The smaller of the 16 lanes' (score, index) keys of one row, to best[p].
+__device__ __forceinline__ void row_minimum(unsigned long long key, int lane,
+                                            unsigned long long *best) {
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    const unsigned lo = __shfl_xor((unsigned)(key & 0xffffffffu), o, 64);
+    const unsigned hi = __shfl_xor((unsigned)(key >> 32), o, 64);
+    const unsigned long long k2 = ((unsigned long long)hi << 32) | lo;
+    key = k2 < key ? k2 : key;
   }
-  const int m0 = mt * BM, n0 = nt * BN;
+  if ((lane & 15) == 0 && key != ~0ull) atomicMin(best, key);
+}
 
-  // global -> register staging of one K step
-  uint4 ra[NA], rb[NB];
-  auto gload = [&](int k0) {
+template <int NWM, int NWN, int TI, int TJ, int MODE>
+__global__ void __launch_bounds__(64 * NWM * NWN, 2) k_pose_mma(PoseGemmArgs a) {
+  constexpr int kT = 64 * NWM * NWN, BM = NWM * TI * 16, BN = NWN * TJ * 16;
+  constexpr int NA = BM * 8 / kT, NB = BN * 8 / kT;  // 16-byte loads per thread and step
+  static_assert(NA * kT == BM * 8 && NB * kT == BN * 8, "tile shape");
+  // (four arrays: the compiler then knows that the fragment reads of one
+  // buffer need not wait for the loads that fill the other)
+  __shared__ __attribute__((aligned(1024))) unsigned short sA0[BM * kMmaK], sA1[BM * kMmaK];
+  __shared__ __attribute__((aligned(1024))) unsigned short sB0[BN * kMmaK], sB1[BN * kMmaK];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wv / NWN) * TI * 16, wn = (wv % NWN) * TJ * 16;
+  // blocks are the BM x BN parts of 256 x 256 tiles a.t0 ...; every XCD runs
+  // one contiguous range of them, 8 tiles down the rows before the next
+  // column, so that its L2 holds the rows that its blocks share
+  constexpr int QN = 256 / BN, QS = 256 / BM * QN;
+  const int Mt = (a.M + 255) / 256, Nt = (a.N + 255) / 256;
+  const int part = xcd_work(blockIdx.x, gridDim.x);
+  const int t = a.t0 + part / QS, sub = part % QS;
+  const int first = t / (8 * Nt) * 8, gs = min(Mt - first, 8), within = t - first * Nt;
+  const int m0 = (first + within % gs) * 256 + sub / QN * BM, n0 = within / gs * 256 + sub % QN * BN;
+  if (m0 >= a.M || n0 >= a.N) return;
+  // 32-bit byte offsets of this thread's pieces from the tile's first rows
+  // (rows past the end repeat the last one; their results are not used)
+  const int64_t a0 = MODE == kPoseScore ? shift_row(a, m0 / a.S, (a.side - 1) * a.side) : (int64_t)m0 * a.lda;
+  const char *pa = (const char *)(a.A + a0), *pb = (const char *)(a.B + (int64_t)n0 * a.ldb + a.boff);
+  unsigned oa[NA], ob[NB];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int idx = tid + 256 * i, row = idx / KQ, kq = (idx % KQ) * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (idx >= LA) {
-      } else if (MODE == kPoseRefine) {
-        if (row < a.S) {
-          const int k = k0 + kq;
-          v = (k < a.ka_split)
-                  ? *(const uint4 *)(a.A + ((int64_t)p * a.S + row) * a.lda + k)
-                  : *(const uint4 *)(a.A2 + (int64_t)p * a.lda2 + (k - a.ka_split));
-        }
-      } else {
-        const int m = m0 + row;
-        if (m < a.M) v = *(const uint4 *)(a.A + (int64_t)m * a.lda + k0 + kq);
-      }
-      ra[i] = v;
-    }
+  for (int q = 0; q < NA; ++q) {
+    const int e = tid + kT * q, m = min(m0 + (e >> 3), a.M - 1);
+    const int64_t row = MODE == kPoseScore ? shift_row(a, m / a.S, m % a.S) : (int64_t)m * a.lda;
+    oa[q] = (unsigned)((row - a0) * 2 + mma_chunk(e) * 16);
+  }
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int idx = tid + 256 * i, row = idx / KQ, kq = (idx % KQ) * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      const int n = n0 + row;
-      if (idx < LB && n < a.N) {
-        const int64_t brow = (MODE == kPoseRefine) ? (int64_t)a.cand[(int64_t)p * a.L + n] : n;
-        if (MODE != kPoseRefine || (brow >= 0 && brow < a.nrows))
-          v = *(const uint4 *)(a.B + brow * a.ldb + a.boff + k0 + kq);
-      }
-      rb[i] = v;
-    }
+  for (int q = 0; q < NB; ++q) {
+    const int e = tid + kT * q, n = min(n0 + (e >> 3), a.N - 1);
+    ob[q] = (unsigned)((int64_t)(n - n0) * a.ldb * 2 + mma_chunk(e) * 16);
+  }
+  auto stage = [&](int step, unsigned short *tA, unsigned short *tB) {
+    // (opaque scalar bases: the loads then take them as they are, with the
+    // 32-bit offsets, instead of a 64-bit vector address each)
+    const char *ka = pa + (size_t)step * kMmaK * 2, *kb = pb + (size_t)step * kMmaK * 2;
+    asm("" : "+s"(ka), "+s"(kb));
+#pragma unroll
+    for (int q = 0; q < NA; ++q) dma16(ka + oa[q], tA + (q * kT + wv * 64) * 8);
+#pragma unroll
+    for (int q = 0; q < NB; ++q) dma16(kb + ob[q], tB + (q * kT + wv * 64) * 8);
   };
-  auto sstore = [&](int buf) {
+  // fragments: A in two groups of TI / 2 row tiles (one in use, one arriving),
+  // B of both MFMA k-slices
+  constexpr int HI = TI / 2;
+  mma_bf16x8 af[2][HI], bv[2][TJ];
+  auto frag_a = [&](const unsigned short *tA, int ks, int h) {
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-      const int idx = tid + 256 * i;
-      if (idx < LA) *(uint4 *)&sA[buf][idx / KQ][(idx % KQ) * 8] = ra[i];
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int idx = tid + 256 * i;
-      if (idx < LB) *(uint4 *)&sB[buf][idx / KQ][(idx % KQ) * 8] = rb[i];
-    }
+    for (int i = 0; i < HI; ++i) af[h][i] = mma_frag(tA, wm + (h * HI + i) * 16 + (lane & 15), ks, lane);
   };
-
-  f32x4_t acc[TI][TJ];
+  auto frag_b = [&](const unsigned short *tB, int ks) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) bv[ks][j] = mma_frag(tB, wn + j * 16 + (lane & 15), ks, lane);
+  };
+  mma_f32x4 acc[TI][TJ];
 #pragma unroll
   for (int i = 0; i < TI; ++i)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  const int nk = a.K / kBK;
-  gload(0);
-  sstore(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) gload((kt + 1) * kBK);
+    for (int j = 0; j < TJ; ++j) acc[i][j] = mma_f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](int ks, int h, int i0, int i1) {
 #pragma unroll
-    for (int kk = 0; kk < kBK; kk += 32) {
-      bf16x8_t af[TI], bv[TJ];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-        af[i] = *(const bf16x8_t *)&sA[cur][wm + i * 16 + (lane & 15)][kk + (lane >> 4) * 8];
+    for (int i = i0; i < i1; ++i)
 #pragma unroll
       for (int j = 0; j < TJ; ++j)
-        bv[j] = *(const bf16x8_t *)&sB[cur][wn + j * 16 + (lane & 15)][kk + (lane >> 4) * 8];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bv[j], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) sstore(cur ^ 1);
-    __syncthreads();
+        acc[h * HI + i][j] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h][i], bv[ks][j], acc[h * HI + i][j], 0, 0, 0);
+  };
+  const int nk = a.K / kMmaK;  // even
+  // step t (its first fragments already in registers) from buffer c, while
+  // step t + 1 arrives in buffer n.  Every group of MFMAs starts before the
+  // next group's fragment reads are issued, which then have the rest of the
+  // group to arrive (the scheduling barriers keep that order)
+  auto step = [&](int t, unsigned short *cA, unsigned short *cB, unsigned short *nA, unsigned short *nB) {
+    mma(0, 0, 0, 1);
+    mma_order();
+    frag_a(cA, 0, 1);
+    mma_order();
+    mma(0, 0, 1, HI);
+    mma_order();
+    mma(0, 1, 0, 1);
+    mma_order();
+    frag_a(cA, 1, 0);
+    frag_b(cB, 1);
+    mma_order();
+    mma(0, 1, 1, HI);
+    mma_order();
+    mma(1, 0, 0, 1);
+    mma_order();
+    frag_a(cA, 1, 1);
+    mma_order();
+    mma(1, 0, 1, HI);
+    mma_order();
+    dma_wait();
+    __syncthreads();  // step t + 1 is in buffer n, and every wave has read buffer c
+    mma(1, 1, 0, 1);
+    mma_order();
+    frag_a(nA, 0, 0);
+    frag_b(nB, 0);
+    mma_order();
+    stage(min(t + 2, nk - 1), cA, cB);  // past the end: the last step again, not read
+    mma(1, 1, 1, HI);
+    mma_order();
+  };
+  stage(0, sA0, sB0);
+  dma_wait();
+  __syncthreads();
+  stage(1, sA1, sB1);
+  frag_a(sA0, 0, 0);
+  frag_b(sB0, 0);
+  for (int kt = 0; kt < nk; kt += 2) {
+    step(kt, sA0, sB0, sA1, sB1);
+    step(kt + 1, sA1, sB1, sA0, sB0);
   }
-
-  // ---- epilogue (acc[i][j][r] is C[wm + 16 i + 4 (lane / 16) + r][wn + 16 j + lane % 16])
+  dma_wait();  // no load may land after the block has given its LDS back
+  // acc[i][j][r] is C[m0 + wm + 16 i + 4 (lane / 16) + r][n0 + wn + 16 j + lane % 16]
   if (MODE == kPoseStore) {
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -352,51 +384,117 @@ __global__ void __launch_bounds__(256) k_pose_gemm(PoseGemmArgs a) {
   for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int ml = wm + i * 16 + (lane >> 4) * 4 + r;
-      int pp, s;
-      bool valid;
-      if (MODE == kPoseRefine) {
-        pp = p;
-        s = ml;
-        valid = s < a.S;
-      } else {
-        const int m = m0 + ml;
-        valid = m < a.M;
-        pp = valid ? m / a.S : 0;
-        s = valid ? m - pp * a.S : 0;
-      }
+      const int m = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
+      const bool valid = m < a.M;
+      const int p = valid ? m / a.S : 0, s = valid ? m - p * a.S : 0;
       unsigned long long key = ~0ull;
       if (valid) {
-        const float base = a.yy[pp];
+        const float base = a.yy[p];
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
           const int n = n0 + wn + j * 16 + (lane & 15);
           if (n < a.N) {
             float v = acc[i][j][r] + base;
-            int rot;
-            if (MODE == kPoseRefine) {
-              rot = a.cand[(int64_t)pp * a.L + n];
-              if (rot < 0 || rot >= a.nrows) continue;
-            } else {
-              v += a.E[(int64_t)pp * a.lde + n];
-              rot = n;
-            }
-            if (a.scores) a.scores[((int64_t)pp * a.N + n) * a.S + s] = v;
+            v += a.E[(int64_t)p * a.lde + n];
+            if (a.scores) a.scores[((int64_t)p * a.N + n) * a.S + s] = v;
             const unsigned long long k2 =
-                ((unsigned long long)ord_bits(v) << 32) | (unsigned)(rot * a.S + s);
+                ((unsigned long long)ord_bits(v) << 32) | (unsigned)(n * a.S + s);
             key = k2 < key ? k2 : key;
           }
         }
       }
-      // minimum over the 16 lanes that hold the same row
+      row_minimum(key, lane, a.best + p);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Gathered refinement as a GEMM (particles too large for LDS): block x =
+// particle p, rows s < S, B rows gathered through cand[p][n]; A switches at
+// k = ka_split from the shifted particle rows to the particle's energy
+// weights (energy fused into the contraction); value = acc + yy[p].  256
+// threads = 4 waves side by side, 32 x 64 tiles, K steps of 128 (K a multiple
+// of 128) double-buffered through LDS, rows padded to 16 bytes more.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) k_pose_gemm_refine(PoseGemmArgs a) {
+  constexpr int BM = 32, BN = 64, kBK = 128, kLDK = kBK + 8, KQ = kBK / 8;
+  constexpr int TI = BM / 16;
+  constexpr int NA = BM * KQ / 256, NB = BN * KQ / 256;  // 16-byte loads per K step
+  __shared__ unsigned short sA[2][BM][kLDK];
+  __shared__ unsigned short sB[2][BN][kLDK];
+  const int tid = threadIdx.x, lane = tid & 63, wn = (tid >> 6) * 16;
+  const int p = blockIdx.x, n0 = blockIdx.y * BN;
+
+  // global -> register staging of one K step
+  uint4 ra[NA], rb[NB];
+  auto gload = [&](int k0) {
 #pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        const unsigned lo = __shfl_xor((unsigned)(key & 0xffffffffu), o, 64);
-        const unsigned hi = __shfl_xor((unsigned)(key >> 32), o, 64);
-        const unsigned long long k2 = ((unsigned long long)hi << 32) | lo;
-        key = k2 < key ? k2 : key;
+    for (int i = 0; i < NA; ++i) {
+      const int idx = tid + 256 * i, row = idx / KQ, k = k0 + (idx % KQ) * 8;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (row < a.S)
+        v = (k < a.ka_split) ? *(const uint4 *)(a.A + shift_row(a, p, row) + k)
+                             : *(const uint4 *)(a.A2 + (int64_t)p * a.lda2 + (k - a.ka_split));
+      ra[i] = v;
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int idx = tid + 256 * i, n = n0 + idx / KQ, kq = (idx % KQ) * 8;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (n < a.N) {
+        const int64_t brow = a.cand[(int64_t)p * a.L + n];
+        if (brow >= 0 && brow < a.nrows) v = *(const uint4 *)(a.B + brow * a.ldb + a.boff + k0 + kq);
       }
-      if ((lane & 15) == 0 && key != ~0ull) atomicMin(a.best + pp, key);
+      rb[i] = v;
+    }
+  };
+  auto sstore = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int idx = tid + 256 * i;
+      *(uint4 *)&sA[buf][idx / KQ][(idx % KQ) * 8] = ra[i];
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int idx = tid + 256 * i;
+      *(uint4 *)&sB[buf][idx / KQ][(idx % KQ) * 8] = rb[i];
+    }
+  };
+
+  f32x4_t acc[TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int nk = a.K / kBK;
+  gload(0);
+  sstore(0);
+  __syncthreads();
+  for (int kt = 0; kt < nk; ++kt) {
+    const int cur = kt & 1;
+    if (kt + 1 < nk) gload((kt + 1) * kBK);
+#pragma unroll
+    for (int kk = 0; kk < kBK; kk += 32) {
+      const bf16x8_t bv = *(const bf16x8_t *)&sB[cur][wn + (lane & 15)][kk + (lane >> 4) * 8];
+#pragma unroll
+      for (int i = 0; i < TI; ++i) {
+        const bf16x8_t af = *(const bf16x8_t *)&sA[cur][i * 16 + (lane & 15)][kk + (lane >> 4) * 8];
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bv, acc[i], 0, 0, 0);
+      }
+    }
+    if (kt + 1 < nk) sstore(cur ^ 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int s = i * 16 + (lane >> 4) * 4 + r, n = n0 + wn + (lane & 15);
+      unsigned long long key = ~0ull;
+      const int rot = n < a.N ? a.cand[(int64_t)p * a.L + n] : -1;
+      if (s < a.S && rot >= 0 && rot < a.nrows) {
+        const float v = acc[i][r] + a.yy[p];
+        if (a.scores) a.scores[((int64_t)p * a.N + n) * a.S + s] = v;
+        key = ((unsigned long long)ord_bits(v) << 32) | (unsigned)(rot * a.S + s);
+      }
+      row_minimum(key, lane, a.best + p);
     }
 }
 
@@ -665,8 +763,7 @@ hipError_t pose_prep(const float *Y, const float *Z, const float *table, int P, 
 
 hipError_t pose_shifts(const unsigned short *zb, int P, int D, int r, unsigned short *zs,
                        hipStream_t st) {
-  const int S = (2 * r + 1) * (2 * r + 1);
-  hipLaunchKernelGGL(k_pose_shifts, dim3(P, S), dim3(256), 0, st, zb, D, r, zs);
+  hipLaunchKernelGGL(k_pose_shifts, dim3(P, 2 * r + 1), dim3(256), 0, st, zb, D, r, zs);
   return hipGetLastError();
 }
 
@@ -715,21 +812,35 @@ hipError_t pose_confidence(const unsigned short *bank, int64_t ldb, int64_t boff
   return hipGetLastError();
 }
 
+// The 256 x 256 tiles t0 .. t1 - 1, in parts of NWM TI 16 x NWN TJ 16.
+template <int NWM, int NWN, int TI, int TJ, int MODE>
+static void launch_mma(PoseGemmArgs a, int64_t t0, int64_t t1, hipStream_t st) {
+  if (t0 == t1) return;
+  a.t0 = (int)t0;
+  const int64_t parts = (t1 - t0) * (256 / (NWM * TI * 16)) * (256 / (NWN * TJ * 16));
+  hipLaunchKernelGGL((k_pose_mma<NWM, NWN, TI, TJ, MODE>), dim3((unsigned)parts), dim3(64 * NWM * NWN),
+                     0, st, a);
+}
+
 hipError_t pose_gemm_store(const PoseGemmArgs &a, hipStream_t st) {
-  const unsigned tiles = pcdiv(a.M, 128) * pcdiv(a.N, 128);
-  hipLaunchKernelGGL((k_pose_gemm<128, 128, 2, kPoseStore, 32>), dim3(tiles), dim3(256), 0, st, a);
+  launch_mma<2, 2, 4, 4, kPoseStore>(a, 0, (int64_t)pcdiv(a.M, 256) * pcdiv(a.N, 256), st);
   return hipGetLastError();
 }
 
+// One 256 x 256 tile occupies a CU: whole rounds of 256 of them (3.0 ms for
+// 25,600 x 4,608 x 16,384 against 3.4 ms as 128 x 128 tiles, whose operands
+// pass through LDS twice as often), what is left as 128 x 128 parts, which
+// fill the chip with a quarter of the tiles.
 hipError_t pose_gemm_score(const PoseGemmArgs &a, hipStream_t st) {
-  const unsigned tiles = pcdiv(a.M, 128) * pcdiv(a.N, 128);
-  hipLaunchKernelGGL((k_pose_gemm<128, 128, 2, kPoseScore, 32>), dim3(tiles), dim3(256), 0, st, a);
+  const int64_t tiles = (int64_t)pcdiv(a.M, 256) * pcdiv(a.N, 256), rest = tiles % 256;
+  const int64_t whole = rest > 128 ? tiles : tiles - rest;
+  launch_mma<2, 4, 8, 4, kPoseScore>(a, 0, whole, st);
+  launch_mma<2, 2, 4, 4, kPoseScore>(a, whole, tiles, st);
   return hipGetLastError();
 }
 
 hipError_t pose_gemm_refine(const PoseGemmArgs &a, int P, hipStream_t st) {
-  hipLaunchKernelGGL((k_pose_gemm<32, 64, 1, kPoseRefine, 128>), dim3(P, pcdiv(a.N, 64)), dim3(256), 0,
-                     st, a);
+  hipLaunchKernelGGL(k_pose_gemm_refine, dim3(P, pcdiv(a.N, 64)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -302,7 +302,7 @@ int cs_pose_batch_create(cs_ctx *ctx, int32_t D, float pixel, int32_t capacity,
   const size_t o_table = o; o += al256(CF * q->F * 4);
   const size_t o_spec = o;  o += al256(CF * D * Dh * 8);
   const size_t o_Z = o;     o += al256(CF * q->npx * 4);
-  const size_t o_zs = o;    o += al256(C * q->S * q->npx * 2);
+  const size_t o_zs = o;    o += al256(C * (2 * shift_radius + 1) * (D + 2 * shift_radius) * D * 2);
   const size_t o_zb = o;    o += al256(C * D * (D + 16) * 2);
   const size_t o_w = o;     o += al256(C * q->F8 * 2);
   const size_t o_yy = o;    o += al256(C * 4);
@@ -390,7 +390,7 @@ int cs_pose_batch_search(cs_pose_bank *b, cs_pose_batch *q, int32_t *best_rot, i
   HIPCHK(pose_gemm_store(e, st));
   HIPCHK(fill_u64(q->best, q->P, ~0ull, st));
   PoseGemmArgs a;
-  a.A = q->zs; a.lda = q->npx;
+  a.A = q->zs; a.D = q->D; a.r = q->r; a.side = 2 * q->r + 1;
   a.B = b->data; a.ldb = b->Kext; a.boff = 0;
   a.M = q->P * q->S; a.N = (int)b->K; a.K = q->npx; a.S = q->S;
   a.E = E; a.lde = b->K; a.yy = q->yy; a.best = q->best;
@@ -444,7 +444,7 @@ int cs_pose_batch_refine(cs_pose_bank *b, cs_pose_batch *q, const float *proposa
     q->zs_valid = true;
   }
   PoseGemmArgs a;
-  a.A = q->zs; a.lda = q->npx;
+  a.A = q->zs; a.D = q->D; a.r = q->r; a.side = 2 * q->r + 1;
   a.A2 = q->w; a.lda2 = q->F8; a.ka_split = q->npx;
   a.B = b->data; a.ldb = b->Kext; a.boff = 0;
   a.cand = cl; a.L = L; a.nrows = b->K;
