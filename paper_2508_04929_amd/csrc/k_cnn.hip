@@ -9,6 +9,8 @@
 // 32x32, K steps of 32 staged through LDS.  Operand tiles are gathered
 // straight from the activations (implicit im2col), 16 bytes per thread.
 #include "cs_cnn.hpp"
+#include "cs_internal.hpp"
+#include "cs_mma.hpp"
 
 namespace cs {
 
@@ -437,6 +439,215 @@ struct ConvWgradOp {
     part[((size_t)z * g.Cout + m) * 9 * g.Cin + n] = v;
   }
 };
+
+// ---------------------------------------------------------------------------
+// The same convolutions and data gradients with operand tiles loaded straight
+// into LDS (channels of a tap a multiple of 32: a K step of 32 stays within
+// one tap).  What bounds them is the latency of the gathered pixels, which
+// come from beyond L2 the first time: a ring of S tiles keeps S - 1 steps of
+// loads in flight.  Per step one counted wait and one barrier: the next
+// step's tile has arrived and every wave has read this step's, whose buffer
+// then takes the loads of step t + S; the next step's fragments are read
+// while this step's MFMAs run.
+//
+// The data gradient runs per parity class of the input pixel (iy & 1, ix & 1):
+// a stride-2 convolution gives only 1, 2, 2 and 4 of the nine taps a matching
+// output pixel, so a class contracts over its own taps alone, 9/4 taps per
+// pixel instead of 9 with three quarters of the products zero.  The steps left
+// out added exact zeros, so the sums keep their bits.
+//
+// MFMA rows are output channels and columns pixels, so that a lane holds four
+// consecutive channels of one pixel and stores them together.
+// ---------------------------------------------------------------------------
+struct ConvMma {
+  const bf16 *src, *w;  // forward: input, weights; data gradient: dout, transposed weights
+  const float *bias;    // forward (may be null)
+  const bf16 *mask;     // data gradient: input activation (may be null)
+  bf16 *out;
+  float *out32;         // may be null
+  int relu;
+  int Hs, Ws, C;        // source side and channels (contraction per tap)
+  int Hm, Wm;           // rows m = (b, y, x) of the GEMM: output pixels, or a quarter of the input's
+  int N;                // output channels
+  int M;
+};
+
+template <int NWM, int NWN, int TI, int TJ, int S, bool DGRAD>
+__global__ void __launch_bounds__(64 * NWM * NWN, 2) k_conv_mma(ConvMma a) {
+  constexpr int kT = 64 * NWM * NWN, BM = NWM * TI * 16, BN = NWN * TJ * 16;
+  constexpr int NA = BM * 4 / kT, NB = BN * 4 / kT;  // 16-byte pieces per thread and step
+  static_assert(NA * kT == BM * 4 && (NB * kT == BN * 4 || BN * 4 < kT) && S >= 3 && S <= 6, "tile shape");
+  // one array per step of the ring (A rows, then B rows): the compiler then
+  // knows that the fragment reads of one need not wait for the others' loads
+  constexpr int kTile = (BM + BN) * 32;
+  __shared__ __attribute__((aligned(1024))) bf16 s0[kTile], s1[kTile], s2[kTile];
+  __shared__ __attribute__((aligned(1024))) bf16 s3[S > 3 ? kTile : 8], s4[S > 4 ? kTile : 8], s5[S > 5 ? kTile : 8];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wv / NWN) * TI * 16, wn = (wv % NWN) * TJ * 16;
+  // an XCD runs one contiguous range of work: the column tiles and parity
+  // classes of a row tile, which read the same pixels, next to each other
+  const int Nt = (a.N + BN - 1) / BN;
+  int t = xcd_work(blockIdx.x, gridDim.x);
+  const int n0 = t % Nt * BN;
+  t /= Nt;
+  const int py = DGRAD ? (t >> 1) & 1 : 0, px = DGRAD ? t & 1 : 0;
+  const int m0 = (DGRAD ? t >> 2 : t) * BM;
+  const int b0 = m0 / (a.Hm * a.Wm);
+  const int64_t s_img = (int64_t)a.Hs * a.Ws * a.C, s_end = (int64_t)(a.M / (a.Hm * a.Wm)) * s_img;
+  const DmaSrc src = dma_src(a.src + b0 * s_img, (s_end - b0 * s_img) * 2);
+  // per piece: byte offset of its row's first tap from src, and whether the
+  // row's first tap row / column lies outside the image
+  int oa[NA];
+  bool oy[NA], ox[NA];
+#pragma unroll
+  for (int q = 0; q < NA; ++q) {
+    const int e = tid + kT * q, m = min(m0 + (e >> 2), a.M - 1);
+    const int x = m % a.Wm, r = m / a.Wm, y = r % a.Hm, b = r / a.Hm - b0;
+    const int sy = DGRAD ? y : 2 * y - 1, sx = DGRAD ? x : 2 * x - 1;
+    oy[q] = DGRAD ? y + 1 == a.Hs : y == 0;
+    ox[q] = DGRAD ? x + 1 == a.Ws : x == 0;
+    oa[q] = ((b * a.Hs + sy) * a.Ws + sx) * a.C * 2 + mma_chunk32(e) * 16;
+  }
+  const DmaSrc wsrc = dma_src(a.w + (size_t)n0 * 9 * a.C, (int64_t)(a.N - n0) * 9 * a.C * 2);
+  constexpr int NB1 = NB ? NB : 1;
+  int ob[NB1];
+#pragma unroll
+  for (int q = 0; q < NB1; ++q) {
+    const int e = tid + kT * q, n = min(n0 + (e >> 2), a.N - 1) - n0;
+    ob[q] = n * 9 * a.C * 2 + mma_chunk32(e) * 16;
+  }
+  const bool wb = NB > 0 || wv * 64 < BN * 4;  // this wave loads weights
+  // taps in ascending order 3 dy + dx; a data gradient's class has dy, dx = 1
+  // on even rows and columns of the input, 0 then 2 on odd ones.  State of
+  // the step to stage next: tap, first channel, and the tap's byte offsets
+  int dy = DGRAD ? 1 - py : 0, dx = DGRAD ? 1 - px : 0, c0 = 0;
+  const int ntaps = DGRAD ? (1 + py) * (1 + px) : 9;
+  const int nk = ntaps * (a.C / 32);
+  auto stage = [&](bf16 *tile) {
+    // forward: source pixel (2 y - 1 + dy, 2 x - 1 + dx); data gradient: dout
+    // pixel (y + 1, ..) on tap 0, (y, ..) on taps 1 and 2
+    const int my = DGRAD ? (dy == 0) : dy, mx = DGRAD ? (dx == 0) : dx;
+    const int pa = ((my * a.Ws + mx) * a.C + c0) * 2, pb = ((3 * dy + dx) * a.C + c0) * 2;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const bool out = (dy == 0 && oy[q]) || (dx == 0 && ox[q]);
+      dma16(src, out ? kDmaZero : (unsigned)(oa[q] + pa), tile + (q * kT + wv * 64) * 8);
+    }
+    if (wb) {
+#pragma unroll
+      for (int q = 0; q < NB1; ++q)
+        dma16(wsrc, (unsigned)(ob[q] + pb), tile + BM * 32 + (q * kT + wv * 64) * 8);
+    }
+    // the next step; past the last tap the last step is staged again (not read)
+    // (selects, no branches: a step stays one block of code)
+    const int end_x = DGRAD ? 2 * px : 2, end_y = DGRAD ? 2 * py : 2, inc = DGRAD ? 2 : 1;
+    const bool in_tap = c0 + 32 < a.C, last = dx >= end_x && dy >= end_y, wrap = dx >= end_x;
+    const bool next_tap = !in_tap && !last;
+    c0 = in_tap ? c0 + 32 : last ? c0 : 0;
+    dy = next_tap && wrap ? dy + inc : dy;
+    dx = next_tap ? (wrap ? (DGRAD ? 1 - px : 0) : dx + inc) : dx;
+  };
+  mma_bf16x8 af[2][TI], bv[2][TJ];
+  auto frags = [&](const bf16 *tile, int h) {
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) bv[h][j] = mma_frag32(tile + BM * 32, wn + j * 16 + (lane & 15), lane);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) af[h][i] = mma_frag32(tile, wm + i * 16 + (lane & 15), lane);
+  };
+  f32x4 acc[TI][TJ];
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](int h, int i0, int i1) {
+#pragma unroll
+    for (int i = i0; i < i1; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[h][j], af[h][i], acc[i][j], 0, 0, 0);
+  };
+  constexpr int kLoads = NA + NB1;  // of a wave that loads weights; others have fewer in flight
+  // one step: its fragments are in registers (set h) and were read from
+  // `cur`, the next step's tile is `nxt`
+  auto step = [&](bf16 *cur, const bf16 *nxt, int h) {
+    dma_wait_but<(S - 2) * (NB ? kLoads : NA)>();  // the next step's loads have arrived
+    mma(h, 0, 1);
+    mma_order();
+    stage(cur);
+    frags(nxt, h ^ 1);
+    mma_order();
+    mma(h, 1, TI);
+    mma_order();
+  };
+  bf16 *const ring[6] = {s0, s1, s2, s3, s4, s5};
+#pragma unroll
+  for (int u = 0; u < S; ++u) stage(ring[u]);
+  dma_wait_but<(S - 1) * (NB ? kLoads : NA)>();
+  frags(ring[0], 0);
+  // (even: the fragment sets alternate; several rounds of the ring, as the
+  // compiler's count starts anew, with a longer wait, where the loop closes)
+  constexpr int kUnroll = S % 2 ? 4 * S : 3 * S;
+  for (int kt = 0;; kt += kUnroll) {
+    bool more = true;
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      step(ring[u % S], ring[(u + 1) % S], u & 1);
+      // (a mark of its own per step: equal steps merged into one block would
+      // hide from the compiler which array each accesses)
+      asm volatile("; step %0" ::"n"(u));
+      if (kt + u + 1 >= nk) {
+        more = false;
+        break;
+      }
+    }
+    if (!more) break;
+  }
+  dma_wait_but<0>();  // no load may land after the block has given its LDS back
+  // acc[i][j][r]: channel n0 + wn + 16 j + 4 (lane / 16) + r of pixel row
+  // m0 + wm + 16 i + lane % 16 (N is a multiple of 8: four channels are in or out together)
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    const int m = m0 + wm + i * 16 + (lane & 15);
+    if (m >= a.M) continue;
+    size_t pix = m;
+    if (DGRAD) {
+      const int x = m % a.Wm, r = m / a.Wm, y = r % a.Hm, b = r / a.Hm;
+      pix = ((size_t)b * 2 * a.Hm + 2 * y + py) * 2 * a.Wm + 2 * x + px;
+    }
+    uint2 act[TJ];
+    if (DGRAD && a.mask) {
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        const int n = min(n0 + wn + j * 16 + (lane >> 4) * 4, a.N - 4);
+        act[j] = *(const uint2 *)(a.mask + pix * a.N + n);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int n = n0 + wn + j * 16 + (lane >> 4) * 4;
+      if (n >= a.N) continue;
+      float v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        v[r] = acc[i][j][r];
+        if (DGRAD) {
+          if (a.mask) {
+            const unsigned w = r < 2 ? act[j].x : act[j].y;
+            if (!(bf2f((bf16)(r & 1 ? w >> 16 : w)) > 0.f)) v[r] = 0.f;
+          }
+        } else {
+          v[r] += a.bias ? a.bias[n + r] : 0.f;
+          if (a.relu) v[r] = fmaxf(v[r], 0.f);
+        }
+      }
+      if (a.out32) *(float4 *)(a.out32 + pix * a.N + n) = make_float4(v[0], v[1], v[2], v[3]);
+      uint2 o;
+      o.x = (unsigned)f2bf(v[0]) | (unsigned)f2bf(v[1]) << 16;
+      o.y = (unsigned)f2bf(v[2]) | (unsigned)f2bf(v[3]) << 16;
+      *(uint2 *)(a.out + pix * a.N + n) = o;
+    }
+  }
+}
 
 // ---------------------------------------------------------------------------
 // Linear layers: y[b][o] = sum_i W[o][i] x[b][i] + bias[o]
@@ -1001,6 +1212,37 @@ static hipError_t launch_gemm(const Op &op, int M, int N, int K, int splits, hip
   return hipGetLastError();
 }
 
+// The direct-to-LDS kernel takes a multiple of 32 channels per tap, as long as
+// 32-bit byte offsets reach across the images of one tile; other channel
+// counts go to k_gemm.
+static bool conv_mma_ok(int C, int B, int Hi, int Wi) {
+  return C % 32 == 0 && (int64_t)B * Hi * Wi < ((int64_t)1 << 31) &&
+         (int64_t)Hi * Wi * C * 2 + 512 * (int64_t)C * 8 < ((int64_t)1 << 30);
+}
+
+template <int NWM, int NWN, int TI, int TJ, int S, bool DGRAD>
+static void launch_conv_tile(const ConvMma &a, hipStream_t st) {
+  const unsigned tiles = cdiv_(a.M, NWM * TI * 16) * cdiv_(a.N, NWN * TJ * 16) * (DGRAD ? 4 : 1);
+  hipLaunchKernelGGL((k_conv_mma<NWM, NWN, TI, TJ, S, DGRAD>), dim3(tiles), dim3(64 * NWM * NWN), 0, st, a);
+}
+
+template <bool DGRAD>
+static hipError_t launch_conv_mma(const ConvMma &a, hipStream_t st) {
+  const int cls = DGRAD ? 4 : 1;
+  auto tiles = [&](int bm, int bn) { return (int64_t)cdiv_(a.M, bm) * cdiv_(a.N, bn) * cls; };
+  if (a.N > 64 && tiles(256, 128) >= 256)
+    launch_conv_tile<4, 2, 4, 4, 6, DGRAD>(a, st);
+  else if (a.N > 64 && tiles(128, 128) >= 256)
+    launch_conv_tile<2, 2, 4, 4, 5, DGRAD>(a, st);
+  else if (a.N > 32 && a.N <= 64 && tiles(128, 64) >= 512)
+    launch_conv_tile<2, 2, 4, 2, 6, DGRAD>(a, st);
+  else if (a.N <= 32 && tiles(256, 32) >= 512)
+    launch_conv_tile<4, 1, 4, 2, 4, DGRAD>(a, st);
+  else
+    launch_conv_tile<2, 2, 2, 2, 6, DGRAD>(a, st);
+  return hipGetLastError();
+}
+
 int wgrad_splits(int M, int N, int K) {
   const int tiles = (int)(cdiv_(M, 64) * cdiv_(N, 64));
   int s = (512 + tiles - 1) / tiles;
@@ -1015,6 +1257,13 @@ hipError_t conv_fwd(const bf16 *in, const bf16 *w, const float *bias, int B, int
     hipLaunchKernelGGL(k_conv1_fwd, dim3(cdiv_(np, 64)), dim3(256), 0, st, in, w, bias, B, Hi, Wi,
                        Cout, relu, out, out32);
     return hipGetLastError();
+  }
+  if (conv_mma_ok(Cin, B, Hi, Wi)) {
+    ConvMma a{};
+    a.src = in; a.w = w; a.bias = bias; a.out = out; a.out32 = out32; a.relu = relu;
+    a.Hs = Hi; a.Ws = Wi; a.C = Cin; a.Hm = Hi / 2; a.Wm = Wi / 2; a.N = Cout;
+    a.M = B * (Hi / 2) * (Wi / 2);
+    return launch_conv_mma<false>(a, st);
   }
   ConvFwdOp op;
   op.g = {B, Hi, Wi, Cin, Hi / 2, Wi / 2, Cout};
@@ -1034,6 +1283,13 @@ hipError_t conv12_fwd(const bf16 *in0, const bf16 *w1, const float *b1, const bf
 
 hipError_t conv_dgrad(const bf16 *dout, const bf16 *wt, const bf16 *act_in, int B, int Hi, int Wi,
                       int Cin, int Cout, bf16 *din, float *din32, hipStream_t st) {
+  if (conv_mma_ok(Cout, B, Hi, Wi)) {
+    ConvMma a{};
+    a.src = dout; a.w = wt; a.mask = act_in; a.out = din; a.out32 = din32;
+    a.Hs = a.Hm = Hi / 2; a.Ws = a.Wm = Wi / 2; a.C = Cout; a.N = Cin;
+    a.M = B * (Hi / 2) * (Wi / 2);
+    return launch_conv_mma<true>(a, st);
+  }
   ConvDgradOp op;
   op.g = {B, Hi, Wi, Cin, Hi / 2, Wi / 2, Cout};
   op.tap_uniform = Cout % BK == 0;

@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(64 * NWM * NWN, 2) k_pose_mma(PoseGemmArgs a) 
   // 32-bit byte offsets of this thread's pieces from the tile's first rows
   // (rows past the end repeat the last one; their results are not used)
   const int64_t a0 = MODE == kPoseScore ? shift_row(a, m0 / a.S, (a.side - 1) * a.side) : (int64_t)m0 * a.lda;
-  const char *pa = (const char *)(a.A + a0), *pb = (const char *)(a.B + (int64_t)n0 * a.ldb + a.boff);
+  const DmaSrc pa = dma_src(a.A + a0, kDmaMax), pb = dma_src(a.B + (int64_t)n0 * a.ldb + a.boff, kDmaMax);
   unsigned oa[NA], ob[NB];
 #pragma unroll
   for (int q = 0; q < NA; ++q) {
@@ -285,14 +285,11 @@ __global__ void __launch_bounds__(64 * NWM * NWN, 2) k_pose_mma(PoseGemmArgs a) 
     ob[q] = (unsigned)((int64_t)(n - n0) * a.ldb * 2 + mma_chunk(e) * 16);
   }
   auto stage = [&](int step, unsigned short *tA, unsigned short *tB) {
-    // (opaque scalar bases: the loads then take them as they are, with the
-    // 32-bit offsets, instead of a 64-bit vector address each)
-    const char *ka = pa + (size_t)step * kMmaK * 2, *kb = pb + (size_t)step * kMmaK * 2;
-    asm("" : "+s"(ka), "+s"(kb));
+    const unsigned k0 = (unsigned)step * kMmaK * 2;
 #pragma unroll
-    for (int q = 0; q < NA; ++q) dma16(ka + oa[q], tA + (q * kT + wv * 64) * 8);
+    for (int q = 0; q < NA; ++q) dma16(pa, k0 + oa[q], tA + (q * kT + wv * 64) * 8);
 #pragma unroll
-    for (int q = 0; q < NB; ++q) dma16(kb + ob[q], tB + (q * kT + wv * 64) * 8);
+    for (int q = 0; q < NB; ++q) dma16(pb, k0 + ob[q], tB + (q * kT + wv * 64) * 8);
   };
   // fragments: A in two groups of TI / 2 row tiles (one in use, one arriving),
   // B of both MFMA k-slices
