@@ -41,8 +41,8 @@ struct cs_cnn {
   std::vector<bf16 *> act;   // act[0] input, act[l + 1] output of layer l
   std::vector<bf16 *> dact;  // dact[l + 1] gradient of the pre-activation of layer l
   float *out8 = nullptr;
-  float *part = nullptr;
-  size_t part_cap = 0;
+  float *part = nullptr;  // partial sums of every layer's gradients, summed at the end of a step
+  std::vector<size_t> part_off;  // start of each layer's partials; back(): total
   float *loss_part = nullptr;
   int64_t step = 0;
   int last_B = 0;
@@ -201,8 +201,12 @@ int cs_cnn_create(cs_ctx *ctx, int32_t D, int32_t max_batch, uint64_t seed, cs_c
     net->dact.push_back(d);
   }
   rc |= alloc((size_t)max_batch * 8 * 4, (void **)&net->out8);
-  net->part_cap = (size_t)1 << 23;
-  rc |= alloc(net->part_cap * 4, (void **)&net->part);
+  net->part_off.push_back(0);
+  for (auto &L : net->layers)
+    net->part_off.push_back(net->part_off.back() +
+                            al(L.conv ? conv_wgrad_part(max_batch, L.Hi, L.Hi, L.Cin, L.Cout, true)
+                                      : lin_wgrad_part(max_batch, L.In, L.Out)));
+  rc |= alloc(net->part_off.back() * 4, (void **)&net->part);
   rc |= alloc(((size_t)max_batch / 256 + 2) * 4, (void **)&net->loss_part);
   if (rc) {
     for (void *p : net->allocs) (void)hipFree(p);
@@ -306,26 +310,31 @@ int cs_cnn_train_step(cs_cnn *net, const float *images, const float *rot_target,
   HIPCHK(head_loss(net->out8, rot_target, shift_target, B, lambda, net->loss_part,
                    net->dact[nl], nullptr, st));
   HIPCHK(sum_into(net->loss_part, (B + 255) / 256, loss, st));
-  // backward, last layer first
+  // backward, last layer first; the sums over partials of all layers follow
+  // in one launch
+  std::vector<ReduceJob> jobs;
   for (int l = nl - 1; l >= 0; --l) {
     const Layer &L = net->layers[l];
     bf16 *dy = net->dact[l + 1];
     float *gw = net->grad + L.w_off, *gb = net->grad + L.b_off;
+    float *part = net->part + net->part_off[l];
+    const size_t cap = net->part_off[l + 1] - net->part_off[l];
+    ReduceJob j[2];
     if (L.conv) {
-      const int Ho = L.Hi / 2;
-      HIPCHK(conv_wgrad(dy, net->act[l], B, L.Hi, L.Hi, L.Cin, L.Cout, net->part, net->part_cap, gw, st));
-      HIPCHK(colsum(dy, B * Ho * Ho, L.Cout, net->part, net->part_cap, gb, st));
+      HIPCHK(conv_wgrad(dy, net->act[l], B, L.Hi, L.Hi, L.Cin, L.Cout, part, cap, gw, gb, j, st));
       if (l > 0)
         HIPCHK(conv_dgrad(dy, net->wbuf + L.wt_off, net->act[l], B, L.Hi, L.Hi, L.Cin, L.Cout,
                           net->dact[l], nullptr, st));
     } else {
-      HIPCHK(lin_wgrad(dy, net->act[l], B, L.In, L.Out, net->part, net->part_cap, gw, st));
-      HIPCHK(colsum(dy, B, L.Out, net->part, net->part_cap, gb, st));
+      HIPCHK(lin_wgrad(dy, net->act[l], B, L.In, L.Out, part, cap, gw, gb, j, st));
       HIPCHK(lin_dgrad(dy, net->wbuf + L.wt_off, net->act[l], B, L.In, L.Out, net->dact[l], nullptr, st));
     }
+    for (ReduceJob &r : j) {
+      if (grads_out && r.n) r.out2 = grads_out + (r.out - net->grad);
+      jobs.push_back(r);
+    }
   }
-  if (grads_out)
-    HIPCHK(hipMemcpyAsync(grads_out, net->grad, net->nparam * 4, hipMemcpyDeviceToDevice, st));
+  HIPCHK(reduce_parts(jobs.data(), (int)jobs.size(), st));
   if (apply_update) {
     net->step += 1;
     rc = cs_adam_step(ctx, net->param, net->grad, net->adam_m, net->adam_v, net->nparam, net->step,
@@ -392,11 +401,13 @@ int cs_bf16_conv3x3s2_wgrad(cs_ctx *ctx, const uint16_t *dout, const uint16_t *i
       (Cin != 1 && Cin % 8) || (Cin == 1 && Cout > 32))
     return fail(ctx, CS_ERR_INVALID_ARG, "bad conv wgrad arguments");
   HIPCHK(hipSetDevice(ctx->device));
-  const size_t cap = (size_t)1 << 23;
+  const size_t cap = conv_wgrad_part(B, H, W, Cin, Cout, (((uintptr_t)dout | (uintptr_t)in) & 15) == 0);
   int rc = ensure_aux(ctx, cap * 4);
   if (rc) return rc;
+  ReduceJob j[2];
   HIPCHK(conv_wgrad((const bf16 *)dout, (const bf16 *)in, B, H, W, Cin, Cout, (float *)ctx->aux, cap,
-                    dw, (hipStream_t)stream));
+                    dw, nullptr, j, (hipStream_t)stream));
+  HIPCHK(reduce_parts(j, 1, (hipStream_t)stream));
   return CS_OK;
 }
 
@@ -433,8 +444,10 @@ int cs_bf16_linear_wgrad(cs_ctx *ctx, const uint16_t *dy, const uint16_t *x, int
   const size_t cap = (size_t)1 << 23;
   int rc = ensure_aux(ctx, cap * 4);
   if (rc) return rc;
-  HIPCHK(lin_wgrad((const bf16 *)dy, (const bf16 *)x, B, In, Out, (float *)ctx->aux, cap, dw,
+  ReduceJob j[2];
+  HIPCHK(lin_wgrad((const bf16 *)dy, (const bf16 *)x, B, In, Out, (float *)ctx->aux, cap, dw, nullptr, j,
                    (hipStream_t)stream));
+  HIPCHK(reduce_parts(j, 1, (hipStream_t)stream));
   return CS_OK;
 }
 

@@ -21,17 +21,36 @@ hipError_t conv12_fwd(const bf16 *in0, const bf16 *w1, const float *b1, const bf
                       const float *b2, int B, int H0, bf16 *out, hipStream_t st);
 hipError_t conv_dgrad(const bf16 *dout, const bf16 *wt, const bf16 *act_in, int B, int Hi, int Wi,
                       int Cin, int Cout, bf16 *din, float *din32, hipStream_t st);
+// A sum of partials still to be taken: out[i] = sum_z part[z n + i], z <
+// splits (also stored to out2 when that is set).
+struct ReduceJob {
+  const float *part;
+  float *out, *out2;
+  int64_t n;
+  int splits, groups, block0;  // groups, block0: set by reduce_parts
+};
+constexpr int kReduceJobs = 16;
+struct ReduceJobs {
+  int count;
+  ReduceJob j[kReduceJobs];
+};
+hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st);
+// Weight gradient dw and (db not null) bias gradient db: writes partials into
+// part (conv_wgrad_part / lin_wgrad_part floats; aligned: both operands on
+// 16-byte boundaries) and returns the two sums that
+// reduce_parts has still to take from them.
+size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool aligned);
 hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout,
-                      float *part, size_t part_cap, float *dw, hipStream_t st);
+                      float *part, size_t part_cap, float *dw, float *db, ReduceJob jobs[2],
+                      hipStream_t st);
 // Linear layers, weights [Out][In] (dgrad takes [In][Out]); In, Out multiples of 8.
 hipError_t lin_fwd(const bf16 *x, const bf16 *w, const float *bias, int B, int In, int Out,
                    int relu, bf16 *y, float *y32, hipStream_t st);
 hipError_t lin_dgrad(const bf16 *dy, const bf16 *wt, const bf16 *x_act, int B, int In, int Out,
                      bf16 *dx, float *dx32, hipStream_t st);
+size_t lin_wgrad_part(int B, int In, int Out);
 hipError_t lin_wgrad(const bf16 *dy, const bf16 *x, int B, int In, int Out, float *part,
-                     size_t part_cap, float *dw, hipStream_t st);
-hipError_t colsum(const bf16 *g, int M, int N, float *part, size_t part_cap, float *out,
-                  hipStream_t st);
+                     size_t part_cap, float *dw, float *db, ReduceJob jobs[2], hipStream_t st);
 hipError_t standardize(const float *img, int B, int npx, bf16 *out, hipStream_t st);
 hipError_t head(const float *out8, int B, float *rot, float *shift, hipStream_t st);
 hipError_t head_loss(const float *out8, const float *rot_t, const float *shift_t, int B,

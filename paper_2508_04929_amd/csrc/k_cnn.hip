@@ -412,34 +412,6 @@ struct ConvDgradOp {
   __device__ int64_t ldo() const { return g.Cin; }
 };
 
-// weight gradient: M = Cout, N = 9 Cin (n = tap * Cin + ci), K = B Ho Wo
-// pixels; split-K partials part[z][M][N] (FP32).
-struct ConvWgradOp {
-  static constexpr bool kATrans = true, kBTrans = true;
-  ConvGeom g;
-  const bf16 *dout, *in;
-  float *part;
-  struct Row {};
-  // 8 consecutive output channels of pixel p
-  __device__ const uint4 *ptr_aT(int m, int p, bool &ok) const {
-    ok = true;
-    return (const uint4 *)&dout[(size_t)p * g.Cout + m];
-  }
-  // 8 consecutive (tap, ci) columns of the im2col row of pixel p
-  __device__ const uint4 *ptr_bT(int n, int p, bool &ok) const {
-    const int ox = p % g.Wo, t = p / g.Wo, oy = t % g.Ho, b = t / g.Ho;
-    const int tap = n / g.Cin, ci = n - tap * g.Cin;
-    const int iy = 2 * oy + tap / 3 - 1, ix = 2 * ox + tap % 3 - 1;
-    ok = iy >= 0 && iy < g.Hi && ix >= 0 && ix < g.Wi;
-    return (const uint4 *)(ok ? &in[(((size_t)b * g.Hi + iy) * g.Wi + ix) * g.Cin + ci] : in);
-  }
-  static constexpr bool kStaged = false;
-  __device__ float epi_in(int, int) const { return 0.f; }
-  __device__ void store(int m, int n, float v, int z, float) const {
-    part[((size_t)z * g.Cout + m) * 9 * g.Cin + n] = v;
-  }
-};
-
 // ---------------------------------------------------------------------------
 // The same convolutions and data gradients with operand tiles loaded straight
 // into LDS (channels of a tap a multiple of 32: a K step of 32 stays within
@@ -742,27 +714,374 @@ struct LinWgradOp {  // M = Out, N = In, K = B; split-K partials
   }
 };
 
-// Sum of split-K partials in a fixed order: out[i] = sum_z part[z][i].
-__global__ void __launch_bounds__(256)
-k_splitk_reduce(const float *part, int splits, int64_t n, float *out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  // loads issued 8 ahead, added in split order
-  float s = 0.f;
-  int z = 0;
-  for (; z + 8 <= splits; z += 8) {
-    float v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(z + u) * n + i];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) s += v[u];
-  }
-  for (; z < splits; ++z) s += part[(size_t)z * n + i];
-  out[i] = s;
+// ---------------------------------------------------------------------------
+// Weight gradient of a convolution: dW[co][tap Cin + ci] = sum over pixels of
+// dout[p][co] in[p moved by tap][ci], and the bias gradient with it.  Tiles of
+// 32 pixels come straight from the NHWC tensors into LDS as they lie (rows =
+// pixels); the MFMA fragments, which need consecutive pixels of one channel,
+// are read with the transposing LDS read (16 lanes take 4 pixels x 16 channels
+// and get 4 pixels of one channel each), instead of eight 2-byte LDS writes
+// per 16 bytes loaded.  Pixels are split over blockIdx.z; part[z][Cout][9 Cin],
+// part_b[z][Cout].
+//
+// In LDS a 256-byte line (one row of 128 channels, two of 64) holds eight
+// pieces of 16 channels, piece P of line l at place P ^ (l & 7) (^ (l & 3) for
+// two rows): the eight pixels that half a wave reads then lie in distinct
+// banks.  A fragment's pixels are 4 g .. 4 g + 3 and 16 + 4 g .. for lane group
+// g, the same for both operands.
+//
+// The five layers of a batch of 256 take 118 us (it was 415 with 64 x 64 tiles
+// transposed by 2-byte LDS writes); latency of the pixel gathers bounds them.
+// ---------------------------------------------------------------------------
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short mma_v4;
+
+// n / d for 0 <= n < 2^31 as mulhi(n, mul) >> sh.
+struct FastDiv {
+  unsigned mul;
+  int sh, d;
+};
+__device__ __forceinline__ int fdiv(int n, FastDiv f) {
+  return f.d == 1 ? n : (int)(__umulhi((unsigned)n, f.mul) >> f.sh);
 }
 
-// Column sums of an [M][N] BF16 gradient (bias gradients): partials over
-// row chunks part[chunk][N], then a fixed-order reduce.
+// 16-byte piece e of a tile of W channels (64 or 128): its pixel and 8-channel chunk.
+template <int W>
+__device__ __forceinline__ void px_piece(int e, int &row, int &chunk) {
+  const int line = e >> 4, pos = (e & 15) >> 1;
+  if (W == 128) {
+    row = line;
+    chunk = ((pos ^ (line & 7)) << 1) | (e & 1);
+  } else {
+    const int q = pos ^ (line & 3);
+    row = 2 * line + (q >> 2);
+    chunk = ((q & 3) << 1) | (e & 1);
+  }
+}
+// Fragment of channels c0 .. c0 + 15 (c0 a multiple of 16) over the tile's 32 pixels.
+template <int W>
+__device__ __forceinline__ mma_bf16x8 px_frag(const bf16 *tile, int c0, int lane) {
+  union {
+    mma_v4 v[2];
+    mma_bf16x8 f;
+  } u;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = 16 * h + 4 * (lane >> 4) + ((lane >> 2) & 3);
+    const int line = W == 128 ? row : row >> 1, P = W == 128 ? c0 / 16 : (row & 1) * 4 + c0 / 16;
+    const int pos = P ^ (line & (W == 128 ? 7 : 3));
+    u.v[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) mma_v4 *)(tile + line * 128 + pos * 16 + (lane & 3) * 4));
+  }
+  return u.f;
+}
+
+struct WgradMma {
+  const bf16 *dout, *in;
+  float *part, *part_b;
+  int Hi, Wi, Cin, Ho, Wo, Cout;
+  FastDiv div_w, div_h, div_c;  // by Wo, Ho, Cin
+  int K, kchunk;                // pixels, pixels per split (a multiple of 32)
+};
+
+template <int TI, int S>  // 2 x 2 waves, each TI x 4 MFMA tiles; ring of S tiles
+__global__ void __launch_bounds__(256, 2) k_wgrad_mma(WgradMma a) {
+  constexpr int BM = 32 * TI, BN = 128, TJ = 4;
+  constexpr int NA = BM / 64, NB = 2;  // 16-byte pieces per thread and step
+  constexpr int kTile = (BM + BN) * 32;
+  __shared__ __attribute__((aligned(1024))) bf16 s0[kTile], s1[kTile], s2[kTile], s3[kTile];
+  static_assert(S == 4, "ring");
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wv >> 1) * TI * 16, wn = (wv & 1) * TJ * 16;
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, N = 9 * a.Cin;
+  const int kb = blockIdx.z * a.kchunk, ke = min(a.K, kb + a.kchunk);
+  int ra[NA], oa[NA], rb[NB], dy[NB], dx[NB], ob[NB];
+#pragma unroll
+  for (int q = 0; q < NA; ++q) {
+    int chunk;
+    px_piece<BM>(tid + 256 * q, ra[q], chunk);
+    const int m = m0 + chunk * 8;
+    oa[q] = m < a.Cout ? (ra[q] * a.Cout + m) * 2 : -1;
+  }
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    int chunk;
+    px_piece<BN>(tid + 256 * q, rb[q], chunk);
+    const int n = n0 + chunk * 8, tap = fdiv(min(n, N - 8), a.div_c);
+    dy[q] = tap / 3;
+    dx[q] = tap - 3 * dy[q];
+    ob[q] = n < N ? (n - tap * a.Cin) * 2 : -1;
+  }
+  int p0 = kb;  // first pixel of the step to stage next
+  auto stage = [&](bf16 *tile) {
+    const DmaSrc sd = dma_src(a.dout + (size_t)p0 * a.Cout, kDmaMax);
+    // input offsets from the first row that the step's pixels can touch
+    const int t0 = fdiv(p0, a.div_w), f0 = fdiv(t0, a.div_h);
+    const int64_t row0 = max((int64_t)f0 * a.Hi + 2 * (t0 - f0 * a.Ho) - 1, (int64_t)0);
+    const DmaSrc si = dma_src(a.in + row0 * a.Wi * a.Cin, kDmaMax);
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const bool ok = oa[q] >= 0 && p0 + ra[q] < ke;
+      dma16(sd, ok ? (unsigned)oa[q] : kDmaZero, tile + (q * 256 + wv * 64) * 8);
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+      const int p = p0 + rb[q], t = fdiv(p, a.div_w), ox = p - t * a.Wo, b = fdiv(t, a.div_h);
+      const int iy = 2 * (t - b * a.Ho) + dy[q] - 1, ix = 2 * ox + dx[q] - 1;
+      const bool ok = ob[q] >= 0 && p < ke && iy >= 0 && ix >= 0;
+      const int row = (int)((int64_t)b * a.Hi + iy - row0);
+      const unsigned o = (unsigned)((row * a.Wi + ix) * a.Cin * 2 + ob[q]);
+      dma16(si, ok ? o : kDmaZero, tile + BM * 32 + (q * 256 + wv * 64) * 8);
+    }
+    p0 = p0 + 32 < ke ? p0 + 32 : p0;  // past the last step the last one again (not read)
+  };
+  const bool bias = blockIdx.y == 0 && (wv & 1) == 0;  // this wave also sums dout itself
+  mma_bf16x8 af[2][TI], bv[2][TJ], ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (short)0x3f80;
+  auto frags = [&](const bf16 *tile, int h) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) af[h][i] = px_frag<BM>(tile, wm + i * 16, lane);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) bv[h][j] = px_frag<BN>(tile + BM * 32, wn + j * 16, lane);
+  };
+  f32x4 acc[TI][TJ], accb[TI];
+#pragma unroll
+  for (int i = 0; i < TI; ++i) {
+    accb[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto step = [&](bf16 *cur, const bf16 *nxt, int h) {
+    dma_wait_but<(S - 2) * (NA + NB)>();
+    stage(cur);
+    frags(nxt, h ^ 1);
+    mma_order();
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h][i], bv[h][j], acc[i][j], 0, 0, 0);
+    }
+    if (bias) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+        accb[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h][i], ones, accb[i], 0, 0, 0);
+    }
+    mma_order();
+  };
+  bf16 *const ring[4] = {s0, s1, s2, s3};
+  const int nk = (ke - kb + 31) / 32;
+#pragma unroll
+  for (int u = 0; u < S; ++u) stage(ring[u]);
+  dma_wait_but<(S - 1) * (NA + NB)>();
+  frags(ring[0], 0);
+  constexpr int kUnroll = 2 * S;
+  for (int kt = 0;; kt += kUnroll) {
+    bool more = true;
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) {
+      step(ring[u % S], ring[(u + 1) % S], u & 1);
+      asm volatile("; step %0" ::"n"(u));  // keeps equal steps apart, as in k_conv_mma
+      if (kt + u + 1 >= nk) {
+        more = false;
+        break;
+      }
+    }
+    if (!more) break;
+  }
+  dma_wait_but<0>();  // no load may land after the block has given its LDS back
+  float *part = a.part + (size_t)blockIdx.z * a.Cout * N;
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + wm + i * 16 + (lane >> 4) * 4 + r;
+      if (m >= a.Cout) continue;
+      if (bias && (lane & 15) == 0) a.part_b[(size_t)blockIdx.z * a.Cout + m] = accb[i][r];
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        const int n = n0 + wn + j * 16 + (lane & 15);
+        if (n < N) part[(size_t)m * N + n] = acc[i][j][r];
+      }
+    }
+}
+
+// First layer (one input channel, 32 output channels, output rows a multiple
+// of 32 pixels): the same on 32 x 16 outputs, the columns being the nine taps
+// and, tenth, a constant 1 (the bias gradient).  Each wave runs its own range
+// of 32-pixel steps with a ring of its own, no barriers: dout pieces straight
+// into LDS, the input values of four consecutive outputs from one 16-byte load
+// (their even or odd elements by tap column).  HBM-bound by dout: 28 us for
+// 67 MB, 2.4 TB/s; 139 us with the operands staged as floats for the VALU.
+__global__ void __launch_bounds__(256)
+k_conv1_wgrad_mma(const bf16 *in, const bf16 *dpre, int B, int Hi, int Wi, float *part,
+                  float *part_b) {
+  constexpr int S = 4, kTile = 32 * 32;
+  __shared__ __attribute__((aligned(1024))) bf16 s0[4][kTile], s1[4][kTile], s2[4][kTile], s3[4][kTile];
+  __shared__ float red[4][32][10];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int Ho = Hi / 2, Wo = Wi / 2, spr = Wo / 32;  // steps per output row
+  const int64_t steps = (int64_t)B * Ho * spr, waves = (int64_t)gridDim.x * 4;
+  const int64_t w = (int64_t)blockIdx.x * 4 + wv;
+  const int64_t b0 = steps * w / waves, b1 = steps * (w + 1) / waves;
+  const int nk = (int)(b1 - b0);
+  const int tap = lane & 15, g = lane >> 4, dy = tap / 3, dx = tap - 3 * dy;
+  // pieces of a dout step: 64 bytes per pixel, 16-channel half P of pixel row
+  // at P ^ ((row >> 2) & 1)
+  unsigned off[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = lane + 64 * q, row = e >> 2, P = ((e >> 1) & 1) ^ ((row >> 2) & 1);
+    off[q] = (unsigned)(row * 64 + P * 32 + (e & 1) * 16);
+  }
+  int64_t sd = b0;
+  auto stage = [&](bf16 *tile) {
+    const DmaSrc src = dma_src(dpre + sd * 32 * 32, 2048);
+    dma16(src, off[0], tile);
+    dma16(src, off[1], tile + 64 * 8);
+    sd = sd + 1 < b1 ? sd + 1 : sd;  // past the last step the last one again (not read)
+  };
+  struct X {
+    uint4 v[2];
+    bf16 prev[2];
+    bool in;
+  };
+  int64_t sx = b0;
+  auto load_x = [&]() {
+    X x;
+    const int64_t row = sx / spr;
+    const int ox0 = (int)(sx - row * spr) * 32, oy = (int)(row % Ho);
+    const int64_t b = row / Ho;
+    const int iy = 2 * oy + dy - 1;
+    x.in = tap < 9 && iy >= 0;
+    const bf16 *line = in + (b * Hi + (x.in ? iy : 0)) * Wi;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = 2 * (ox0 + 16 * h + 4 * g);
+      x.v[h] = *(const uint4 *)(line + e);
+      const bf16 pv = line[max(e - 1, 0)];
+      x.prev[h] = e > 0 ? pv : (bf16)0;
+    }
+    sx = sx + 1 < b1 ? sx + 1 : sx;
+    return x;
+  };
+  auto xfrag = [&](const X &x) {
+    mma_bf16x8 f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const unsigned d[4] = {x.v[h].x, x.v[h].y, x.v[h].z, x.v[h].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned before = e ? d[e ? e - 1 : 0] >> 16 : x.prev[h];
+        unsigned v = dx == 0 ? before : dx == 1 ? d[e] & 0xffffu : d[e] >> 16;
+        v = x.in ? v : 0u;
+        f[4 * h + e] = (short)(tap == 9 ? 0x3f80u : v);
+      }
+    }
+    return f;
+  };
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  auto compute = [&](const bf16 *tile, const X &x) {
+    const mma_bf16x8 bx = xfrag(x);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      union {
+        mma_v4 v[2];
+        mma_bf16x8 f;
+      } u;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int row = 16 * h + 4 * g + ((lane >> 2) & 3);
+        const int P = c ^ ((row >> 2) & 1);
+        u.v[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) mma_v4 *)(tile + row * 32 + P * 16 + (lane & 3) * 4));
+      }
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(u.f, bx, acc[c], 0, 0, 0);
+    }
+  };
+  if (nk > 0) {
+    bf16 *const ring[4] = {s0[wv], s1[wv], s2[wv], s3[wv]};
+#pragma unroll
+    for (int u = 0; u < S - 1; ++u) stage(ring[u]);
+    X x = load_x();
+    for (int t0 = 0;; t0 += S) {
+      bool more = true;
+#pragma unroll
+      for (int u = 0; u < S; ++u) {
+        // the tile filled now was last read one step ago, by this wave
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        stage(ring[(u + S - 1) % S]);
+        const X nx = load_x();
+        // younger than this step's pieces: those of three steps and the input
+        // loads of two (four each); fewer are let through than may be
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        compute(ring[u], x);
+        x = nx;
+        asm volatile("; step %0" ::"n"(u));
+        if (t0 + u + 1 >= nk) {
+          more = false;
+          break;
+        }
+      }
+      if (!more) break;
+    }
+  }
+  dma_wait_but<0>();
+  // the four waves' sums, added in wave order
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (tap < 10) red[wv][16 * c + 4 * g + r][tap] = acc[c][r];
+  __syncthreads();
+  for (int i = threadIdx.x; i < 320; i += 256) {
+    const int co = i / 10, t = i % 10;
+    const float v = (red[0][co][t] + red[1][co][t]) + (red[2][co][t] + red[3][co][t]);
+    if (t < 9)
+      part[(size_t)blockIdx.x * 288 + co * 9 + t] = v;
+    else
+      part_b[(size_t)blockIdx.x * 32 + co] = v;
+  }
+}
+
+// Sums of partials in a fixed order, several arrays in one launch: job j has
+// out[i] = sum_z part[z n + i].  A block takes 256 / G outputs' columns with G
+// threads each (G grows with the number of partials), whose sums are added in
+// order.  A training step's 16 sums took 309 us in launches of their own, up
+// to 4,096 partials per thread one after the other; together they take 34 us,
+// about 60 MB read.
+__global__ void __launch_bounds__(256) k_reduce_parts(ReduceJobs jobs) {
+  __shared__ float red[256];
+  int j = 0;
+  while (j + 1 < jobs.count && (int)blockIdx.x >= jobs.j[j + 1].block0) ++j;
+  const ReduceJob J = jobs.j[j];
+  const int G = J.groups, W = 256 / G;
+  const int c = threadIdx.x % W, gz = threadIdx.x / W;
+  const int64_t i = (int64_t)((int)blockIdx.x - J.block0) * W + c;
+  float s = 0.f;
+  if (i < J.n) {
+    const int z1 = (int)((int64_t)J.splits * (gz + 1) / G);
+    int z = (int)((int64_t)J.splits * gz / G);
+    for (; z + 8 <= z1; z += 8) {  // eight loads in flight
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = J.part[(size_t)(z + u) * J.n + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; z < z1; ++z) s += J.part[(size_t)z * J.n + i];
+  }
+  red[threadIdx.x] = s;
+  __syncthreads();
+  if (gz == 0 && i < J.n) {
+    for (int k = 1; k < G; ++k) s += red[k * W + c];
+    J.out[i] = s;
+    if (J.out2) J.out2[i] = s;
+  }
+}
+
+// Column sums of an [M][N] BF16 gradient (bias gradient of a linear layer):
+// partials over row chunks, part[chunk][N].
 __global__ void __launch_bounds__(256)
 k_colsum(const bf16 *g, int M, int N, int rows_per_chunk, float *part) {
   const int n = blockIdx.x * 256 + threadIdx.x;
@@ -861,7 +1180,7 @@ k_conv1_fwd(const bf16 *in, const bf16 *w, const float *bias, int B, int Hi, int
 // chunk's pixels in pixel order.
 __global__ void __launch_bounds__(256)
 k_conv1_wgrad(const bf16 *in, const bf16 *dpre, int B, int Hi, int Wi, int Cout,
-              int pix_per_block, float *part) {
+              int pix_per_block, float *part, float *part_b) {
   __shared__ float xs[256][9];
   __shared__ float gs[256 * 32];  // Cout <= 32 gradient values per pixel
   const int Ho = Hi / 2, Wo = Wi / 2;
@@ -882,6 +1201,11 @@ k_conv1_wgrad(const bf16 *in, const bf16 *dpre, int B, int Hi, int Wi, int Cout,
     float s = 0.f;
     for (int pl = 0; pl < np; ++pl) s += gs[pl * Cout + co] * xs[pl][tap];
     part[(size_t)blockIdx.x * Cout * 9 + ct] = s;
+  }
+  for (int co = threadIdx.x; co < Cout; co += 256) {  // bias gradient
+    float s = 0.f;
+    for (int pl = 0; pl < np; ++pl) s += gs[pl * Cout + co];
+    part_b[(size_t)blockIdx.x * Cout + co] = s;
   }
 }
 
@@ -1025,16 +1349,32 @@ k_conv12_fwd(const bf16 *in0, const bf16 *w1, const float *b1, const bf16 *w2, c
 // ---------------------------------------------------------------------------
 // Input standardisation: x = (img - mean) / std per image, to BF16.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
+// One block of 1,024 threads per image, four pixels per load where the images
+// are 16-byte aligned (V = 4): at 256 threads and 4 bytes each image was one
+// chain of 64 dependent round trips.
+template <int V>
+__global__ void __launch_bounds__(1024)
 k_standardize(const float *img, int npx, bf16 *out) {
-  __shared__ double red[2][4];
+  __shared__ double red[2][16];
   const int b = blockIdx.x;
   const float *x = img + (size_t)b * npx;
   double s = 0.0, s2 = 0.0;
-  for (int i = threadIdx.x; i < npx; i += 256) {
-    const double v = x[i];
-    s += v;
-    s2 += v * v;
+  auto load = [&](int i, float *v) {
+    if (V == 4) {
+      const float4 f = *(const float4 *)(x + i);
+      v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+    } else {
+      v[0] = x[i];
+    }
+  };
+  for (int i = threadIdx.x * V; i < npx; i += 1024 * V) {
+    float v[4];
+    load(i, v);
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      s += (double)v[e];
+      s2 += (double)v[e] * v[e];
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -1046,10 +1386,26 @@ k_standardize(const float *img, int npx, bf16 *out) {
     red[1][threadIdx.x >> 6] = s2;
   }
   __syncthreads();
-  const double m = (red[0][0] + red[0][1] + red[0][2] + red[0][3]) / npx;
-  const double var = (red[1][0] + red[1][1] + red[1][2] + red[1][3]) / npx - m * m;
+  double t = 0.0, t2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    t += red[0][k];
+    t2 += red[1][k];
+  }
+  const double m = t / npx, var = t2 / npx - m * m;
   const float inv = var > 0.0 ? (float)(1.0 / sqrt(var)) : 1.f;
-  for (int i = threadIdx.x; i < npx; i += 256) out[(size_t)b * npx + i] = f2bf((x[i] - (float)m) * inv);
+  for (int i = threadIdx.x * V; i < npx; i += 1024 * V) {
+    float v[4];
+    load(i, v);
+    if (V == 4) {
+      uint2 o;
+      o.x = (unsigned)f2bf((v[0] - (float)m) * inv) | (unsigned)f2bf((v[1] - (float)m) * inv) << 16;
+      o.y = (unsigned)f2bf((v[2] - (float)m) * inv) | (unsigned)f2bf((v[3] - (float)m) * inv) << 16;
+      *(uint2 *)(out + (size_t)b * npx + i) = o;
+    } else {
+      out[(size_t)b * npx + i] = f2bf((v[0] - (float)m) * inv);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1297,33 +1653,102 @@ hipError_t conv_dgrad(const bf16 *dout, const bf16 *wt, const bf16 *act_in, int 
   return launch_gemm(op, B * Hi * Wi, Cin, 9 * Cout, 1, st);
 }
 
-hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout,
-                      float *part, size_t part_cap, float *dw, hipStream_t st) {
-  const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
-  if (Cin == 1) {
-    const int ppb = 256;
-    const unsigned blocks = cdiv_(npix, ppb);
-    if (Cout > 32 || (size_t)blocks * Cout * 9 > part_cap) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_conv1_wgrad, dim3(blocks), dim3(256), 0, st, in, dout, B, Hi, Wi, Cout,
-                       ppb, part);
-    hipLaunchKernelGGL(k_splitk_reduce, dim3(cdiv_(Cout * 9, 256)), dim3(256), 0, st, part,
-                       (int)blocks, (int64_t)Cout * 9, dw);
-    return hipGetLastError();
+static FastDiv fast_div(int d) {
+  FastDiv f{0, 0, d};
+  if (d == 1) return f;
+  int l = 0;
+  while (((int64_t)1 << l) < d) ++l;  // ceil(log2 d)
+  f.mul = (unsigned)((((uint64_t)1 << (31 + l)) / (uint64_t)d) + 1);
+  f.sh = l - 1;
+  return f;
+}
+
+hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st) {
+  ReduceJobs J{};
+  int block = 0;
+  for (int i = 0; i < count; ++i) {
+    ReduceJob &r = J.j[J.count];
+    r = jobs[i];
+    if (r.n == 0) continue;
+    r.groups = r.splits >= 64 ? 16 : r.splits >= 8 ? 4 : 1;
+    r.block0 = block;
+    block += (int)cdiv_(r.n, 256 / r.groups);
+    if (++J.count == kReduceJobs || i + 1 == count) {
+      hipLaunchKernelGGL(k_reduce_parts, dim3(block), dim3(256), 0, st, J);
+      J = ReduceJobs{};
+      block = 0;
+    }
   }
-  ConvWgradOp op;
-  op.g = {B, Hi, Wi, Cin, Hi / 2, Wi / 2, Cout};
-  op.dout = dout; op.in = in; op.part = part;
-  const int M = Cout, N = 9 * Cin, K = (int)npix;
-  int s = wgrad_splits(M, N, K);
-  while ((size_t)s * M * N > part_cap && s > 1) --s;
-  if ((size_t)s * M * N > part_cap) return hipErrorInvalidValue;
-  int kchunk = (K + s - 1) / s;
-  kchunk = (kchunk + MK - 1) / MK * MK;
-  s = (K + kchunk - 1) / kchunk;
-  hipError_t e = launch_gemm(op, M, N, K, s, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_splitk_reduce, dim3(cdiv_((int64_t)M * N, 256)), dim3(256), 0, st, part, s,
-                     (int64_t)M * N, dw);
+  if (J.count) hipLaunchKernelGGL(k_reduce_parts, dim3(block), dim3(256), 0, st, J);
+  return hipGetLastError();
+}
+
+// Splits of a weight gradient's pixels: about one block of 128 x 128 outputs
+// per CU (two of 64 x 128), each at least 16 steps of 32 pixels long so that
+// the partials stay a small part of the traffic.
+constexpr int kConv1Blocks = 512;  // two per CU
+static int wgrad_plan(int Cin, int Cout, int64_t K, int *kchunk) {
+  const int tiles = (int)(cdiv_(Cout, Cout > 64 ? 128 : 64) * cdiv_(9 * Cin, 128));
+  const int want = (Cout > 64 ? 256 : 512) / tiles;
+  int64_t s = std::max<int64_t>(1, std::min<int64_t>(want, K / 512));
+  const int64_t c = (cdiv_(K, s) + 31) / 32 * 32;
+  *kchunk = (int)c;
+  return (int)((K + c - 1) / c);
+}
+
+// Values of a partial array: 2^23 at most for one split, or for the first
+// layer's chunks of 256 pixels.
+constexpr int64_t kPartMax = (int64_t)1 << 23;
+
+static bool conv1_wgrad_rows(int Wi, int Cout) { return Cout == 32 && Wi % 64 == 0; }
+
+size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool aligned) {
+  const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
+  if (Cin == 1)
+    return (size_t)(aligned && conv1_wgrad_rows(Wi, Cout) ? kConv1Blocks : cdiv_(npix, 256)) * Cout * 10;
+  int kc;
+  // (fewer images never take more splits)
+  return (size_t)wgrad_plan(Cin, Cout, npix, &kc) * Cout * (9 * Cin + 1);
+}
+
+hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout,
+                      float *part, size_t part_cap, float *dw, float *db, ReduceJob jobs[2],
+                      hipStream_t st) {
+  const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
+  const bool aligned = (((uintptr_t)dout | (uintptr_t)in) & 15) == 0;
+  const int64_t least = Cin == 1 ? (int64_t)cdiv_(npix, 256) * Cout * 9 : (int64_t)Cout * 9 * Cin;
+  if (least > kPartMax || (Cin == 1 && Cout > 32) || npix >= ((int64_t)1 << 31) - 64 ||
+      conv_wgrad_part(B, Hi, Wi, Cin, Cout, aligned) > part_cap)
+    return hipErrorInvalidValue;
+  int s;
+  float *part_b;
+  if (Cin == 1 && aligned && conv1_wgrad_rows(Wi, Cout)) {
+    // output rows of whole 32-pixel steps (every network input side)
+    s = kConv1Blocks;
+    part_b = part + (size_t)s * Cout * 9;
+    hipLaunchKernelGGL(k_conv1_wgrad_mma, dim3(s), dim3(256), 0, st, in, dout, B, Hi, Wi, part, part_b);
+  } else if (Cin == 1) {
+    s = (int)cdiv_(npix, 256);
+    part_b = part + (size_t)s * Cout * 9;
+    hipLaunchKernelGGL(k_conv1_wgrad, dim3(s), dim3(256), 0, st, in, dout, B, Hi, Wi, Cout, 256, part,
+                       part_b);
+  } else {
+    WgradMma a{};
+    a.dout = dout; a.in = in;
+    a.Hi = Hi; a.Wi = Wi; a.Cin = Cin; a.Ho = Hi / 2; a.Wo = Wi / 2; a.Cout = Cout;
+    a.div_w = fast_div(a.Wo); a.div_h = fast_div(a.Ho); a.div_c = fast_div(Cin);
+    a.K = (int)npix;
+    s = wgrad_plan(Cin, Cout, npix, &a.kchunk);
+    part_b = part + (size_t)s * Cout * 9 * Cin;
+    a.part = part;
+    a.part_b = part_b;
+    if (Cout > 64)
+      hipLaunchKernelGGL((k_wgrad_mma<4, 4>), dim3(cdiv_(Cout, 128), cdiv_(9 * Cin, 128), s), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL((k_wgrad_mma<2, 4>), dim3(cdiv_(Cout, 64), cdiv_(9 * Cin, 128), s), dim3(256), 0, st, a);
+  }
+  jobs[0] = ReduceJob{part, dw, nullptr, (int64_t)Cout * 9 * Cin, s, 1, 0};
+  jobs[1] = ReduceJob{part_b, db, nullptr, db ? Cout : 0, s, 1, 0};
   return hipGetLastError();
 }
 
@@ -1343,34 +1768,34 @@ hipError_t lin_dgrad(const bf16 *dy, const bf16 *wt, const bf16 *x_act, int B, i
   return launch_gemm(op, B, In, Out, 1, st);
 }
 
+size_t lin_wgrad_part(int B, int In, int Out) {
+  return (size_t)wgrad_splits(Out, In, B) * Out * In + (size_t)std::max(1, std::min(1024, B / 32)) * Out;
+}
+
 hipError_t lin_wgrad(const bf16 *dy, const bf16 *x, int B, int In, int Out, float *part,
-                     size_t part_cap, float *dw, hipStream_t st) {
+                     size_t part_cap, float *dw, float *db, ReduceJob jobs[2], hipStream_t st) {
   LinWgradOp op;
   op.g = {B, In, Out};
   op.dy = dy; op.x = x; op.part = part;
   const int M = Out, N = In, K = B;
   int s = wgrad_splits(M, N, K);
-  while ((size_t)s * M * N > part_cap && s > 1) --s;
-  if ((size_t)s * M * N > part_cap) return hipErrorInvalidValue;
+  const int chunks = std::max(1, std::min(1024, B / 32));
+  const size_t cap = part_cap - (db ? (size_t)chunks * Out : 0);
+  while ((size_t)s * M * N > cap && s > 1) --s;
+  if (part_cap < (size_t)chunks * Out || (size_t)s * M * N > cap) return hipErrorInvalidValue;
   int kchunk = (K + s - 1) / s;
   kchunk = (kchunk + MK - 1) / MK * MK;
   s = (K + kchunk - 1) / kchunk;
   hipError_t e = launch_gemm(op, M, N, K, s, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_splitk_reduce, dim3(cdiv_((int64_t)M * N, 256)), dim3(256), 0, st, part, s,
-                     (int64_t)M * N, dw);
-  return hipGetLastError();
-}
-
-hipError_t colsum(const bf16 *g, int M, int N, float *part, size_t part_cap, float *out,
-                  hipStream_t st) {
-  int chunks = std::max(1, std::min(1024, M / 256));
-  while ((size_t)chunks * N > part_cap && chunks > 1) chunks /= 2;
-  if ((size_t)chunks * N > part_cap) return hipErrorInvalidValue;
-  const int rpc = (M + chunks - 1) / chunks;
-  hipLaunchKernelGGL(k_colsum, dim3(cdiv_(N, 256), chunks), dim3(256), 0, st, g, M, N, rpc, part);
-  hipLaunchKernelGGL(k_splitk_reduce, dim3(cdiv_(N, 256)), dim3(256), 0, st, part, chunks,
-                     (int64_t)N, out);
+  jobs[0] = ReduceJob{part, dw, nullptr, (int64_t)M * N, s, 1, 0};
+  jobs[1] = ReduceJob{};
+  if (db) {
+    float *pb = part + (size_t)s * M * N;
+    hipLaunchKernelGGL(k_colsum, dim3(cdiv_(Out, 256), chunks), dim3(256), 0, st, dy, B, Out,
+                       (B + chunks - 1) / chunks, pb);
+    jobs[1] = ReduceJob{pb, db, nullptr, Out, chunks, 1, 0};
+  }
   return hipGetLastError();
 }
 
@@ -1380,7 +1805,10 @@ hipError_t sum_into(const float *part, int n, float *out, hipStream_t st) {
 }
 
 hipError_t standardize(const float *img, int B, int npx, bf16 *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_standardize, dim3(B), dim3(256), 0, st, img, npx, out);
+  if (npx % 4 == 0 && ((uintptr_t)img & 15) == 0 && ((uintptr_t)out & 7) == 0)
+    hipLaunchKernelGGL(k_standardize<4>, dim3(B), dim3(1024), 0, st, img, npx, out);
+  else
+    hipLaunchKernelGGL(k_standardize<1>, dim3(B), dim3(1024), 0, st, img, npx, out);
   return hipGetLastError();
 }
 

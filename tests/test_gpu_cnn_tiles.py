@@ -76,3 +76,20 @@ def test_conv_dgrad_tiles(gpu_lib, B, H, W, Cin, Cout, masked):
     if masked:
         ref = ref * (act > 0)
     _check(dx32, dx, ref, mag, 9 * Cout, "dgrad")
+
+
+# one split and several, remainders of the 32-pixel steps, tiles of 64 and 128
+# output channels, ragged (tap, channel) columns; the first layer's row kernel
+# (32 channels, rows of whole steps) and its general one
+@pytest.mark.parametrize("B,H,W,Cin,Cout", [
+    (1, 2, 2, 8, 8), (1, 6, 10, 24, 72), (3, 10, 14, 40, 64), (2, 8, 8, 96, 136),
+    (9, 48, 48, 32, 64), (33, 32, 32, 64, 128), (5, 66, 34, 16, 200), (7, 64, 64, 128, 256),
+    (1, 64, 64, 1, 32), (5, 64, 128, 1, 32), (70, 64, 64, 1, 32), (3, 32, 32, 1, 32), (2, 64, 64, 1, 24),
+])
+def test_conv_wgrad_tiles(gpu_lib, B, H, W, Cin, Cout):
+    announce(f"conv wgrad B={B} {H}x{W} {Cin}->{Cout}")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, dy = _rand(g, B, H, W, Cin), _rand(g, B, H // 2, W // 2, Cout)
+    dw = gpu_lib.conv_wgrad(dy, x)
+    d, cols = dy.double().reshape(-1, Cout), _columns(x)
+    _check(dw.reshape(Cout, -1), None, d.t() @ cols, d.abs().t() @ cols.abs(), d.shape[0], "wgrad")
