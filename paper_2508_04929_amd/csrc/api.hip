@@ -83,22 +83,10 @@ hipError_t scratch_address(int device, char **out) {
 
 namespace cs {
 
-bool fft_plan(int L, FftPlan &P) {
-  if (L < 2 || L > kMaxD) return false;
-  P.L = L;
-  P.nst = 0;
-  int r = L;
-  while (r % 4 == 0) { P.radix[P.nst++] = 4; r /= 4; }
-  while (r % 2 == 0) { P.radix[P.nst++] = 2; r /= 2; }
-  while (r % 3 == 0) { P.radix[P.nst++] = 3; r /= 3; }
-  return r == 1 && P.nst <= 12;
-}
+// A transform length with kernels: even, prime factors 2 and 3, up to 512.
+bool fft_length(int L) { return L >= 2 && L <= kMaxD && fft_shape(L).ts > 0; }
 
 }  // namespace cs
-
-namespace {
-
-}  // namespace
 
 namespace cs {
 
@@ -222,16 +210,6 @@ int ensure_ws(cs_ctx *ctx, size_t need, hipStream_t stream) {
 
 namespace cs {
 
-int fft_cols_per_block(int D, int64_t B) {
-  // four columns per block (18 KB of LDS at D = 256: eight blocks per CU
-  // hide the latency of the strided column loads), two when a small batch
-  // would leave the pass with fewer than a few hundred blocks; each column's
-  // transform is the same whatever the blocking
-  int c = 4;
-  while (c > 2 && (int64_t)((D / 2 + c) / c) * B < 512) c >>= 1;
-  return c;
-}
-
 int get_twiddles(cs_ctx *ctx, int L, const float2 **out) {
   auto it = ctx->twiddles.find(L);
   if (it != ctx->twiddles.end()) { *out = it->second; return CS_OK; }
@@ -273,8 +251,7 @@ int validate(cs_ctx *ctx, const cs_gaussians *g, const cs_views *v, const cs_ctf
   if ((int64_t)v->b * (int64_t)std::max<int64_t>(g->n, 1) >= (int64_t)1 << 31)
     return fail(ctx, CS_ERR_UNSUPPORTED, "B*N must be below 2^31");
   if (ctf) {
-    FftPlan P;
-    if (v->d % 2 != 0 || !fft_plan(v->d, P))
+    if (!fft_length(v->d))
       return fail(ctx, CS_ERR_UNSUPPORTED, "CTF needs an even D with prime factors 2 and 3 (got %d)", v->d);
     if (!ctf->defocus_u || !ctf->defocus_v) return fail(ctx, CS_ERR_INVALID_ARG, "null defocus");
     if (!(ctf->voltage_kv > 0.0)) return fail(ctx, CS_ERR_INVALID_ARG, "voltage must be positive");
@@ -498,33 +475,20 @@ int launch_backward_finish(cs_ctx *ctx, const Plan &P, hipStream_t st) {
   return CS_OK;
 }
 
-// Launch shapes of the FFT kernels for one image side.
-struct FftLaunch {
-  FftPlan P;
+// Launch shapes and twiddles of the FFT kernels for one image side.
+struct FftPass {
   const float2 *tw = nullptr;
-  dim3 rgrid, cgrid, rblock;
-  size_t rlds = 0, clds = 0;
-  int cpw = 16;
+  FftLaunch rows, cols;
 };
 
-int fft_setup(cs_ctx *ctx, const Geom &G, const float2 *tw, FftLaunch &F) {
-  fft_plan(G.D, F.P);
+int fft_setup(cs_ctx *ctx, const Geom &G, const float2 *tw, FftPass &F) {
   F.tw = tw;
   if (!F.tw) {
     int rc = get_twiddles(ctx, G.D, &F.tw);
     if (rc) return rc;
   }
-  F.rgrid = dim3(cdiv(G.D / 2, 4), G.B);
-  F.rlds = (size_t)(4 * 2 + 1) * G.D * 8;  // four row pairs (ping-pong) + twiddles
-  F.rblock = dim3(256);
-  if ((int64_t)F.rgrid.x * G.B < 512) {    // small batches: one row pair per block
-    F.rgrid = dim3(G.D / 2, G.B);
-    F.rlds = (size_t)(1 * 2 + 1) * G.D * 8;
-    F.rblock = dim3(64);
-  }
-  F.cpw = fft_cols_per_block(G.D, G.B);
-  F.cgrid = dim3(cdiv(G.D / 2 + 1, F.cpw), G.B);
-  F.clds = (size_t)(F.cpw * 2 + 1) * G.D * 8;
+  F.rows = fft_rows_launch(G.D, G.B);
+  F.cols = fft_cols_launch(G.D, G.D / 2 + 1, G.B, true);
   return CS_OK;
 }
 
@@ -543,14 +507,17 @@ int launch_ctf_table(cs_ctx *ctx, const Plan &P, hipStream_t st) {
 // dst = F^-1(H^ F src) for one problem (CTF table already built).
 int launch_ctf_roundtrip(cs_ctx *ctx, const Plan &P, const float *src, float *dst, hipStream_t st) {
   const Geom &G = P.G;
-  FftLaunch F;
+  FftPass F;
   int rc = fft_setup(ctx, G, P.tw, F);
   if (rc) return rc;
+  const RowsFwdFn k_fft_rows_fwd = fft_rows_fwd(G.D);
+  const ColsCtfFn k_fft_cols_ctf = fft_cols_ctf(G.D, F.cols.narrow);
+  const RowsInvFn k_fft_rows_inv = fft_rows_inv(G.D);
   float2 *spec = (float2 *)(P.ws + P.L.spec);
-  TLAUNCH(k_fft_rows_fwd, F.rgrid, F.rblock, F.rlds, st, src, F.P, F.tw, G.B, spec);
-  TLAUNCH(k_fft_cols_ctf, F.cgrid, dim3(256), F.clds, st, spec, F.P, F.tw, G.B, F.cpw,
+  TLAUNCH(k_fft_rows_fwd, F.rows.grid, F.rows.block, F.rows.lds, st, src, F.tw, spec);
+  TLAUNCH(k_fft_cols_ctf, F.cols.grid, F.cols.block, F.cols.lds, st, spec, F.tw,
           (const float *)(P.ws + P.L.ctf));
-  TLAUNCH(k_fft_rows_inv, F.rgrid, F.rblock, F.rlds, st, (const float2 *)spec, F.P, F.tw, G.B, dst);
+  TLAUNCH(k_fft_rows_inv, F.rows.grid, F.rows.block, F.rows.lds, st, (const float2 *)spec, F.tw, dst);
   return CS_OK;
 }
 
@@ -563,19 +530,23 @@ int launch_loss(cs_ctx *ctx, const Plan &P, hipStream_t st) {
   const float gscale = (float)(2.0 * scale);
   int parts;
   if (P.ctf) {
-    FftLaunch F;
+    FftPass F;
     int rc = fft_setup(ctx, G, P.tw, F);
     if (rc) return rc;
+    const RowsFwdFn k_fft_rows_fwd = fft_rows_fwd(G.D);
+    const ColsCtfFn k_fft_cols_ctf = fft_cols_ctf(G.D, F.cols.narrow);
+    const RowsInvLossFn k_fft_rows_inv_loss = fft_rows_inv_loss(G.D);
+    const RowsInvFn k_fft_rows_inv = fft_rows_inv(G.D);
     float2 *spec = (float2 *)(P.ws + P.L.spec);
     const float *table = (const float *)(P.ws + P.L.ctf);
-    TLAUNCH(k_fft_rows_fwd, F.rgrid, F.rblock, F.rlds, st, Q, F.P, F.tw, G.B, spec);
-    TLAUNCH(k_fft_cols_ctf, F.cgrid, dim3(256), F.clds, st, spec, F.P, F.tw, G.B, F.cpw, table);
-    TLAUNCH(k_fft_rows_inv_loss, F.rgrid, F.rblock, F.rlds, st, spec, F.P, F.tw, G.B, P.observed,
-            P.images_out, gscale, loss_part);
+    TLAUNCH(k_fft_rows_fwd, F.rows.grid, F.rows.block, F.rows.lds, st, Q, F.tw, spec);
+    TLAUNCH(k_fft_cols_ctf, F.cols.grid, F.cols.block, F.cols.lds, st, spec, F.tw, table);
+    TLAUNCH(k_fft_rows_inv_loss, F.rows.grid, F.rows.block, F.rows.lds, st, spec, F.tw, P.observed,
+            P.images_out, gscale, P.bwd ? 1 : 0, loss_part);
     parts = G.D / 2;
     if (P.bwd) {
-      TLAUNCH(k_fft_cols_ctf, F.cgrid, dim3(256), F.clds, st, spec, F.P, F.tw, G.B, F.cpw, table);
-      TLAUNCH(k_fft_rows_inv, F.rgrid, F.rblock, F.rlds, st, (const float2 *)spec, F.P, F.tw, G.B, Q);
+      TLAUNCH(k_fft_cols_ctf, F.cols.grid, F.cols.block, F.cols.lds, st, spec, F.tw, table);
+      TLAUNCH(k_fft_rows_inv, F.rows.grid, F.rows.block, F.rows.lds, st, (const float2 *)spec, F.tw, Q);
     }
   } else {
     TLAUNCH(k_residual, dim3(G.D, G.B), dim3(256), 0, st, Q, P.observed, P.images_out, G.B, G.D,

@@ -14,13 +14,11 @@ namespace cs {
 // ---------------------------------------------------------------------------
 __device__ inline double ctf_at(double sx, double sy, const CtfDev &c, double du, double dv,
                          double c2a, double s2a, double ph, double amp_s) {
-  const double s2 = sx * sx + sy * sy;
-  double df = 0.5 * (du + dv);
-  if (s2 > 0.0 && du != dv) {
-    const double cos2 = (sx * sx - sy * sy) / s2, sin2 = 2.0 * sx * sy / s2;
-    df += 0.5 * (du - dv) * (cos2 * c2a + sin2 * s2a);
-  }
-  const double chi = M_PI * c.lam * df * s2 - 0.5 * M_PI * c.cs * c.lam * c.lam * c.lam * s2 * s2 - ph;
+  // the defocus term as a quadratic form in (sx, sy): df(a) s^2 without the
+  // azimuth, so no FP64 division
+  const double xx = sx * sx, yy = sy * sy, s2 = xx + yy;
+  const double dfs2 = 0.5 * (du + dv) * s2 + 0.5 * (du - dv) * ((xx - yy) * c2a + 2.0 * sx * sy * s2a);
+  const double chi = M_PI * c.lam * dfs2 - 0.5 * M_PI * c.cs * c.lam * c.lam * c.lam * s2 * s2 - ph;
   // phase in FP64, reduced to [-pi, pi] in FP64, then one FP32 sincos (about
   // 1e-7 absolute in the CTF)
   const double turns = chi * (0.5 / M_PI);

@@ -83,13 +83,6 @@ struct CtfDev {
   int enabled;
 };
 
-// Mixed-radix (4, 2, 3) Stockham plan for one transform length.
-struct FftPlan {
-  int L;
-  int nst;
-  int radix[12];
-};
-
 // ----------------------------------------------------------------------------
 // Device helpers
 // ----------------------------------------------------------------------------
@@ -221,26 +214,36 @@ __global__ void k_check_finite(const float *p, int64_t n, int bit, int *flag);
 
 __global__ void k_twiddles(int L, float2 *tw);
 
-__global__ void k_fft_rows_fwd(const float *src, FftPlan P, const float2 *tw, int B, float2 *spec);
-
 __global__ void k_ctf_table(int L, float pixel, CtfDev ctf, int B, float *table);
 
-__global__ void k_fft_cols_ctf(float2 *spec, FftPlan P, const float2 *tw, int B, int cpw,
-                               const float *table);
+// FFT passes of one length (k_fft.hip, k_fft_cols.hip): the kernel of that
+// length, its threads per transform and LDS values, and launch shapes.
+typedef void (*RowsFwdFn)(const float *src, const float2 *tw, float2 *spec);
+typedef void (*RowsInvFn)(const float2 *spec, const float2 *tw, float *dst);
+typedef void (*RowsInvLossFn)(float2 *spec, const float2 *tw, const float *obs, float *images_out,
+                              float grad_scale, int adjoint, float *loss_part);
+typedef void (*ColsCtfFn)(float2 *spec, const float2 *tw, const float *table);
+typedef void (*ColsShiftFn)(float2 *spec, const float2 *tw, const float *shift, float inv_pixel,
+                            float sign);
+typedef void (*AxisFn)(float2 *data, const float2 *tw, int inner);
+RowsFwdFn fft_rows_fwd(int L);
+RowsInvFn fft_rows_inv(int L);
+RowsInvLossFn fft_rows_inv_loss(int L);
+ColsCtfFn fft_cols_ctf(int L, bool narrow);
+ColsShiftFn fft_cols_shift(int L);
+AxisFn fft_axis(int L);
+struct FftShape {
+  int ts = 0, slots = 0;
+};
+FftShape fft_shape(int L);
+struct FftLaunch {
+  dim3 grid, block;
+  size_t lds;
+  bool narrow;
+};
+FftLaunch fft_rows_launch(int L, int64_t B);                                 // row pairs of B images
+FftLaunch fft_cols_launch(int L, int64_t columns, int64_t B, bool may_narrow);
 
-__global__ void k_fft_cols_shift(float2 *spec, FftPlan P, const float2 *tw, int cpw,
-                                 const float *shift, float inv_pixel, float sign);
-__global__ void k_fft_rows_inv(const float2 *spec, FftPlan P, const float2 *tw, int B,
-                               float *dst);
-
-__global__ void k_fft_rows_inv_loss(float2 *spec, FftPlan P, const float2 *tw, int B,
-                                    const float *obs, float *images_out, float grad_scale,
-                                    float *loss_part);
-
-__global__ void k_fft_axis(float2 *data, FftPlan P, const float2 *tw, int inner, int cpw);
-
-__global__ void k_fft_cols_power(const float2 *spec, FftPlan P, const float2 *tw, int B, int cpw,
-                                 unsigned short *out, size_t ld);
 __global__ void k_loss_reduce(const float *loss_part, int B, int parts, float scale, float *loss);
 
 __global__ void k_loss_total(float *loss, int B);

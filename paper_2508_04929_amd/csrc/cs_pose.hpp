@@ -10,6 +10,21 @@ namespace cs {
 
 enum { kPoseStore = 0, kPoseScore = 1 };
 
+// Mixed-radix (4, 2, 3) Stockham plan of the FFT passes in k_pose_fft.hip.
+struct FftPlan {
+  int L;
+  int nst;
+  int radix[12];
+};
+bool fft_plan(int L, FftPlan &P);
+int fft_cols_per_block(int D, int64_t B);  // columns per block of their column passes
+__global__ void k_pose_fft_rows_fwd(const float *src, FftPlan P, const float2 *tw, int B, float2 *spec);
+__global__ void k_pose_fft_cols_ctf(float2 *spec, FftPlan P, const float2 *tw, int B, int cpw,
+                                    const float *table);
+__global__ void k_pose_fft_rows_inv(const float2 *spec, FftPlan P, const float2 *tw, int B, float *dst);
+__global__ void k_pose_fft_cols_power(const float2 *spec, FftPlan P, const float2 *tw, int B, int cpw,
+                                      unsigned short *out, size_t ld);
+
 // Operands of the pose GEMMs (bfloat16 as raw uint16, K contiguous).
 struct PoseGemmArgs {
   const unsigned short *A = nullptr;   // store: rows lda elements apart; score, refine: the

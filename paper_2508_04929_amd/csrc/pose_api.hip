@@ -44,6 +44,32 @@ struct cs_pose_bank {
   cs_pose_batch *tmp = nullptr;     // batch of the raw-image convenience calls
 };
 
+namespace cs {
+
+bool fft_plan(int L, FftPlan &P) {
+  if (L < 2 || L > 512) return false;
+  P.L = L;
+  P.nst = 0;
+  int r = L;
+  while (r % 4 == 0) { P.radix[P.nst++] = 4; r /= 4; }
+  while (r % 2 == 0) { P.radix[P.nst++] = 2; r /= 2; }
+  while (r % 3 == 0) { P.radix[P.nst++] = 3; r /= 3; }
+  return r == 1 && P.nst <= 12;
+}
+
+
+int fft_cols_per_block(int D, int64_t B) {
+  // four columns per block (18 KB of LDS at D = 256: eight blocks per CU
+  // hide the latency of the strided column loads), two when a small batch
+  // would leave the pass with fewer than a few hundred blocks; each column's
+  // transform is the same whatever the blocking
+  int c = 4;
+  while (c > 2 && (int64_t)((D / 2 + c) / c) * B < 512) c >>= 1;
+  return c;
+}
+
+}  // namespace cs
+
 namespace {
 
 constexpr int kRowTeamsHost = 4;  // row pairs per block of the row FFT kernels
@@ -115,6 +141,15 @@ int ensure_scratch(cs_pose_bank *b, size_t bytes) {
   return CS_OK;
 }
 
+// One grid row per image (the kernel strides rows beyond 65535), a few
+// entries per thread where there are enough images to fill the chip.
+void launch_ctf_table(int D, float pixel, const cs_ctf *ctf, int P, float *table,
+                      hipStream_t st) {
+  const size_t per = (size_t)D * (D / 2 + 1), ept = P >= 16 ? 8 : 1;
+  hipLaunchKernelGGL(k_ctf_table, dim3(cdivu(per, 256 * ept), P < 65535 ? P : 65535), dim3(256), 0, st, D,
+                     pixel, make_ctf(ctf), P, table);
+}
+
 // Z = F^-1(H^ F Y) for P particles, plus the CTF table H^ / D^2.
 int ctf_filter_into(cs_ctx *ctx, int D, float pixel, const float *Y, const cs_ctf *ctf, int P,
                     float *table, float2 *spec, float *Z, hipStream_t st) {
@@ -124,27 +159,20 @@ int ctf_filter_into(cs_ctx *ctx, int D, float pixel, const float *Y, const cs_ct
   const float2 *tw = nullptr;
   int rc = get_twiddles(ctx, D, &tw);
   if (rc) return rc;
-  // one grid row per particle (the kernel strides rows beyond 65535), a few
-  // entries per thread where there are enough particles to fill the chip
-  const size_t per = (size_t)D * Dh;
-  const size_t ept = P >= 16 ? 8 : 1;
-  const unsigned rows = (unsigned)(P < 65535 ? P : 65535);
-  hipLaunchKernelGGL(k_ctf_table, dim3(cdivu(per, 256 * ept), rows), dim3(256), 0, st, D, ctf_pixel(ctf, pixel),
-                     make_ctf(ctf), P,
-                     table);
+  launch_ctf_table(D, ctf_pixel(ctf, pixel), ctf, P, table, st);
   LAUNCHCHK("k_ctf_table");
   const dim3 rgrid(cdivu(D / 2, kRowTeamsHost), P);
   const size_t rlds = (size_t)(kRowTeamsHost * 2 + 1) * D * 8;
   const int cpw = fft_cols_per_block(D, P);
   const dim3 cgrid(cdivu(Dh, cpw), P);
   const size_t clds = (size_t)(cpw * 2 + 1) * D * 8;
-  hipLaunchKernelGGL(k_fft_rows_fwd, rgrid, dim3(256), rlds, st, Y, P_, tw, P, spec);
-  LAUNCHCHK("k_fft_rows_fwd");
-  hipLaunchKernelGGL(k_fft_cols_ctf, cgrid, dim3(256), clds, st, spec, P_, tw, P, cpw,
+  hipLaunchKernelGGL(k_pose_fft_rows_fwd, rgrid, dim3(256), rlds, st, Y, P_, tw, P, spec);
+  LAUNCHCHK("k_pose_fft_rows_fwd");
+  hipLaunchKernelGGL(k_pose_fft_cols_ctf, cgrid, dim3(256), clds, st, spec, P_, tw, P, cpw,
                      (const float *)table);
-  LAUNCHCHK("k_fft_cols_ctf");
-  hipLaunchKernelGGL(k_fft_rows_inv, rgrid, dim3(256), rlds, st, (const float2 *)spec, P_, tw, P, Z);
-  LAUNCHCHK("k_fft_rows_inv");
+  LAUNCHCHK("k_pose_fft_cols_ctf");
+  hipLaunchKernelGGL(k_pose_fft_rows_inv, rgrid, dim3(256), rlds, st, (const float2 *)spec, P_, tw, P, Z);
+  LAUNCHCHK("k_pose_fft_rows_inv");
   return CS_OK;
 }
 
@@ -249,9 +277,9 @@ int cs_pose_bank_create(cs_ctx *ctx, const cs_gaussians *g, const float *rot, in
     if (rc) return bail(rc);
     if (rows_to_bf16(Q, kc, b->npx, b->data + k0 * b->Kext, b->Kext, st) != hipSuccess)
       return bail(fail(ctx, CS_ERR_HIP, "bank conversion failed"));
-    hipLaunchKernelGGL(k_fft_rows_fwd, dim3(cdivu(D / 2, kRowTeamsHost), kc), dim3(256),
+    hipLaunchKernelGGL(k_pose_fft_rows_fwd, dim3(cdivu(D / 2, kRowTeamsHost), kc), dim3(256),
                        (size_t)(kRowTeamsHost * 2 + 1) * D * 8, st, Q, P, tw, kc, spec);
-    hipLaunchKernelGGL(k_fft_cols_power, dim3(cdivu(Dh, cpw), kc), dim3(256),
+    hipLaunchKernelGGL(k_pose_fft_cols_power, dim3(cdivu(Dh, cpw), kc), dim3(256),
                        (size_t)(cpw * 2 + 1) * D * 8, st, (const float2 *)spec, P, tw, kc, cpw,
                        b->data + k0 * b->Kext + b->npx, (size_t)b->Kext);
     if (hipGetLastError() != hipSuccess) return bail(fail(ctx, CS_ERR_HIP, "bank spectra failed"));
@@ -542,8 +570,7 @@ int cs_ctf_filter(cs_ctx *ctx, const float *images, const cs_ctf *ctf, int32_t B
                   float pixel, float *out, void *stream) {
   if (!ctx) return CS_ERR_INVALID_ARG;
   if (!images || !out || B < 1) return fail(ctx, CS_ERR_INVALID_ARG, "bad filter arguments");
-  FftPlan P;
-  if (D < 2 || D % 2 != 0 || D > 512 || !fft_plan(D, P))
+  if (!fft_length(D))
     return fail(ctx, CS_ERR_UNSUPPORTED, "D must be even with prime factors 2, 3 (<= 512)");
   if (!(pixel > 0.f)) return fail(ctx, CS_ERR_INVALID_ARG, "pixel size must be positive");
   if (ctf && (!ctf->defocus_u || !ctf->defocus_v)) return fail(ctx, CS_ERR_INVALID_ARG, "null defocus");
@@ -554,8 +581,22 @@ int cs_ctf_filter(cs_ctx *ctx, const float *images, const cs_ctf *ctf, int32_t B
   const size_t tb = al256((size_t)B * D * Dh * 4), sb = al256((size_t)B * D * Dh * 8);
   int rc = grow(ctx, &ctx->aux, &ctx->aux_bytes, tb + sb);
   if (rc) return rc;
-  return ctf_filter_into(ctx, D, pixel, images, ctf, B, (float *)ctx->aux,
-                         (float2 *)((char *)ctx->aux + tb), out, (hipStream_t)stream);
+  float *table = (float *)ctx->aux;
+  float2 *spec = (float2 *)((char *)ctx->aux + tb);
+  hipStream_t st = (hipStream_t)stream;
+  const float2 *tw = nullptr;
+  rc = get_twiddles(ctx, D, &tw);
+  if (rc) return rc;
+  launch_ctf_table(D, ctf_pixel(ctf, pixel), ctf, B, table, st);
+  LAUNCHCHK("k_ctf_table");
+  const FftLaunch r = fft_rows_launch(D, B), c = fft_cols_launch(D, Dh, B, true);
+  hipLaunchKernelGGL(fft_rows_fwd(D), r.grid, r.block, r.lds, st, images, tw, spec);
+  LAUNCHCHK("k_fft_rows_fwd");
+  hipLaunchKernelGGL(fft_cols_ctf(D, c.narrow), c.grid, c.block, c.lds, st, spec, tw, (const float *)table);
+  LAUNCHCHK("k_fft_cols_ctf");
+  hipLaunchKernelGGL(fft_rows_inv(D), r.grid, r.block, r.lds, st, (const float2 *)spec, tw, out);
+  LAUNCHCHK("k_fft_rows_inv");
+  return CS_OK;
 }
 
 int cs_add_noise(cs_ctx *ctx, float *images, int32_t B, int32_t D, float snr_db, uint64_t seed,

@@ -12,7 +12,6 @@ using namespace cs;
 
 namespace {
 
-constexpr int kRowTeamsShift = 4;                     // row pairs per block of the row passes
 constexpr size_t kShiftChunkBytes = (size_t)256 << 20;  // spectrum staged per chunk of images
 
 size_t al256t(size_t x) { return (x + 255) & ~size_t(255); }
@@ -29,8 +28,7 @@ int cs_fourier_shift(cs_ctx *ctx, const float *images, const float *shift, int64
   if (B < 1) return fail(ctx, CS_ERR_INVALID_ARG, "B must be >= 1");
   if (!(pixel > 0.f) || !std::isfinite(pixel)) return fail(ctx, CS_ERR_INVALID_ARG, "pixel size must be positive");
   if (direction != 1.f && direction != -1.f) return fail(ctx, CS_ERR_INVALID_ARG, "direction must be +1 or -1");
-  FftPlan P;
-  if (D < 2 || D % 2 != 0 || D > 512 || !fft_plan(D, P))
+  if (!fft_length(D))
     return fail(ctx, CS_ERR_UNSUPPORTED, "D must be even with prime factors 2 and 3 (<= 512)");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
@@ -43,18 +41,17 @@ int cs_fourier_shift(cs_ctx *ctx, const float *images, const float *shift, int64
   rc = grow(ctx, &ctx->aux, &ctx->aux_bytes, al256t((size_t)chunk * per));
   if (rc) return rc;
   float2 *spec = (float2 *)ctx->aux;
-  const size_t rlds = (size_t)(kRowTeamsShift * 2 + 1) * D * 8;
+  const RowsFwdFn k_fft_rows_fwd = fft_rows_fwd(D);
+  const ColsShiftFn k_fft_cols_shift = fft_cols_shift(D);
+  const RowsInvFn k_fft_rows_inv = fft_rows_inv(D);
   const size_t npix = (size_t)D * D;
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int nb = (int)std::min<int64_t>(chunk, B - b0);
-    const int cpw = fft_cols_per_block(D, nb);
-    const size_t clds = (size_t)(cpw * 2 + 1) * D * 8;
-    const dim3 rgrid(cdivt(D / 2, kRowTeamsShift), nb);
-    TLAUNCH(k_fft_rows_fwd, rgrid, dim3(256), rlds, st, images + b0 * npix, P, tw, nb, spec);
-    TLAUNCH(k_fft_cols_shift, dim3(cdivt(Dh, cpw), nb), dim3(256), clds, st, spec, P, tw, cpw,
-            shift + 2 * b0, 1.f / pixel, direction);
-    TLAUNCH(k_fft_rows_inv, rgrid, dim3(256), rlds, st, (const float2 *)spec, P, tw, nb,
-            out + b0 * npix);
+    const FftLaunch r = fft_rows_launch(D, nb), c = fft_cols_launch(D, Dh, nb, false);
+    TLAUNCH(k_fft_rows_fwd, r.grid, r.block, r.lds, st, images + b0 * npix, tw, spec);
+    TLAUNCH(k_fft_cols_shift, c.grid, c.block, c.lds, st, spec, tw, shift + 2 * b0, 1.f / pixel,
+            direction);
+    TLAUNCH(k_fft_rows_inv, r.grid, r.block, r.lds, st, (const float2 *)spec, tw, out + b0 * npix);
   }
   return CS_OK;
 }

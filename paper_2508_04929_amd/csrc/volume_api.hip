@@ -10,7 +10,6 @@ using namespace cs;
 namespace {
 
 constexpr float kDefaultQCutVol = 27.631021115928547f;  // 2 ln 1e6, as the renderer
-constexpr int kRowTeamsVol = 4;                          // row pairs per block of k_fft_rows_fwd
 
 size_t al256v(size_t x) { return (x + 255) & ~size_t(255); }
 unsigned cdivv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
@@ -102,8 +101,7 @@ int cs_fsc(cs_ctx *ctx, const float *vol_a, const float *vol_b, int32_t D, float
            void *stream) {
   if (!ctx) return CS_ERR_INVALID_ARG;
   if (!vol_a || !vol_b || !fsc) return fail(ctx, CS_ERR_INVALID_ARG, "null volume or output");
-  FftPlan P;
-  if (D < 2 || D % 2 != 0 || D > 512 || !fft_plan(D, P))
+  if (!fft_length(D))
     return fail(ctx, CS_ERR_UNSUPPORTED, "D must be even with prime factors 2 and 3 (<= 512)");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
@@ -124,17 +122,16 @@ int cs_fsc(cs_ctx *ctx, const float *vol_a, const float *vol_b, int32_t D, float
   TLAUNCH(k_fsc_energy_part, dim3(kEnergyBlocks), dim3(256), 0, st, vol_a, vol_b,
           (int64_t)D * D * D, part);
   TLAUNCH(k_fsc_energy_scale, dim3(1), dim3(kEnergyBlocks), 0, st, (const double *)part, D, scale);
-  const dim3 rgrid(cdivv(D / 2, kRowTeamsVol), D);
-  const size_t rlds = (size_t)(kRowTeamsVol * 2 + 1) * D * 8;
-  const int cpw = fft_cols_per_block(D, D);
-  const size_t alds = (size_t)(cpw * 2 + 1) * D * 8;
+  const RowsFwdFn k_fft_rows_fwd = fft_rows_fwd(D);
+  const AxisFn k_fft_axis = fft_axis(D);
+  const FftLaunch rx = fft_rows_launch(D, D), ry = fft_cols_launch(D, Dh, D, false);
+  const FftLaunch rz = fft_cols_launch(D, (int64_t)D * Dh, 1, false);
   for (int v = 0; v < 2; ++v) {
     const float *src = v ? vol_b : vol_a;
     float2 *F = v ? fb : fa;
-    TLAUNCH(k_fft_rows_fwd, rgrid, dim3(256), rlds, st, src, P, tw, D, F);   // x (real rows)
-    TLAUNCH(k_fft_axis, dim3(cdivv(Dh, cpw), D), dim3(256), alds, st, F, P, tw, Dh, cpw);  // y
-    TLAUNCH(k_fft_axis, dim3(cdivv((int64_t)D * Dh, cpw), 1), dim3(256), alds, st, F, P, tw,
-            D * Dh, cpw);                                                        // z
+    TLAUNCH(k_fft_rows_fwd, rx.grid, rx.block, rx.lds, st, src, tw, F);       // x (real rows)
+    TLAUNCH(k_fft_axis, ry.grid, ry.block, ry.lds, st, F, tw, Dh);            // y
+    TLAUNCH(k_fft_axis, rz.grid, rz.block, rz.lds, st, F, tw, D * Dh);        // z
   }
   TLAUNCH(k_fill_u64z, dim3(cdivv(3 * ns, 256)), dim3(256), 0, st, sums, 3 * ns);
   const unsigned blocks = std::min<unsigned>(2048, cdivv((int64_t)D * D * Dh, 256));
