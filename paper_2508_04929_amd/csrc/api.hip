@@ -26,6 +26,15 @@ constexpr int kDefaultTile = 64;
 constexpr int kDefaultHalo = 16;
 constexpr int kDefaultBudget = 2048;
 constexpr int kMinAutoBudget = 256;
+// Calls of at most this many Gaussian-image pairs give four lanes to a record,
+// and smaller tiles and work items to images of few tiles (see make_geom): such
+// a call lasts as long as one wave's walk over its tallest record.  Loss and
+// gradient, us, default tile and one lane -> this, by pairs:
+//   one 128 x 128 image   2000: 105 -> 78, 16000: 119 -> 94, 32000: 123 -> 114, 48000: 125 -> 133
+//   16 images of 64 x 64  2000: 106 -> 80, 16000: 118 -> 90, 32000: 122 -> 102, 48000: 125 -> 116
+//   32 images of 128^2    2000: 117 -> 106, 16000: 133 -> 123, 32000: 137 -> 137, 48000: 142 -> 154
+constexpr int64_t kSmallPairs = 32768;
+constexpr int kSmallTile = 32, kSmallBudget = 64, kSmallTiles = 256;
 
 // Automatic work-item size: the default budget while N B Gaussian-image
 // pairs fill about a thousand work items, smaller (down to 256) for calls
@@ -108,7 +117,7 @@ enum Mode { RENDER, BACKWARD, LOSS };
 struct Layout {
   size_t gc = 0, key = 0, count = 0, off = 0, blk = 0, item_off = 0, n_items = 0, queues = 0,
          items = 0, list = 0, partials = 0, Q = 0, spec = 0, ctf = 0, mom = 0, loss_part = 0,
-         pose_part = 0, wabs = 0, wscale = 0, wideq = 0;
+         pose_part = 0, wabs = 0;
   size_t total = 0;
   int max_items = 0;
   int nbx = 0;  // Gaussian blocks of the binning kernels
@@ -119,12 +128,14 @@ struct Plan {
   cs_gaussians g{};
   cs_views v{};
   const cs_ctf *ctf = nullptr;
+  cs_options opt{};
   Geom G{};
   Layout L;
   char *ws = nullptr;  // this problem's workspace region
   const float2 *tw = nullptr;  // FFT twiddles; null = the context's cached table
   bool fwd = false;    // runs the forward splat
   bool bwd = false;    // runs the adjoint
+  int rs = 1;          // lanes per record of the splat kernels
   // RENDER
   float *images = nullptr;
   // BACKWARD
@@ -161,11 +172,7 @@ Layout make_layout(const Geom &G, bool need_partials, bool need_mom, bool need_f
   L.items = take((size_t)L.max_items * 16 + 16);
   L.list = take(BN * 32 + 32);
   L.wabs = take(BN * 4 + 16);
-  if (need_partials) {
-    L.partials = take((size_t)L.max_items * G.C * G.C * 4);
-    L.wscale = take((size_t)G.B * 8);
-    L.wideq = take((size_t)G.B * G.D * G.D * 8);
-  }
+  if (need_partials) L.partials = take((size_t)L.max_items * G.C * G.C * 4);
   L.Q = take((size_t)G.B * G.D * G.D * 4);
   if (need_fft) {
     L.spec = take((size_t)G.B * G.D * (G.D / 2 + 1) * 8);
@@ -273,7 +280,8 @@ int validate(cs_ctx *ctx, const cs_gaussians *g, const cs_views *v, const cs_ctf
   return CS_OK;
 }
 
-Geom make_geom(const cs_gaussians *g, const cs_views *v, const cs_options *opt) {
+// `small` allows the small tile.
+Geom make_geom(const cs_gaussians *g, const cs_views *v, const cs_options *opt, bool small) {
   Geom G;
   G.B = (int)v->b;
   G.N = (int)g->n;
@@ -282,18 +290,34 @@ Geom make_geom(const cs_gaussians *g, const cs_views *v, const cs_options *opt) 
   G.pixel = v->pixel;
   const float qc = (opt && opt->q_cut > 0.f) ? opt->q_cut : kDefaultQCut;
   G.qk = qc * kHalfLog2e;
-  G.T = (opt && opt->tile) ? opt->tile : kDefaultTile;
+  // Few pairs in few tiles: a quarter of the tile and a smaller work item
+  // spread them over more blocks.  With more tiles the default ones fill the
+  // chip, and four times as many canvases only cost (512 images of 64 x 64 with
+  // 128 Gaussians each: 221 us with default tiles, 275 us with small ones).
+  // Never beside a halo above the default, whose canvases would outgrow the
+  // tile.
+  small = small && (int64_t)G.N * G.B <= kSmallPairs && !(opt && (opt->tile || opt->halo > kDefaultHalo)) &&
+          (int64_t)G.B * cdiv(G.D, kDefaultTile) * cdiv(G.D, kDefaultTile) <= kSmallTiles;
+  G.T = (opt && opt->tile) ? opt->tile : small ? kSmallTile : kDefaultTile;
   G.halo = (opt && opt->halo) ? opt->halo : std::min(kDefaultHalo, G.T);
   G.C = G.T + 2 * G.halo;
   G.S = G.C + 4;  // padding columns keep unrolled row walks inside a row
   G.ntx = (G.D + G.T - 1) / G.T;
   G.ntiles = G.ntx * G.ntx;
   G.K = G.ntiles + 1;
-  G.budget = (opt && opt->budget) ? opt->budget : auto_budget(G.N, G.B);
+  G.budget = (opt && opt->budget) ? opt->budget : small ? kSmallBudget : auto_budget(G.N, G.B);
   G.scale_act = g->scale_act;
   G.amp_act = g->amp_act;
   G.deal = opt ? opt->lane_order : 0;
+  G.wide_parts = std::max(4, (512 + G.B - 1) / G.B);
   return G;
+}
+
+// Geometry and workspace of a plan whose problem and passes are set.
+void lay_out(Plan &P, bool small = true) {
+  P.G = make_geom(&P.g, &P.v, &P.opt, small);
+  P.rs = (int64_t)P.G.N * P.G.B <= kSmallPairs ? 4 : 1;
+  P.L = make_layout(P.G, P.fwd, P.bwd, P.ctf != nullptr);
 }
 
 }  // namespace
@@ -373,6 +397,8 @@ ProbDev prob_dev(const Plan &P) {
   d.items = (const int4 *)(P.ws + P.L.items);
   d.n_items = (const int *)(P.ws + P.L.n_items);
   d.wabs = (const float *)(P.ws + P.L.wabs);
+  d.off = (const int *)(P.ws + P.L.off);
+  d.count = (const int *)(P.ws + P.L.count);
   d.queue = (int *)(P.ws + P.L.queues);
   d.partials = (float *)(P.ws + P.L.partials);
   d.GQ = P.GQ();
@@ -384,12 +410,17 @@ ProbDev prob_dev(const Plan &P) {
 // problems: problems with the same canvas size share one launch (up to
 // kMaxProblems each), so that no problem runs at the occupancy of a larger
 // canvas; groups keep the problems' order.  Allocates nothing.
-int launch_one_persistent(cs_ctx *ctx, bool forward, const MultiProb &MP, size_t lds,
-                          hipStream_t st) {
+int launch_one_persistent(cs_ctx *ctx, bool forward, const MultiProb &MP, size_t lds, int64_t items,
+                          int rs, hipStream_t st) {
+  typedef void (*SplatFn)(MultiProb);
+  const SplatFn k_splat_fwd = rs == 1 ? &k_splat_fwd_rs<1> : &k_splat_fwd_rs<4>;
+  const SplatFn k_splat_bwd = rs == 1 ? &k_splat_bwd_rs<1> : &k_splat_bwd_rs<4>;
   int grid = 0;
-  int rc = persistent_grid(ctx, forward ? (const void *)k_splat_fwd : (const void *)k_splat_bwd,
-                           lds, &grid);
+  int rc = persistent_grid(ctx, (const void *)(forward ? k_splat_fwd : k_splat_bwd), lds, &grid);
   if (rc) return rc;
+  // no more blocks than there can be work items, as the rest would only queue up
+  // at the counter (but some for wide records, which are no work items)
+  grid = (int)std::min<int64_t>(grid, std::max<int64_t>(items, forward ? 1 : 256));
   if (forward) {
     TLAUNCH(k_splat_fwd, dim3(grid), dim3(kBlock), lds, st, MP);
   } else {
@@ -399,57 +430,56 @@ int launch_one_persistent(cs_ctx *ctx, bool forward, const MultiProb &MP, size_t
 }
 
 int launch_persistent(cs_ctx *ctx, bool forward, const Plan *const *all, int n, hipStream_t st) {
-  auto canvas = [&](int i) { return all[i]->G.C * all[i]->G.S; };
+  auto canvas = [&](int i) { return all[i]->G.C * all[i]->G.S * 8 + all[i]->rs; };
   for (int i = 0; i < n; ++i) {
     bool seen = false;  // canvas size already launched with an earlier group
     for (int j = 0; j < i && !seen; ++j) seen = canvas(j) == canvas(i);
     if (seen) continue;
     MultiProb MP{};
     size_t lds = 0;
+    int64_t items = 0;
     for (int k = i; k < n; ++k) {
       if (canvas(k) != canvas(i)) continue;
       MP.p[MP.count++] = prob_dev(*all[k]);
-      lds = std::max(lds, (size_t)canvas(k) * 4);
+      lds = std::max(lds, (size_t)all[k]->G.C * all[k]->G.S * 4);
+      items += all[k]->L.max_items;
       if (MP.count == kMaxProblems) {
-        int rc = launch_one_persistent(ctx, forward, MP, lds, st);
+        int rc = launch_one_persistent(ctx, forward, MP, lds, items, all[k]->rs, st);
         if (rc) return rc;
         MP = MultiProb{};
         lds = 0;
+        items = 0;
       }
     }
     if (MP.count) {
-      int rc = launch_one_persistent(ctx, forward, MP, lds, st);
+      int rc = launch_one_persistent(ctx, forward, MP, lds, items, all[i]->rs, st);
       if (rc) return rc;
     }
   }
   return CS_OK;
 }
 
-// After the forward splat: Q of one problem (reduce + wide Gaussians).
-// Blocks per image of the wide-record kernels (grid rows are images): about
-// 512 blocks in all, at least 4 per image.
-int big_blocks(int B) { return std::max(4, (512 + B - 1) / B); }
-
+// After the forward splat: Q of one problem.
 int launch_forward_finish(cs_ctx *ctx, const Plan &P, float *Q, hipStream_t st) {
   const Geom &G = P.G;
   char *ws = P.ws;
-  // split each tile's pixels over up to 4 blocks when there are few tiles
-  // (one image): the per-pixel sums are unchanged
-  const int per_tile = (G.T * G.T / 4 + kBlock - 1) / kBlock;
-  const int zsplit = std::max(1, std::min(per_tile, (int)((512 + (int64_t)G.ntiles * G.B - 1) /
-                                                          ((int64_t)G.ntiles * G.B))));
+  // split each tile's pixels over several blocks when there are few tiles,
+  // and a pixel group's items over four threads where that is not enough: one
+  // image of 128 x 128 and 66000 Gaussians takes 142 us for loss and gradient
+  // without and 123 us with, batch-1 steps 97 and 90 us; 64 images of 128 x 128
+  // (1024 tiles) take 189 us without and 195 us with
+  typedef void (*ReduceFn)(const float *, const int *, const int *, const int *, const int *, const float4 *,
+                           Geom, float *);
+  const int64_t tiles = (int64_t)G.ntiles * G.B;
+  const size_t quads = (size_t)G.T * G.T / 4;
+  const int S = tiles * cdiv(quads, kBlock) < 512 ? 4 : 1;
+  const ReduceFn k_canvas_reduce = S == 1 ? &k_canvas_reduce_s<1> : &k_canvas_reduce_s<4>;
+  const int per_tile = (int)cdiv(quads, kBlock / S);
+  const int zsplit = std::max(1, std::min(per_tile, (int)((512 * S + tiles - 1) / tiles)));
   TLAUNCH(k_canvas_reduce, dim3(G.ntiles, G.B, zsplit), dim3(kBlock), 0, st,
           (const float *)(ws + P.L.partials), (const int *)(ws + P.L.item_off),
-          (const int4 *)(ws + P.L.items), G, Q);
-  double *wscale = (double *)(ws + P.L.wscale);
-  long long *wq = (long long *)(ws + P.L.wideq);
-  TLAUNCH(k_big_prep, dim3(G.B), dim3(kBlock), 0, st, (const int *)(ws + P.L.off),
-          (const int *)(ws + P.L.count), (const float *)(ws + P.L.wabs), G, wscale, wq);
-  TLAUNCH(k_big_fwd, dim3(big_blocks(G.B), G.B), dim3(kBlock), 0, st, (const float4 *)(ws + P.L.list),
-          (const int *)(ws + P.L.off), (const int *)(ws + P.L.count),
-          (const int *)(ws + P.L.n_items) + 1, G, (const double *)wscale, wq);
-  TLAUNCH(k_big_add, dim3(cdiv((size_t)G.D * G.D, 4 * kBlock), G.B), dim3(kBlock), 0, st,
-          (const int *)(ws + P.L.count), G, (const double *)wscale, (const long long *)wq, Q);
+          (const int *)(ws + P.L.n_items), (const int *)(ws + P.L.off), (const int *)(ws + P.L.count),
+          (const float4 *)(ws + P.L.list), G, Q);
   return CS_OK;
 }
 
@@ -457,9 +487,6 @@ int launch_backward_finish(cs_ctx *ctx, const Plan &P, hipStream_t st) {
   const Geom &G = P.G;
   char *ws = P.ws;
   float *mom = (float *)(ws + P.L.mom);
-  TLAUNCH(k_big_bwd, dim3(big_blocks(G.B), G.B), dim3(kBlock), 0, st, (const float4 *)(ws + P.L.list),
-          (const int *)(ws + P.L.off), (const int *)(ws + P.L.count),
-          (const int *)(ws + P.L.n_items) + 1, G, P.GQ(), mom);
   TLAUNCH(k_chain, dim3(cdiv(G.N, 64)), dim3(kBlock), 0, st, (const float4 *)(ws + P.L.gc),
           P.g.log_scales, P.g.quats, P.g.amps, P.v.rot, P.v.shift, G, (const int *)(ws + P.L.key),
           mom, P.grads.means, P.grads.log_scales, P.grads.quats, P.grads.amps);
@@ -679,11 +706,26 @@ int enqueue(cs_ctx *ctx, std::vector<Plan> &plans, hipStream_t st) {
 // Workspace for all plans; assigns every plan its region and creates the
 // host-side resources the launches need (before any capture).
 int place(cs_ctx *ctx, std::vector<Plan> &plans, hipStream_t st) {
-  size_t total = 0;
   std::vector<size_t> offs;
-  for (auto &P : plans) {
-    offs.push_back(total);
-    total += align_up(P.L.total);
+  auto total_bytes = [&] {
+    size_t total = 0;
+    offs.clear();
+    for (auto &P : plans) {
+      offs.push_back(total);
+      total += align_up(P.L.total);
+    }
+    return total;
+  };
+  size_t total = total_bytes();
+  if (total > ctx->ws_bytes) {
+    // small tiles may need more room than the default ones: not where the
+    // workspace cannot grow that far (its limit; a caller's capture)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    (void)hipStreamIsCapturing(st, &cap);
+    if (cap != hipStreamCaptureStatusNone || (ctx->ws_max && total > ctx->ws_max)) {
+      for (auto &P : plans) lay_out(P, false);
+      total = total_bytes();
+    }
   }
   int rc = ensure_ws(ctx, total, st);
   if (rc) return rc;
@@ -707,15 +749,15 @@ int make_loss_plan(cs_ctx *ctx, const cs_problem &pr, Plan &P) {
   P.g = pr.g;
   P.v = pr.v;
   P.ctf = pr.ctf;
-  P.G = make_geom(&pr.g, &pr.v, &pr.opt);
+  P.opt = pr.opt;
   P.observed = pr.observed;
   P.reduction = pr.reduction;
   P.loss = pr.loss;
   P.images_out = pr.images_out;
   P.grads = pr.grads;
-  P.fwd = P.G.N > 0;
-  P.bwd = P.G.N > 0 && has_grads(pr.grads);
-  P.L = make_layout(P.G, P.fwd, P.bwd, P.ctf != nullptr);
+  P.fwd = P.g.n > 0;
+  P.bwd = P.g.n > 0 && has_grads(pr.grads);
+  lay_out(P);
   return CS_OK;
 }
 
@@ -877,8 +919,9 @@ int cs_create(int device, cs_ctx **out) {
   const hipError_t se = scratch_address(device, &c->scratch);
   if (se != hipSuccess) c->scratch_err = hipGetErrorString(se);
   // allow canvases above 64 KiB of LDS
-  (void)hipFuncSetAttribute((const void *)k_splat_fwd, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-  (void)hipFuncSetAttribute((const void *)k_splat_bwd, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  for (const void *k : {(const void *)&k_splat_fwd_rs<1>, (const void *)&k_splat_fwd_rs<4>,
+                        (const void *)&k_splat_bwd_rs<1>, (const void *)&k_splat_bwd_rs<4>})
+    (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   (void)hipGetLastError();
   *out = c;
   return CS_OK;
@@ -918,10 +961,10 @@ int cs_render(cs_ctx *ctx, const cs_gaussians *g, const cs_views *v, const cs_ct
   P.g = *g;
   P.v = *v;
   P.ctf = ctf;
-  P.G = make_geom(g, v, opt);
+  if (opt) P.opt = *opt;
   P.images = images;
-  P.fwd = P.G.N > 0;
-  P.L = make_layout(P.G, P.fwd, false, ctf != nullptr);
+  P.fwd = P.g.n > 0;
+  lay_out(P);
   rc = place(ctx, plans, st);
   if (rc) return rc;
   rc = enqueue(ctx, plans, st);
@@ -948,11 +991,11 @@ int cs_render_backward(cs_ctx *ctx, const cs_gaussians *g, const cs_views *v, co
   P.g = *g;
   P.v = *v;
   P.ctf = ctf;
-  P.G = make_geom(g, v, opt);
+  if (opt) P.opt = *opt;
   P.d_images = d_images;
   P.grads = *grads;
   P.bwd = true;
-  P.L = make_layout(P.G, false, true, ctf != nullptr);
+  lay_out(P);
   rc = place(ctx, plans, st);
   if (rc) return rc;
   rc = enqueue(ctx, plans, st);
@@ -1162,7 +1205,7 @@ int cs_pair_count(cs_ctx *ctx, const cs_gaussians *g, const cs_views *v, const c
   if (!counts) return fail(ctx, CS_ERR_INVALID_ARG, "null counts");
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
-  const Geom G = make_geom(g, v, opt);
+  const Geom G = make_geom(g, v, opt, false);
   rc = fill(ctx, (float *)counts, 2 * (size_t)G.B, st);  // all-zero bits
   if (rc) return rc;
   if (G.N == 0) return CS_OK;

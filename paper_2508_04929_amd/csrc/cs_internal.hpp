@@ -10,14 +10,13 @@
 //                  owner tile's segment of the list (stable: by index)
 //   k_splat_fwd    per work item: additive splat (Eq. 9) into an LDS canvas
 //                  covering the owner tile plus a halo -> partial canvases
-//   k_canvas_reduce per tile: sum of the overlapping partial canvases -> Q
-//   k_big_*        Gaussians wider than the halo: 64-bit fixed-point sums
-//                  per image (order-free), then added to Q
+//   k_canvas_reduce per tile: sum of the overlapping partial canvases, plus the
+//                  Gaussians wider than the halo -> Q
 //   FFT kernels    X = F^-1(H^ . F Q), residual, loss, G_Q = F^-1(H^ . F G_X)
 //                  (Eq. 14, Sec. 3.3.5; H^ real and even -> self-adjoint)
 //   k_splat_bwd    per work item: per-(image, Gaussian) pixel moments of
-//                  G_Q against the splat (Eq. 16-20 need only these)
-//   k_big_bwd      the same for wide Gaussians
+//                  G_Q against the splat (Eq. 16-20 need only these), wide
+//                  Gaussians last
 //   k_chain        per Gaussian: moments -> screen gradients -> world frame,
 //                  summed over images, then s, q, A chain rule (Eq. 18-21)
 #pragma once
@@ -50,6 +49,7 @@ struct Geom {
   int scale_act;  // 0 exp, 1 softplus
   int amp_act;    // 0 identity, 1 softplus
   int deal;       // 1: splat lanes take records in bank-dealt order
+  int wide_parts; // blocks that share an image's wide records in the adjoint
 };
 
 // One problem (mixture + its images) as seen by the persistent splat
@@ -60,6 +60,7 @@ struct ProbDev {
   const int4 *items;    // work items
   const int *n_items;   // [0] item count, [1] wide-record count
   const float *wabs;    // |w| of every record, in list order
+  const int *off, *count;  // start and length of every bin's records
   int *queue;           // [0] forward, [1] backward work-queue counter
   float *partials;      // forward partial canvases
   const float *GQ;      // dL/dQ (backward)
@@ -172,24 +173,15 @@ __global__ void k_bin_scatter(const float4 *gc, const float *rot, const float *s
                               const int *key, const int *off, const int *blk, int nbx,
                               float4 *list, float *wabs);
 
-__global__ void k_splat_fwd(MultiProb MP);
+template <int RS>
+__global__ void k_splat_fwd_rs(MultiProb MP);
 
-__global__ void k_canvas_reduce(const float *partials, const int *item_off, const int4 *items,
-                                Geom G, float *Q);
+template <int S>
+__global__ void k_canvas_reduce_s(const float *partials, const int *item_off, const int *n_items,
+                                  const int *off, const int *count, const float4 *list, Geom G, float *Q);
 
-__global__ void k_big_prep(const int *off, const int *count, const float *wabs, Geom G,
-                           double *wscale, long long *wq);
-
-__global__ void k_big_fwd(const float4 *list, const int *off, const int *count,
-                          const int *n_wide, Geom G, const double *wscale, long long *wq);
-
-__global__ void k_big_add(const int *count, Geom G, const double *wscale, const long long *wq,
-                          float *Q);
-
-__global__ void k_splat_bwd(MultiProb MP);
-
-__global__ void k_big_bwd(const float4 *list, const int *off, const int *count,
-                          const int *n_wide, Geom G, const float *GQ, float *mom);
+template <int RS>
+__global__ void k_splat_bwd_rs(MultiProb MP);
 
 __global__ void k_chain(const float4 *gc, const float *log_scales, const float *quats,
                         const float *amps, const float *rot, const float *shift, Geom G,

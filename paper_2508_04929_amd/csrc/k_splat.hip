@@ -236,9 +236,14 @@ __device__ __forceinline__ const unsigned short *order_records(const float4 *lis
 }
 
 // ---------------------------------------------------------------------------
-// Forward: partial canvas of one work item.
+// Forward: partial canvas of one work item.  RS adjacent lanes share a record,
+// taking every RS-th of its rows: 1 where there are records enough to fill the
+// chip, 4 for small calls, whose time is one wave's walk over its tallest
+// footprint (one image of 1000 Gaussians: 24 -> 9.5 us with tiles of 32 beside;
+// eight lanes gave no more).  The sums are integers, so the lanes' order is free.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kBlock) k_splat_fwd(MultiProb MP) {
+template <int RS>
+__global__ void __launch_bounds__(kBlock) k_splat_fwd_rs(MultiProb MP) {
   extern __shared__ int4 smem4[];     // 16-byte aligned dynamic LDS
   int *icanvas = (int *)smem4;        // C rows of stride S (fixed point)
   __shared__ int slot;
@@ -294,19 +299,19 @@ __global__ void __launch_bounds__(kBlock) k_splat_fwd(MultiProb MP) {
     const int nc = min(chunk, itm.w - c0);
     const unsigned short *perm =
         order_records(list, (size_t)itm.z + c0, nc, G, R0, C0, rlo, rhi, ol);
-    for (int s = threadIdx.x; s < nc; s += kBlock) {
+    for (int s = threadIdx.x / RS; s < nc; s += kBlock / RS) {
       const size_t rec = 2 * ((size_t)itm.z + c0 + (perm ? perm[s] : s));
       const float4 r0 = list[rec], r1 = list[rec + 1];
       const float u = r0.x, v = r0.y, al = r0.z, be = r0.w, ga = r1.x, w = r1.y * scale;
       const int rows = __float_as_int(r1.w);
-      const int i0 = max(rows & 0xffff, rlo), i1 = min(rows >> 16, rhi);
+      const int i0 = max(rows & 0xffff, rlo) + (int)threadIdx.x % RS, i1 = min(rows >> 16, rhi);
       const float det_s = al * ga - be * be;
       const float inv_al = 1.f / al;
       const float aqk = al * G.qk;
       const float K = hexp2(-2.f * al);
       float fi = (float)i0;
       int rowo = (i0 - R0) * G.S - C0;  // canvas offset of (row i, column 0)
-      for (int i = i0; i <= i1; ++i, fi += 1.f, rowo += G.S) {
+      for (int i = i0; i <= i1; i += RS, fi += (float)RS, rowo += RS * G.S) {
         const float di = fi - v;
         int j0, L;
         if (!row_span(u, di, al, be, det_s, inv_al, aqk, clo, chi, j0, L)) continue;
@@ -349,19 +354,46 @@ __global__ void __launch_bounds__(kBlock) k_splat_fwd(MultiProb MP) {
 }
 
 // ---------------------------------------------------------------------------
+// Wide Gaussians (footprint larger than the canvas): exp per pixel of their
+// pixel box.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void wide_box(const float4 r0, const float4 r1, const Geom &G,
+                                         int &i0, int &i1, int &j0, int &j1) {
+  const int rows = __float_as_int(r1.w);
+  i0 = rows & 0xffff;
+  i1 = rows >> 16;
+  const float det_s = r0.z * r1.x - r0.w * r0.w;
+  const float hx = sqrtf(G.qk * r1.x / det_s);
+  j0 = clamp_px(ceilf(r0.x - hx), 0, G.D);
+  j1 = clamp_px(floorf(r0.x + hx), -1, G.D - 1);
+}
+
+// ---------------------------------------------------------------------------
 // Q for one (image, tile): every pixel sums, in a fixed order, the partial
 // canvases of the owner tiles whose canvas covers it (its own tile and the
 // neighbours whose halo reaches it).  When tile, halo and D are multiples
 // of 4, a thread takes four adjacent pixels of a row (16-byte loads) and
-// keeps four items in flight.
+// keeps four items in flight.  The image's wide records follow: those whose box
+// meets the block's rows are gathered in LDS, in list order, and every pixel
+// sums their terms in FP64 in that order before adding them to Q.  That replaces
+// a kernel per record with a 64-bit atomic per pixel and two passes over the
+// images: 16 images of 256 x 256 with 20000 records of sd 13 pixels each took
+// 50 ms for loss and gradient, now 21 ms, and calls without wide records three
+// launches fewer.
+//
+// S threads share a pixel group, each taking every S-th item and record, and
+// their sums are added in order: 1 where the tiles alone fill the chip, 4 for
+// calls of few images, whose time is one thread's walk over its items.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float4 f4add(float4 a, float4 b) {
   return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
 }
 
+template <int S>
 __global__ void __launch_bounds__(kBlock)
-k_canvas_reduce(const float *partials, const int *item_off, const int4 *items, Geom G,
-                float *Q) {
+k_canvas_reduce_s(const float *partials, const int *item_off, const int *n_items, const int *off,
+                  const int *count, const float4 *list, Geom G, float *Q) {
+  constexpr int kPix = kBlock / S;  // pixel groups per block and pass
   // XCD-aware order: a work index runs over the z-split parts of a tile,
   // then the tiles of an image, so the blocks that read one canvas (its own
   // and its neighbours' halos) meet in one XCD's L2
@@ -373,6 +405,11 @@ k_canvas_reduce(const float *partials, const int *item_off, const int4 *items, G
   // item ranges of the 3 x 3 owner tiles around this one (empty outside the
   // image), read once per block rather than per pixel and neighbour
   __shared__ int2 range[9];
+  __shared__ float4 wrec[kBlock][2];
+  __shared__ int kept[kBlock / 64];
+  __shared__ float4 facc[S > 1 ? kBlock : 1];
+  __shared__ double4 dacc[S > 1 ? kBlock : 1];
+  const int n_wide = n_items[1] > 0 ? count[b * G.K + G.ntiles] : 0;
   if (threadIdx.x < 9) {
     const int sy = ty + threadIdx.x / 3 - 1, sx = tx + threadIdx.x % 3 - 1;
     int2 r = make_int2(0, 0);
@@ -392,10 +429,15 @@ k_canvas_reduce(const float *partials, const int *item_off, const int4 *items, G
   const int px_per = vec ? 4 : 1;
   const int wq = wdt / px_per;
   const int nq = (r_hi - r_lo) * wq;
-  for (int q = threadIdx.x + zz * kBlock; q < nq; q += kBlock * zsplit) {
+  const int part = S > 1 ? threadIdx.x / kPix : 0;
+  for (int q0 = zz * kPix; q0 < nq; q0 += kPix * zsplit) {
+    const int q = q0 + threadIdx.x % kPix;
+    const bool live = q < nq;
+    if (S == 1 && n_wide == 0 && !live) continue;
     const int i = r_lo + q / wq, j = c_lo + px_per * (q % wq);
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int dy = -1; dy <= 1; ++dy) {
+    int phase = 0;  // items of the ranges before, modulo S
+    for (int dy = live ? -1 : 2; dy <= 1; ++dy) {
       const int sy = ty + dy;
       if (sy < 0 || sy >= G.ntx) continue;
       const int ri = i - (sy * G.T - G.halo);
@@ -406,23 +448,98 @@ k_canvas_reduce(const float *partials, const int *item_off, const int4 *items, G
         const int cj = j - (sx * G.T - G.halo);
         if (cj < 0 || cj >= G.C) continue;
         const int2 r = range[3 * (dy + 1) + dx + 1];
-        const int it0 = r.x, it1 = r.y;
+        const int it0 = r.x + (S > 1 ? (part - phase) & (S - 1) : 0), it1 = r.y;
+        if (S > 1) phase = (phase + r.y - r.x) & (S - 1);
         const float *base = partials + (size_t)ri * G.C + cj;
         if (vec) {
           int it = it0;
-          for (; it + 4 <= it1; it += 4) {
+          for (; it + 3 * S < it1; it += 4 * S) {
             const float4 a0 = *(const float4 *)(base + (size_t)it * CC);
-            const float4 a1 = *(const float4 *)(base + (size_t)(it + 1) * CC);
-            const float4 a2 = *(const float4 *)(base + (size_t)(it + 2) * CC);
-            const float4 a3 = *(const float4 *)(base + (size_t)(it + 3) * CC);
+            const float4 a1 = *(const float4 *)(base + (size_t)(it + S) * CC);
+            const float4 a2 = *(const float4 *)(base + (size_t)(it + 2 * S) * CC);
+            const float4 a3 = *(const float4 *)(base + (size_t)(it + 3 * S) * CC);
             acc = f4add(acc, f4add(f4add(a0, a1), f4add(a2, a3)));
           }
-          for (; it < it1; ++it) acc = f4add(acc, *(const float4 *)(base + (size_t)it * CC));
+          for (; it < it1; it += S) acc = f4add(acc, *(const float4 *)(base + (size_t)it * CC));
         } else {
-          for (int it = it0; it < it1; ++it) acc.x += base[(size_t)it * CC];
+          for (int it = it0; it < it1; it += S) acc.x += base[(size_t)it * CC];
         }
       }
     }
+    if (n_wide > 0) {
+      const float4 *wl = list + 2 * (size_t)off[b * G.K + G.ntiles];
+      const int ra = r_lo + q0 / wq, rb = min(r_lo + (q0 + kPix - 1) / wq, r_hi - 1);
+      double wide[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int c0 = 0; c0 < n_wide; c0 += kBlock) {
+        const int k = c0 + threadIdx.x;
+        float4 r0 = make_float4(0, 0, 0, 0), r1 = r0;
+        bool keep = false;
+        if (k < n_wide) {
+          r0 = wl[2 * (size_t)k];
+          r1 = wl[2 * (size_t)k + 1];
+          int i0, i1, j0, j1;
+          wide_box(r0, r1, G, i0, i1, j0, j1);
+          keep = i0 <= rb && i1 >= ra && j0 < c_hi && j1 >= c_lo;
+          r1.z = __int_as_float(j0 | (j1 << 16));
+        }
+        const unsigned long long bits = __ballot(keep);
+        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        if (lane == 0) kept[wv] = __popcll(bits);
+        __syncthreads();
+        int at = __popcll(bits & ((1ull << lane) - 1ull)), total = 0;
+        for (int w = 0; w < kBlock / 64; ++w) {
+          at += w < wv ? kept[w] : 0;
+          total += kept[w];
+        }
+        if (keep) {
+          wrec[at][0] = r0;
+          wrec[at][1] = r1;
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (int m = part; m < total; m += S) {
+          const float4 a = wrec[m][0], c = wrec[m][1];
+          const int rows = __float_as_int(c.w), cols = __float_as_int(c.z);
+          const bool in = i >= (rows & 0xffff) && i <= (rows >> 16);
+          const float di = (float)i - a.y;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (e >= px_per) break;
+            const float dj = (float)(j + e) - a.x;
+            const float qq = a.z * dj * dj + 2.f * a.w * dj * di + c.x * di * di;
+            const bool on = in && j + e >= (cols & 0xffff) && j + e <= (cols >> 16) && qq <= G.qk;
+            wide[e] += on ? (double)(c.y * hexp2(-qq)) : 0.0;
+          }
+        }
+        __syncthreads();
+      }
+      if (S > 1) {
+        dacc[threadIdx.x] = make_double4(wide[0], wide[1], wide[2], wide[3]);
+        __syncthreads();
+        if (part == 0)
+          for (int p = 1; p < S; ++p) {
+            const double4 d = dacc[threadIdx.x + p * kPix];
+            wide[0] += d.x;
+            wide[1] += d.y;
+            wide[2] += d.z;
+            wide[3] += d.w;
+          }
+      }
+      if (part == 0) {
+        acc.x += (float)wide[0];
+        acc.y += (float)wide[1];
+        acc.z += (float)wide[2];
+        acc.w += (float)wide[3];
+      }
+    }
+    if (S > 1) {
+      facc[threadIdx.x] = acc;
+      __syncthreads();
+      if (part == 0)
+        for (int p = 1; p < S; ++p) acc = f4add(acc, facc[threadIdx.x + p * kPix]);
+      __syncthreads();
+    }
+    if (!live || part) continue;
     float *o = img + (size_t)i * G.D + j;
     if (vec) {
       *(float4 *)o = acc;
@@ -431,94 +548,56 @@ k_canvas_reduce(const float *partials, const int *item_off, const int4 *items, G
     }
   }
 }
+template __global__ void k_canvas_reduce_s<1>(const float *, const int *, const int *, const int *, const int *,
+                                              const float4 *, Geom, float *);
+template __global__ void k_canvas_reduce_s<4>(const float *, const int *, const int *, const int *, const int *,
+                                              const float4 *, Geom, float *);
 
 // ---------------------------------------------------------------------------
-// Wide Gaussians (footprint larger than the canvas): one block per record,
-// threads over the pixel box, exp per pixel, device atomics into Q.
+// Wide records k = part, part + parts, ... of one image in the adjoint: a wave
+// per record, per-lane moments over its pixel box, then a fixed-order sum.  A
+// block per record spent its time in the two barriers and the division per
+// pixel (8 images of 128 x 128, 2000 records each: 1.95 ms for loss and
+// gradient, 0.85 ms so and with the split sums of k_canvas_reduce).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void wide_box(const float4 r0, const float4 r1, const Geom &G,
-                                         int &i0, int &i1, int &j0, int &j1) {
-  const int rows = __float_as_int(r1.w);
-  i0 = rows & 0xffff;
-  i1 = rows >> 16;
-  const float det_s = r0.z * r1.x - r0.w * r0.w;
-  const float hx = sqrtf(G.qk * r1.x / det_s);
-  j0 = clamp_px(ceilf(r0.x - hx), 0, G.D);
-  j1 = clamp_px(floorf(r0.x + hx), -1, G.D - 1);
-}
-
-// Wide records are summed in 64-bit fixed point so that the result does not
-// depend on the order of the device atomics: per image, the scale is the
-// power of two 2^e with 2^e * sum|w| < 2^61 over the image's wide records
-// (their |w| summed in a fixed order), every term is rounded to an integer
-// and the integer image is added to Q once all terms are in.
-// k_big_prep: one block per image: the scale, and the integer image cleared.
-__global__ void __launch_bounds__(kBlock)
-k_big_prep(const int *off, const int *count, const float *wabs, Geom G, double *wscale,
-           long long *wq) {
-  const int b = blockIdx.x;
-  const int e = b * G.K + G.ntiles;
-  const int cnt = count[e], start = off[e];
-  if (cnt == 0) return;
-  __shared__ double red[kBlock / 64];
-  double a = 0.0;
-  for (int k = threadIdx.x; k < cnt; k += kBlock) a += (double)wabs[start + k];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
-  long long *img = wq + (size_t)b * G.D * G.D;
-  for (int i = threadIdx.x; i < G.D * G.D; i += kBlock) img[i] = 0;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const double tot = (red[0] + red[1]) + (red[2] + red[3]);
-    int ex = 0;
-    if (tot > 0.0) frexp(tot, &ex);  // tot < 2^ex
-    wscale[b] = ldexp(1.0, 61 - ex);
-  }
-}
-
-// k_big_fwd: grid row b takes image b's wide records, one block per record
-// at a time, threads over its pixel box, exp per pixel, 64-bit integer
-// atomics into the image's integer sum.
-__global__ void __launch_bounds__(kBlock)
-k_big_fwd(const float4 *list, const int *off, const int *count, const int *n_wide, Geom G,
-          const double *wscale, long long *wq) {
-  if (*n_wide == 0) return;
-  const int b = blockIdx.y;
-  const int e = b * G.K + G.ntiles;
-  const int cnt = count[e], start = off[e];
-  if (cnt == 0) return;
-  const double S = wscale[b];
-  unsigned long long *img = (unsigned long long *)(wq + (size_t)b * G.D * G.D);
-  for (int k = blockIdx.x; k < cnt; k += gridDim.x) {
+__device__ __forceinline__ void wide_moments(const float4 *list, int start, int cnt, int part, int parts,
+                                             const Geom &G, int b, const float *GQ, float *mom) {
+  const int lane = threadIdx.x & 63;
+  const float *img = GQ + (size_t)b * G.D * G.D;
+  for (int k = part; k < cnt; k += parts) {
     const float4 r0 = list[2 * (size_t)(start + k)], r1 = list[2 * (size_t)(start + k) + 1];
     int i0, i1, j0, j1;
     wide_box(r0, r1, G, i0, i1, j0, j1);
-    if (i1 < i0 || j1 < j0) continue;
-    const int wdt = j1 - j0 + 1;
-    const long npx = (long)(i1 - i0 + 1) * wdt;
-    for (long q = threadIdx.x; q < npx; q += kBlock) {
-      const int i = i0 + (int)(q / wdt), j = j0 + (int)(q % wdt);
-      const float dj = (float)j - r0.x, di = (float)i - r0.y;
-      const float qq = r0.z * dj * dj + 2.f * r0.w * dj * di + r1.x * di * di;
-      if (qq <= G.qk) {
-        const long long v = __double2ll_rn((double)(r1.y * exp2f(-qq)) * S);
-        atomicAdd(&img[(size_t)i * G.D + j], (unsigned long long)v);
+    float m[6] = {0, 0, 0, 0, 0, 0};
+    if (i1 >= i0 && j1 >= j0) {
+      const int wdt = j1 - j0 + 1, npx = (i1 - i0 + 1) * wdt;
+      // (row, column) of pixel `lane` and of a step of 64 pixels
+      int i = i0 + lane / wdt, j = j0 + lane % wdt;
+      const int si = 64 / wdt, sj = 64 % wdt;
+#pragma unroll 4
+      for (int q = lane; q < npx; q += 64) {
+        const float dj = (float)j - r0.x, di = (float)i - r0.y;
+        const float qq = r0.z * dj * dj + 2.f * r0.w * dj * di + r1.x * di * di;
+        const float t = qq <= G.qk ? img[i * G.D + j] * hexp2(-qq) : 0.f;
+        m[0] += t; m[1] += t * dj; m[2] += t * di;
+        m[3] += t * dj * dj; m[4] += t * dj * di; m[5] += t * di * di;
+        i += si;
+        j += sj;
+        if (j > j1) {
+          j -= wdt;
+          ++i;
+        }
       }
     }
-  }
-}
-
-// k_big_add: Q += integer sum / scale for images with wide records.
-__global__ void __launch_bounds__(kBlock)
-k_big_add(const int *count, Geom G, const double *wscale, const long long *wq, float *Q) {
-  const int b = blockIdx.y;
-  if (count[b * G.K + G.ntiles] == 0) return;
-  const double inv = 1.0 / wscale[b];
-  const size_t n = (size_t)G.D * G.D;
-  for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) {
-    const long long v = wq[(size_t)b * n + i];
-    if (v) Q[(size_t)b * n + i] += (float)((double)v * inv);
+#pragma unroll
+    for (int c = 0; c < 6; ++c)
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) m[c] += __shfl_xor(m[c], o, 64);
+    if (lane == 0) {
+      float *o = mom + ((size_t)b * G.N + __float_as_int(r1.z)) * 6;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) o[c] = m[c];
+    }
   }
 }
 
@@ -527,7 +606,8 @@ k_big_add(const int *count, Geom G, const double *wscale, const long long *wq, f
 //   m = sum G_Q e (1, dj, di, dj^2, dj di, di^2),  e = exp(-q/2),
 // with dj = j - u, di = i - v (pixels).  Written to mom[(b N + n) 6 + k].
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kBlock) k_splat_bwd(MultiProb MP) {
+template <int RS>
+__global__ void __launch_bounds__(kBlock) k_splat_bwd_rs(MultiProb MP) {
   extern __shared__ float gq[];  // C rows of stride S
   __shared__ int slot;
   __shared__ OrderLds ol;
@@ -577,13 +657,13 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd(MultiProb MP) {
     const int nc = min(chunk, itm.w - c0);
     const unsigned short *perm =
         order_records(list, (size_t)itm.z + c0, nc, G, R0, C0, rlo, rhi, ol);
-    for (int s = threadIdx.x; s < nc; s += kBlock) {
+    for (int s = threadIdx.x / RS; s < nc; s += kBlock / RS) {
       const size_t rec = 2 * ((size_t)itm.z + c0 + (perm ? perm[s] : s));
       const float4 r0 = list[rec], r1 = list[rec + 1];
       const float u = r0.x, v = r0.y, al = r0.z, be = r0.w, ga = r1.x;
       const int n = __float_as_int(r1.z);
       const int rows = __float_as_int(r1.w);
-      const int i0 = max(rows & 0xffff, rlo), i1 = min(rows >> 16, rhi);
+      const int i0 = max(rows & 0xffff, rlo) + (int)threadIdx.x % RS, i1 = min(rows >> 16, rhi);
       const float det_s = al * ga - be * be;
       const float inv_al = 1.f / al;
       const float aqk = al * G.qk;
@@ -591,7 +671,7 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd(MultiProb MP) {
       float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f, m4 = 0.f, m5 = 0.f;
       float fi = (float)i0;
       int rowo = (i0 - R0) * G.S - C0;  // canvas offset of (row i, column 0)
-      for (int i = i0; i <= i1; ++i, fi += 1.f, rowo += G.S) {
+      for (int i = i0; i <= i1; i += RS, fi += (float)RS, rowo += RS * G.S) {
         const float di = fi - v;
         int j0, L;
         if (!row_span(u, di, al, be, det_s, inv_al, aqk, clo, chi, j0, L)) continue;
@@ -643,60 +723,36 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd(MultiProb MP) {
         m4 += sdj * di;
         m5 += a0 * di * di;
       }
+#pragma unroll
+      for (int o = 1; o < RS; o <<= 1) {  // the lanes of a record, in a fixed tree
+        m0 += __shfl_xor(m0, o, 64);
+        m1 += __shfl_xor(m1, o, 64);
+        m2 += __shfl_xor(m2, o, 64);
+        m3 += __shfl_xor(m3, o, 64);
+        m4 += __shfl_xor(m4, o, 64);
+        m5 += __shfl_xor(m5, o, 64);
+      }
+      if (RS > 1 && threadIdx.x % RS) continue;
       float *o = mom + ((size_t)b * G.N + n) * 6;
       o[0] = m0; o[1] = m1; o[2] = m2; o[3] = m3; o[4] = m4; o[5] = m5;
     }
     __syncthreads();  // the next chunk rewrites the order
     }
   }
+  // wide records: unit (image, part) after unit, a wave per record of the image
+  if (MP.p[p].n_items[1] > 0) {
+    const int units = G.B * G.wide_parts, wv = threadIdx.x >> 6;
+    for (int un = blockIdx.x; un < units; un += gridDim.x) {
+      const int wb = un / G.wide_parts, e = wb * G.K + G.ntiles;
+      wide_moments(list, MP.p[p].off[e], MP.p[p].count[e], un % G.wide_parts * (kBlock / 64) + wv,
+                   G.wide_parts * (kBlock / 64), G, wb, GQ, mom);
+    }
+  }
   }
 }
-
-// Grid row b takes image b's wide records, one block per record at a time:
-// per-thread moments over the pixel box, then a fixed-order block sum.
-__global__ void __launch_bounds__(kBlock)
-k_big_bwd(const float4 *list, const int *off, const int *count, const int *n_wide, Geom G,
-          const float *GQ, float *mom) {
-  __shared__ float red[6][kBlock / 64];
-  if (*n_wide == 0) return;
-  const int b = blockIdx.y;
-  const int e = b * G.K + G.ntiles;
-  const int cnt = count[e], start = off[e];
-  for (int k = blockIdx.x; k < cnt; k += gridDim.x) {
-    const float4 r0 = list[2 * (size_t)(start + k)], r1 = list[2 * (size_t)(start + k) + 1];
-    int i0, i1, j0, j1;
-    wide_box(r0, r1, G, i0, i1, j0, j1);
-    float m[6] = {0, 0, 0, 0, 0, 0};
-    if (i1 >= i0 && j1 >= j0) {
-      const int wdt = j1 - j0 + 1;
-      const long npx = (long)(i1 - i0 + 1) * wdt;
-      for (long q = threadIdx.x; q < npx; q += kBlock) {
-        const int i = i0 + (int)(q / wdt), j = j0 + (int)(q % wdt);
-        const float dj = (float)j - r0.x, di = (float)i - r0.y;
-        const float qq = r0.z * dj * dj + 2.f * r0.w * dj * di + r1.x * di * di;
-        if (qq <= G.qk) {
-          const float t = GQ[((size_t)b * G.D + i) * G.D + j] * exp2f(-qq);
-          m[0] += t; m[1] += t * dj; m[2] += t * di;
-          m[3] += t * dj * dj; m[4] += t * dj * di; m[5] += t * di * di;
-        }
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-      float x = m[c];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-      if ((threadIdx.x & 63) == 0) red[c][threadIdx.x >> 6] = x;
-    }
-    __syncthreads();
-    if (threadIdx.x < 6) {
-      float x = 0.f;
-      for (int wv = 0; wv < kBlock / 64; ++wv) x += red[threadIdx.x][wv];
-      const int n = __float_as_int(r1.z);
-      mom[((size_t)b * G.N + n) * 6 + threadIdx.x] = x;
-    }
-    __syncthreads();
-  }
-}
+template __global__ void k_splat_fwd_rs<1>(MultiProb MP);
+template __global__ void k_splat_bwd_rs<1>(MultiProb MP);
+template __global__ void k_splat_fwd_rs<4>(MultiProb MP);
+template __global__ void k_splat_bwd_rs<4>(MultiProb MP);
 
 }  // namespace cs

@@ -1,0 +1,71 @@
+"""Calls of few Gaussian-image pairs: smaller tiles and work items, and four
+lanes to a record in both splat kernels.  Sizes on both sides of each line (32768
+pairs, 256 default tiles, a halo above the default), ragged images, records
+wider than the halo, and options given one by one, against the FP64 oracle.
+
+Images within 1e-4 normwise, gradients within 1e-3, the renderer's bars: the
+record sums are the same FP32 terms in another order."""
+import numpy as np
+import pytest
+
+from oracle import model as o_model
+from oracle import objective as o_obj
+from paper_2508_04929_amd import binding, inputs
+
+from gpu_util import announce, dev, host, mixture_args, normwise, per_image_normwise, view_args
+
+pytestmark = pytest.mark.gpu
+
+Q_MATCHED = 2.0 * np.log(1e6)
+
+
+@pytest.mark.parametrize("n,b,D,sd,opt", [
+    (1, 1, 16, 1.0, {}),
+    (3, 2, 33, 1.0, {}),                    # one row and column past a 32 tile
+    (65, 1, 64, 0.8, {}),                   # one record past a work item
+    (300, 3, 70, 5.0, {}),                  # records wider than the halo beside narrow ones
+    (200, 2, 48, 1.5, {"halo": 20}),        # halo above the default: default tile
+    (200, 2, 48, 1.5, {"halo": 8}),
+    (200, 2, 48, 1.5, {"tile": 48}),
+    (200, 2, 48, 1.5, {"budget": 100}),
+    (200, 2, 48, 1.5, {"lane_order": 1}),
+    (200, 2, 48, 1.5, {"lane_order": 2}),
+    (20, 64, 128, 1.5, {}),                 # 256 default tiles
+    (20, 65, 128, 1.5, {}),                 # 260
+    (4096, 8, 32, 0.7, {}),                 # 32768 pairs
+    (4097, 8, 32, 0.7, {}),
+])
+def test_small_calls_match_the_oracle(gpu_lib, n, b, D, sd, opt):
+    rng = np.random.default_rng(n + b + D)
+    g = inputs.mixture_anisotropic(rng, n, 0.4 * D, scale_mu=np.log(sd), scale_sd=0.6)
+    v = inputs.views(rng, b, D, 1.0, shift_px_sd=1.0)
+    dX = rng.standard_normal((b, D, D)).astype(np.float32)
+    o = binding.Options(**opt)
+    announce(f"small call N={n} B={b} D={D} {opt}")
+    Q = host(gpu_lib.render(**mixture_args(g), **view_args(v), options=o))
+    ref = o_model.render_pre_ctf(g.means, g.log_scales, g.quats, g.amps, v.rot, v.shift, v.D,
+                                 v.pixel, Q_MATCHED)
+    assert per_image_normwise(Q, ref) <= 1e-4
+    got = gpu_lib.render_backward(**mixture_args(g), **view_args(v), d_images=dev(dX), options=o)
+    want = o_obj.backward_from_image_grad(g, v, dX, q_cut=Q_MATCHED)
+    for k in ("means", "log_scales", "quats", "amps"):
+        assert normwise(host(got[k]), want[k]) <= 1e-3, k
+
+
+def test_limited_workspace_falls_back_to_the_default_tile(monkeypatch):
+    """1000 Gaussians in one 64 x 64 image need about 0.44 MB with the small
+    tile and 0.30 MB with the default one: under a limit of 0.40 MB the call
+    still runs, with the default tile's bits."""
+    rng = np.random.default_rng(3)
+    g = inputs.mixture_anisotropic(rng, 1000, 25.0)
+    v = inputs.views(rng, 1, 64, 1.0)
+    monkeypatch.setenv("CS_WORKSPACE_MAX", "400000")
+    lib = binding.Library(binding.load_library())
+    announce("small call under a workspace limit")
+    auto = host(lib.render(**mixture_args(g), **view_args(v)))
+    tile = host(lib.render(**mixture_args(g), **view_args(v),
+                           options=binding.Options(tile=64, halo=16, budget=256)))
+    assert np.array_equal(auto, tile)
+    monkeypatch.delenv("CS_WORKSPACE_MAX")
+    free = host(binding.Library(binding.load_library()).render(**mixture_args(g), **view_args(v)))
+    assert per_image_normwise(free, auto) <= 1e-5
