@@ -34,6 +34,8 @@ constexpr int kMinAutoBudget = 256;
 //   16 images of 64 x 64  2000: 106 -> 80, 16000: 118 -> 90, 32000: 122 -> 102, 48000: 125 -> 116
 //   32 images of 128^2    2000: 117 -> 106, 16000: 133 -> 123, 32000: 137 -> 137, 48000: 142 -> 154
 constexpr int64_t kSmallPairs = 32768;
+// ... and up to this many build the Gaussians in the counting pass.
+constexpr int64_t kBuildPairs = 262144;
 constexpr int kSmallTile = 32, kSmallBudget = 64, kSmallTiles = 256;
 
 // Automatic work-item size: the default budget while N B Gaussian-image
@@ -146,6 +148,7 @@ struct Plan {
   float *loss = nullptr;
   float *images_out = nullptr;
   cs_grads grads{};
+  AdamDev adam{};  // set: the chain rule steps the parameters and writes no gradients
   float *Q() const { return (float *)(ws + L.Q); }
   const float *GQ() const {
     if (mode == BACKWARD && !ctf) return d_images;
@@ -309,6 +312,12 @@ Geom make_geom(const cs_gaussians *g, const cs_views *v, const cs_options *opt, 
   G.scale_act = g->scale_act;
   G.amp_act = g->amp_act;
   G.deal = opt ? opt->lane_order : 0;
+  // eight images per block of the binning kernels, fewer where that would
+  // leave the chip with less than two blocks per CU (16 images of 64 x 64 and
+  // 1000 Gaussians: 8 blocks took 10 us to scatter, 64 blocks take 4; 37 images
+  // and 2000 Gaussians 12 and 7)
+  G.ipb = kImgPerBinBlock;
+  while (G.ipb > 1 && (int64_t)cdiv(G.N, kBlock) * cdiv(G.B, G.ipb) < 512) G.ipb /= 2;
   G.wide_parts = std::max(4, (512 + G.B - 1) / G.B);
   return G;
 }
@@ -354,22 +363,42 @@ bool has_grads(const cs_grads &g) {
 // ---------------------------------------------------------------------------
 // Enqueue helpers
 // ---------------------------------------------------------------------------
-int launch_binning(cs_ctx *ctx, const Plan &P, hipStream_t st) {
+// The CTF table of a plan as extra blocks of a binning kernel: a few entries
+// per thread where there are enough images to fill the chip.
+CtfTable ctf_table(const Plan &P) {
+  CtfTable c{};
+  if (!P.ctf) return c;
+  const size_t per = (size_t)P.G.D * (P.G.D / 2 + 1);
+  c.ctf = make_ctf(P.ctf);
+  c.L = P.G.D;
+  c.pixel = ctf_pixel(P.ctf, P.G.pixel);
+  c.blocks = (int)cdiv(per, kBlock * (P.G.B >= 16 ? 8 : 1));
+  c.table = (float *)(P.ws + P.L.ctf);
+  return c;
+}
+
+int launch_binning(cs_ctx *ctx, const Plan &P, bool table, hipStream_t st) {
   const Geom &G = P.G;
   const Layout &L = P.L;
   char *ws = P.ws;
   float4 *gc = (float4 *)(ws + L.gc);
   int *count = (int *)(ws + L.count);
   const size_t BK = (size_t)G.B * G.K;
-  const size_t nb = std::max<size_t>((size_t)G.N, BK);
-  TLAUNCH(k_build, dim3(cdiv(nb, kBlock)), dim3(kBlock), 0, st, P.g.means, P.g.log_scales,
-          P.g.quats, P.g.amps, G, gc, count, (int)BK);
-  const dim3 bgrid(cdiv(G.N, kBlock), cdiv(G.B, kImgPerBinBlock));
-  const size_t hist_bytes = (size_t)kImgPerBinBlock * G.K * 4;
-  TLAUNCH(k_bin_count, bgrid, dim3(kBlock), hist_bytes, st, gc, P.v.rot, P.v.shift, G,
-          (int *)(ws + L.key), (int *)(ws + L.blk), L.nbx);
-  // small problems scan their per-block counts inside k_scan
-  const bool fuse = BK <= 64;
+  const CtfTable c = table ? ctf_table(P) : CtfTable{};
+  const dim3 bgrid(cdiv(G.N, kBlock), cdiv(G.B, G.ipb));
+  // calls that do not fill the chip build the Gaussians in the counting pass
+  // (a launch is 4 to 6 of their 40 to 200 us, of larger ones below one percent)
+  typedef void (*CountFn)(GaussDev, float4 *, const float *, const float *, Geom, int *, int *, int, CtfTable);
+  const bool build = (int64_t)G.N * G.B <= kBuildPairs;
+  const CountFn k_bin_count = build ? &k_bin_count_b<true> : &k_bin_count_b<false>;
+  if (!build)
+    TLAUNCH(k_build, dim3(bgrid.x), dim3(kBlock), 0, st, gauss_dev(P.g), G, gc);
+  TLAUNCH(k_bin_count, dim3(bgrid.x + cdiv((size_t)c.blocks * G.B, bgrid.y), bgrid.y), dim3(kBlock),
+          (size_t)G.ipb * G.K * 4, st, gauss_dev(P.g), gc, P.v.rot, P.v.shift, G,
+          (int *)(ws + L.key), (int *)(ws + L.blk), L.nbx, c);
+  // few counts are scanned inside k_scan: that adds 1 to 4 us to its one block
+  // where the other kernel's launch costs 4 to 6
+  const bool fuse = BK <= 64 || (BK <= 256 && L.nbx <= 64) || (BK <= 2048 && L.nbx <= 16);
   if (!fuse)
     TLAUNCH(k_bin_blockscan, dim3((unsigned)BK), dim3(kBlock), 0, st, (int *)(ws + L.blk), L.nbx,
             count);
@@ -489,11 +518,14 @@ int launch_backward_finish(cs_ctx *ctx, const Plan &P, hipStream_t st) {
   float *mom = (float *)(ws + P.L.mom);
   TLAUNCH(k_chain, dim3(cdiv(G.N, 64)), dim3(kBlock), 0, st, (const float4 *)(ws + P.L.gc),
           P.g.log_scales, P.g.quats, P.g.amps, P.v.rot, P.v.shift, G, (const int *)(ws + P.L.key),
-          mom, P.grads.means, P.grads.log_scales, P.grads.quats, P.grads.amps);
+          mom, P.grads.means, P.grads.log_scales, P.grads.quats, P.grads.amps, P.adam);
   if (P.grads.rot || P.grads.shift) {
     const int nblk = cdiv(G.N, kBlock * kPoseGauss);
     float *part = (float *)(ws + P.L.pose_part);
-    TLAUNCH(k_pose_grad_part, dim3(nblk, cdiv(G.B, kPoseImg)), dim3(kBlock), 0, st,
+    // fewer images per block where that leaves too few blocks (37 images and
+    // 2000 Gaussians: 40 blocks took 27 us, 296 blocks take 7)
+    const int groups = std::max<int>(cdiv(G.B, kPoseImg), std::min<int>(G.B, cdiv(1024, nblk)));
+    TLAUNCH(k_pose_grad_part, dim3(nblk, groups), dim3(kBlock), 0, st,
             (const float4 *)(ws + P.L.gc), P.v.rot, P.v.shift, G, (const int *)(ws + P.L.key), mom,
             part);
     TLAUNCH(k_pose_grad_sum, dim3(G.B), dim3(kBlock), 0, st, (const float *)part, G.B, nblk,
@@ -580,9 +612,14 @@ int launch_loss(cs_ctx *ctx, const Plan &P, hipStream_t st) {
             gscale, loss_part);
     parts = G.D;
   }
-  TLAUNCH(k_loss_reduce, dim3(G.B), dim3(256), 0, st, (const float *)loss_part, G.B, parts,
-          (float)scale, P.loss);
-  if (G.B > 1) TLAUNCH(k_loss_total, dim3(1), dim3(256), 0, st, P.loss, G.B);
+  if (G.B <= 32 && (int64_t)G.B * parts <= 32768) {  // one launch instead of two, 2.6 us for 16 images
+    TLAUNCH(k_loss_small, dim3(1), dim3(1024), 0, st, (const float *)loss_part, G.B, parts, (float)scale,
+            P.loss);
+  } else {
+    TLAUNCH(k_loss_reduce, dim3(G.B), dim3(256), 0, st, (const float *)loss_part, G.B, parts,
+            (float)scale, P.loss);
+    if (G.B > 1) TLAUNCH(k_loss_total, dim3(1), dim3(256), 0, st, P.loss, G.B);
+  }
   return CS_OK;
 }
 
@@ -646,7 +683,10 @@ int enqueue(cs_ctx *ctx, Plan *plans, int count, const Plan **sel, hipStream_t s
   int rc;
   for (int i = 0; i < count; ++i) {
     Plan &P = plans[i];
-    if (P.ctf) {
+    // the CTF table is filled by the binning's first launch, unless its
+    // image gradients have to be filtered before that or nothing is binned
+    const bool bins = P.fwd || P.bwd, table = P.ctf && bins && P.mode != BACKWARD;
+    if (P.ctf && !table) {
       rc = launch_ctf_table(ctx, P, st);
       if (rc) return rc;
     }
@@ -654,8 +694,8 @@ int enqueue(cs_ctx *ctx, Plan *plans, int count, const Plan **sel, hipStream_t s
       rc = launch_ctf_roundtrip(ctx, P, P.d_images, P.Q(), st);
       if (rc) return rc;
     }
-    if (P.fwd || P.bwd) {
-      rc = launch_binning(ctx, P, st);
+    if (bins) {
+      rc = launch_binning(ctx, P, table, st);
       if (rc) return rc;
     }
   }
@@ -786,11 +826,12 @@ std::string signature(cs_ctx *ctx, const cs_problem *problems, int count) {
 }
 
 int run_loss_problems(cs_ctx *ctx, const cs_problem *problems, int count, bool use_graph,
-                      hipStream_t st) {
+                      hipStream_t st, const AdamDev *adam = nullptr) {
   std::vector<Plan> plans(count);
   for (int i = 0; i < count; ++i) {
     int rc = make_loss_plan(ctx, problems[i], plans[i]);
     if (rc) return rc;
+    if (adam) plans[i].adam = *adam;
   }
   int rc = place(ctx, plans, st);
   if (rc) return rc;
@@ -886,8 +927,8 @@ int time_problem(cs_ctx *ctx, const cs_problem &pr, int reps, hipStream_t st, do
 
 namespace cs {
 
-int run_loss(cs_ctx *ctx, const cs_problem &pr, bool use_graph, hipStream_t st) {
-  return run_loss_problems(ctx, &pr, 1, use_graph, st);
+int run_loss(cs_ctx *ctx, const cs_problem &pr, bool use_graph, const AdamDev *adam, hipStream_t st) {
+  return run_loss_problems(ctx, &pr, 1, use_graph, st, adam);
 }
 
 }  // namespace cs
@@ -1193,8 +1234,8 @@ int cs_adam_step(cs_ctx *ctx, float *params, const float *grads, float *m, float
   const float bc1 = (float)(1.0 - std::pow((double)b1, (double)step));
   const float bc2 = (float)(1.0 - std::pow((double)b2, (double)step));
   hipStream_t st = (hipStream_t)stream;
-  TLAUNCH(k_adam, dim3(cdiv(count, kBlock)), dim3(kBlock), 0, st, params, grads, m, v, count, lr,
-          b1, b2, eps, bc1, bc2);
+  TLAUNCH(k_adam, dim3(cdiv(count, kBlock)), dim3(kBlock), 0, st,
+          AdamDev{params, m, v, lr, b1, b2, eps, bc1, bc2}, grads, count);
   return CS_OK;
 }
 
@@ -1214,8 +1255,7 @@ int cs_pair_count(cs_ctx *ctx, const cs_gaussians *g, const cs_views *v, const c
   if (rc) return rc;
   char *ws = (char *)ctx->ws;
   float4 *gc = (float4 *)(ws + L.gc);
-  TLAUNCH(k_build, dim3(cdiv(G.N, kBlock)), dim3(kBlock), 0, st, g->means, g->log_scales,
-          g->quats, g->amps, G, gc, (int *)nullptr, 0);
+  TLAUNCH(k_build, dim3(cdiv(G.N, kBlock)), dim3(kBlock), 0, st, gauss_dev(*g), G, gc);
   TLAUNCH(k_pair_count, dim3(cdiv(G.N, kBlock), G.B), dim3(kBlock), 0, st, gc, v->rot, v->shift,
           G, (unsigned long long *)counts);
   return CS_OK;

@@ -70,7 +70,11 @@ int get_twiddles(cs_ctx *ctx, int L, const float2 **out);  // cached device tabl
 CtfDev make_ctf(const cs_ctf *ctf);                        // disabled when ctf is null
 float ctf_pixel(const cs_ctf *ctf, float geometry_pixel);  // pixel of the CTF's frequency grid
 // one loss-and-gradient problem, eager or through the context's graph cache
-int run_loss(cs_ctx *ctx, const cs_problem &pr, bool use_graph, hipStream_t st);
+// One problem; with `adam` (eager calls only) the chain rule steps the
+// parameters, whose gradients are not written.
+int run_loss(cs_ctx *ctx, const cs_problem &pr, bool use_graph, const AdamDev *adam, hipStream_t st);
+
+inline GaussDev gauss_dev(const cs_gaussians &g) { return GaussDev{g.means, g.log_scales, g.quats, g.amps}; }
 
 }  // namespace cs
 

@@ -28,7 +28,7 @@ namespace cs {
 
 constexpr int kBlock = 256;                  // threads per block of every splat kernel
 constexpr float kHalfLog2e = 0.72134752044448170368f;  // 0.5 * log2(e)
-constexpr int kImgPerBinBlock = 8;           // images per block in the binning kernels
+constexpr int kImgPerBinBlock = 8;           // most images per block in the binning kernels
 
 // Geometry of one rendering call, passed by value to the kernels.
 struct Geom {
@@ -49,6 +49,7 @@ struct Geom {
   int scale_act;  // 0 exp, 1 softplus
   int amp_act;    // 0 identity, 1 softplus
   int deal;       // 1: splat lanes take records in bank-dealt order
+  int ipb;        // images per block of the binning kernels (at most kImgPerBinBlock)
   int wide_parts; // blocks that share an image's wide records in the adjoint
 };
 
@@ -82,6 +83,26 @@ struct CtfDev {
   double w;              // amplitude contrast
   double bfactor;        // Angstrom^2
   int enabled;
+};
+
+// Gaussian parameters (cs_gaussians' arrays).
+struct GaussDev {
+  const float *means, *log_scales, *quats, *amps;
+};
+
+// The CTF table of a call (H^ / D^2 per image), filled by `blocks` blocks per
+// image of a kernel that does other work too; none when blocks = 0.
+struct CtfTable {
+  CtfDev ctf;
+  int L, blocks;
+  float pixel;
+  float *table;
+};
+
+// Adam over flat arrays, bias corrections precomputed (p null: none).
+struct AdamDev {
+  float *p, *m, *v;
+  float lr, b1, b2, eps, bc1, bc2;
 };
 
 // ----------------------------------------------------------------------------
@@ -158,11 +179,11 @@ __device__ __forceinline__ int clamp_px(float x, int lo, int hi) {
 // Kernels (definitions in k_geom.hip, k_splat.hip, k_fft.hip)
 // ----------------------------------------------------------------------------
 
-__global__ void k_build(const float *means, const float *log_scales, const float *quats,
-                        const float *amps, Geom G, float4 *gc, int *zero_buf, int zero_count);
+__global__ void k_build(GaussDev p, Geom G, float4 *gc);
 
-__global__ void k_bin_count(const float4 *gc, const float *rot, const float *shift, Geom G,
-                            int *key, int *blk, int nbx);
+template <bool BUILD>
+__global__ void k_bin_count_b(GaussDev p, float4 *gc, const float *rot, const float *shift, Geom G,
+                              int *key, int *blk, int nbx, CtfTable c);
 
 __global__ void k_bin_blockscan(int *blk, int nbx, int *count);
 
@@ -186,9 +207,9 @@ __global__ void k_splat_bwd_rs(MultiProb MP);
 __global__ void k_chain(const float4 *gc, const float *log_scales, const float *quats,
                         const float *amps, const float *rot, const float *shift, Geom G,
                         const int *key, const float *mom, float *g_means, float *g_log_scales,
-                        float *g_quats, float *g_amps);
+                        float *g_quats, float *g_amps, AdamDev A);
 
-constexpr int kPoseImg = 8;    // images per block of k_pose_grad_part
+constexpr int kPoseImg = 8;    // most images per block of k_pose_grad_part
 constexpr int kPoseGauss = 4;  // Gaussians per thread of k_pose_grad_part
 __global__ void k_pose_grad_part(const float4 *gc, const float *rot, const float *shift, Geom G,
                                  const int *key, const float *mom, float *part);
@@ -197,8 +218,7 @@ __global__ void k_pose_grad_sum(const float *part, int B, int nblk, float *g_rot
 __global__ void k_pair_count(const float4 *gc, const float *rot, const float *shift, Geom G,
                              unsigned long long *counts);
 
-__global__ void k_adam(float *p, const float *g, float *m, float *v, int64_t n, float lr,
-                       float b1, float b2, float eps, float bc1, float bc2);
+__global__ void k_adam(AdamDev A, const float *g, int64_t n);
 
 __global__ void k_fill(float *p, int64_t n, float value);
 
@@ -237,6 +257,8 @@ FftLaunch fft_rows_launch(int L, int64_t B);                                 // 
 FftLaunch fft_cols_launch(int L, int64_t columns, int64_t B, bool may_narrow);
 
 __global__ void k_loss_reduce(const float *loss_part, int B, int parts, float scale, float *loss);
+
+__global__ void k_loss_small(const float *loss_part, int B, int parts, float scale, float *loss);
 
 __global__ void k_loss_total(float *loss, int B);
 

@@ -243,6 +243,30 @@ k_loss_reduce(const float *loss_part, int B, int parts, float scale, float *loss
   }
 }
 
+// Both in one block, for few partials: a wave per image, then the total.
+__global__ void __launch_bounds__(1024)
+k_loss_small(const float *loss_part, int B, int parts, float scale, float *loss) {
+  __shared__ double red[16];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double tot = 0.0;
+  for (int b = wv; b < B; b += 16) {
+    double s = 0.0;
+    for (int k = lane; k < parts; k += 64) s += (double)loss_part[(size_t)b * parts + k];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    const float v = (float)(scale * s);
+    if (lane == 0) loss[b] = v;
+    tot += (double)v;
+  }
+  if (lane == 0) red[wv] = tot;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int w = 0; w < 16; ++w) s += red[w];
+    loss[B] = (float)s;
+  }
+}
+
 __global__ void __launch_bounds__(256) k_loss_total(float *loss, int B) {
   __shared__ double red[4];
   double s = 0.0;

@@ -1,6 +1,7 @@
 // Per-Gaussian and per-(image, Gaussian) kernels: covariance construction,
 // projection, owner-tile binning, the per-Gaussian gradient chain, the pair
 // counter and Adam.
+#include "cs_ctf_dev.hpp"
 #include "cs_internal.hpp"
 
 namespace cs {
@@ -8,38 +9,58 @@ namespace cs {
 // ---------------------------------------------------------------------------
 // Eq. 5 with the Sec. 3.3.1 activations: s = exp(l) or softplus(l),
 // A = a or softplus(a), q normalised, Sigma = R diag(s)^2 R^T.
-// Also clears `zero_count` ints of zero_buf (the binning counters).
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kBlock)
-k_build(const float *means, const float *log_scales, const float *quats, const float *amps,
-        Geom G, float4 *gc, int *zero_buf, int zero_count) {
-  const int n = blockIdx.x * kBlock + threadIdx.x;
-  if (n < zero_count) zero_buf[n] = 0;
-  if (n >= G.N) return;
+__device__ __forceinline__ void build_one(const GaussDev &p, int n, const Geom &G, float4 &g0, float4 &g1,
+                                          float4 &g2) {
   float s[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const float l = log_scales[3 * n + k];
+    const float l = p.log_scales[3 * n + k];
     s[k] = G.scale_act ? softplusf(l) : __expf(l);
   }
-  const float a = amps[n];
+  const float a = p.amps[n];
   const float A = G.amp_act ? softplusf(a) : a;
-  float w = quats[4 * n + 0], x = quats[4 * n + 1], y = quats[4 * n + 2], z = quats[4 * n + 3];
-  const float inv = 1.f / fmaxf(sqrtf(w * w + x * x + y * y + z * z), 1e-12f);
+  float w = p.quats[4 * n + 0], x = p.quats[4 * n + 1], y = p.quats[4 * n + 2], z = p.quats[4 * n + 3];
+  // (explicit fused multiply-adds: the same bits in every kernel)
+  const float inv = 1.f / fmaxf(sqrtf(fmaf(z, z, fmaf(y, y, fmaf(w, w, x * x)))), 1e-12f);
   w *= inv; x *= inv; y *= inv; z *= inv;
   const float R[3][3] = {
-      {1.f - 2.f * (y * y + z * z), 2.f * (x * y - w * z), 2.f * (x * z + w * y)},
-      {2.f * (x * y + w * z), 1.f - 2.f * (x * x + z * z), 2.f * (y * z - w * x)},
-      {2.f * (x * z - w * y), 2.f * (y * z + w * x), 1.f - 2.f * (x * x + y * y)}};
+      {fmaf(fmaf(y, y, z * z), -2.f, 1.f), 2.f * fmaf(x, y, -(w * z)), 2.f * fmaf(x, z, w * y)},
+      {2.f * fmaf(x, y, w * z), fmaf(fmaf(x, x, z * z), -2.f, 1.f), 2.f * fmaf(y, z, -(w * x))},
+      {2.f * fmaf(x, z, -(w * y)), 2.f * fmaf(y, z, w * x), fmaf(fmaf(x, x, y * y), -2.f, 1.f)}};
   float M[3][3];
 #pragma unroll
   for (int r = 0; r < 3; ++r)
 #pragma unroll
     for (int k = 0; k < 3; ++k) M[r][k] = R[r][k] * s[k];
-  auto sig = [&](int i, int j) { return M[i][0] * M[j][0] + M[i][1] * M[j][1] + M[i][2] * M[j][2]; };
-  gc[3 * n + 0] = make_float4(means[3 * n + 0], means[3 * n + 1], means[3 * n + 2], A);
-  gc[3 * n + 1] = make_float4(sig(0, 0), sig(0, 1), sig(0, 2), sig(1, 1));
-  gc[3 * n + 2] = make_float4(sig(1, 2), sig(2, 2), 0.f, 0.f);
+  auto sig = [&](int i, int j) { return fmaf(M[i][2], M[j][2], fmaf(M[i][0], M[j][0], M[i][1] * M[j][1])); };
+  g0 = make_float4(p.means[3 * n + 0], p.means[3 * n + 1], p.means[3 * n + 2], A);
+  g1 = make_float4(sig(0, 0), sig(0, 1), sig(0, 2), sig(1, 1));
+  g2 = make_float4(sig(1, 2), sig(2, 2), 0.f, 0.f);
+}
+
+// Block `blk` of the CTF table's c.blocks blocks per image.
+__device__ __forceinline__ void ctf_table_block(const CtfTable &c, int blk) {
+  const int b = blk / c.blocks, part = blk - b * c.blocks;
+  const int Dh = c.L / 2 + 1, per = c.L * Dh;
+  const float norm = 1.f / ((float)c.L * (float)c.L);
+  const CtfGrid g = ctf_grid(c.L, c.pixel, c.ctf);
+  const CtfParticle q = ctf_particle(c.ctf, b);
+  float *row = c.table + (size_t)b * per;
+  for (int r = part * kBlock + threadIdx.x; r < per; r += c.blocks * kBlock) {
+    const int ky = r / Dh, kx = r % Dh;
+    row[r] = ctf_value(ky, kx, c.L, g, c.ctf, q) * norm;
+  }
+}
+
+__global__ void __launch_bounds__(kBlock) k_build(GaussDev p, Geom G, float4 *gc) {
+  const int n = blockIdx.x * kBlock + threadIdx.x;
+  if (n >= G.N) return;
+  float4 g0, g1, g2;
+  build_one(p, n, G, g0, g1, g2);
+  gc[3 * n + 0] = g0;
+  gc[3 * n + 1] = g1;
+  gc[3 * n + 2] = g2;
 }
 
 __device__ __forceinline__ void load_pose(const float *rot, const float *shift, int b,
@@ -73,26 +94,45 @@ __device__ __forceinline__ int tile_key(const Proj &P, const Geom &G) {
 
 // ---------------------------------------------------------------------------
 // Binning pass 1: key per (image, Gaussian) and per-block bin counts.
-// Block (x, y): Gaussians [256 x, 256 x + 256) of images [8 y, 8 y + 8);
+// Block (x, y): Gaussians [256 x, 256 x + 256) of images [ipb y, ipb y + ipb);
 // blk[(b K + k) nbx + x] receives the block's count of bin k of image b
 // (every bin, zeros included), so that a scan over x orders the bin's
 // entries by Gaussian index.
 // ---------------------------------------------------------------------------
+// A block takes G.ipb images (8, or fewer where that leaves too few blocks).
+// Blocks from column nbx on fill the call's CTF table, which nothing before the
+// column pass waits for.  With BUILD a block also builds its Gaussians, from as
+// many bytes as their built form has (the first image group stores that form for
+// the passes that follow).
+template <bool BUILD>
 __global__ void __launch_bounds__(kBlock)
-k_bin_count(const float4 *gc, const float *rot, const float *shift, Geom G, int *key,
-            int *blk, int nbx) {
-  extern __shared__ int hist[];  // [kImgPerBinBlock][K]
+k_bin_count_b(GaussDev p, float4 *gc, const float *rot, const float *shift, Geom G, int *key, int *blk,
+              int nbx, CtfTable c) {
+  extern __shared__ int hist[];  // [ipb][K]
+  if ((int)blockIdx.x >= nbx) {
+    const int at = (blockIdx.x - nbx) * gridDim.y + blockIdx.y;
+    if (at < c.blocks * G.B) ctf_table_block(c, at);
+    return;
+  }
   const int n = blockIdx.x * kBlock + threadIdx.x;
-  const int b0 = blockIdx.y * kImgPerBinBlock;
-  for (int i = threadIdx.x; i < kImgPerBinBlock * G.K; i += kBlock) hist[i] = 0;
+  const int b0 = blockIdx.y * G.ipb;
+  for (int i = threadIdx.x; i < G.ipb * G.K; i += kBlock) hist[i] = 0;
   __syncthreads();
   float4 g0 = make_float4(0, 0, 0, 0), g1 = g0, g2 = g0;
   if (n < G.N) {
-    g0 = gc[3 * n];
-    g1 = gc[3 * n + 1];
-    g2 = gc[3 * n + 2];
+    if (BUILD) build_one(p, n, G, g0, g1, g2);
+    if (BUILD && blockIdx.y == 0) {
+      gc[3 * n] = g0;
+      gc[3 * n + 1] = g1;
+      gc[3 * n + 2] = g2;
+    }
+    if (!BUILD) {
+      g0 = gc[3 * n];
+      g1 = gc[3 * n + 1];
+      g2 = gc[3 * n + 2];
+    }
   }
-  for (int bi = 0; bi < kImgPerBinBlock; ++bi) {
+  for (int bi = 0; bi < G.ipb; ++bi) {
     const int b = b0 + bi;
     if (b >= G.B) break;
     if (n < G.N) {
@@ -106,11 +146,16 @@ k_bin_count(const float4 *gc, const float *rot, const float *shift, Geom G, int 
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kImgPerBinBlock * G.K; i += kBlock) {
+  for (int i = threadIdx.x; i < G.ipb * G.K; i += kBlock) {
     const int b = b0 + i / G.K;
     if (b < G.B) blk[((size_t)b * G.K + i % G.K) * nbx + blockIdx.x] = hist[i];
   }
 }
+
+template __global__ void k_bin_count_b<false>(GaussDev, float4 *, const float *, const float *, Geom, int *,
+                                              int *, int, CtfTable);
+template __global__ void k_bin_count_b<true>(GaussDev, float4 *, const float *, const float *, Geom, int *,
+                                             int *, int, CtfTable);
 
 // Per bin: exclusive scan of the per-block counts over blocks (in place)
 // and the bin total.  One block of 256 threads per bin.
@@ -183,24 +228,51 @@ k_scan(int *count, Geom G, int *off, int4 *items, int *item_off, int *n_items,
   const int total = G.B * G.K;
   if (blk) {
     // few (image, tile) entries: the per-entry scans of k_bin_blockscan, one
-    // wave per entry (the same integers, one launch fewer)
+    // thread or wave per entry (the same integers, one launch fewer)
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    for (int e = wid; e < total; e += 16) {
-      int *row = blk + (size_t)e * nbx;
-      int carry = 0;
-      for (int base = 0; base < nbx; base += 64) {
-        const int x = base + lane;
-        const int v = x < nbx ? row[x] : 0;
-        int inc = v;
+    if (nbx <= 16) {
+      for (int e = threadIdx.x; e < total; e += 1024) {
+        int *row = blk + (size_t)e * nbx;
+        int v[16];
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int y = __shfl_up(inc, o, 64);
-          if (lane >= o) inc += y;
+        for (int x = 0; x < 16; ++x) v[x] = x < nbx ? row[x] : 0;
+        int carry = 0;
+#pragma unroll
+        for (int x = 0; x < 16; ++x) {
+          if (x < nbx) row[x] = carry;
+          carry += v[x];
         }
-        if (x < nbx) row[x] = carry + inc - v;
-        carry += __shfl(inc, 63, 64);
+        count[e] = carry;
       }
-      if (lane == 0) count[e] = carry;
+    } else {
+      // four entries in flight per wave
+      for (int e0 = wid; e0 < total; e0 += 64) {
+        int carry[4] = {0, 0, 0, 0};
+        for (int base = 0; base < nbx; base += 64) {
+          const int x = base + lane;
+          int v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int e = e0 + 16 * u;
+            v[u] = e < total && x < nbx ? blk[(size_t)e * nbx + x] : 0;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int e = e0 + 16 * u;
+            int inc = v[u];
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+              const int y = __shfl_up(inc, o, 64);
+              if (lane >= o) inc += y;
+            }
+            if (e < total && x < nbx) blk[(size_t)e * nbx + x] = carry[u] + inc - v[u];
+            carry[u] += __shfl(inc, 63, 64);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (lane == 0 && e0 + 16 * u < total) count[e0 + 16 * u] = carry[u];
+      }
     }
     __syncthreads();
   }
@@ -257,7 +329,7 @@ k_bin_scatter(const float4 *gc, const float *rot, const float *shift, Geom G, co
   extern __shared__ unsigned long long wmask[];
   const int n = blockIdx.x * kBlock + threadIdx.x;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int b0 = blockIdx.y * kImgPerBinBlock;
+  const int b0 = blockIdx.y * G.ipb;
   float4 g0 = make_float4(0, 0, 0, 0), g1 = g0, g2 = g0;
   if (n < G.N) {
     g0 = gc[3 * n];
@@ -273,7 +345,7 @@ k_bin_scatter(const float4 *gc, const float *rot, const float *shift, Geom G, co
 #pragma unroll
   for (int bi = 0; bi < kImgPerBinBlock; ++bi) {
     const int b = b0 + bi;
-    kk[bi] = (n < G.N && b < G.B) ? key[(size_t)b * G.N + n] : -1;
+    kk[bi] = (n < G.N && b < G.B && bi < G.ipb) ? key[(size_t)b * G.N + n] : -1;
   }
 #pragma unroll
   for (int bi = 0; bi < kImgPerBinBlock; ++bi) {
@@ -286,7 +358,7 @@ k_bin_scatter(const float4 *gc, const float *rot, const float *shift, Geom G, co
 #pragma unroll
   for (int bi = 0; bi < kImgPerBinBlock; ++bi) {
     const int b = b0 + bi;
-    if (b >= G.B) break;
+    if (b >= G.B || bi >= G.ipb) break;
     for (int i = threadIdx.x; i < (kBlock / 64) * G.K; i += kBlock) wmask[i] = 0ull;
     __syncthreads();
     const int k = kk[bi];
@@ -362,10 +434,20 @@ __device__ __forceinline__ ScreenGrad screen_grad(const Proj &P, const float *m,
   return r;
 }
 
+// One parameter's Adam step (explicit fused multiply-adds: the kernels that
+// share it give the same bits).
+__device__ __forceinline__ void adam_update(const AdamDev &A, int64_t i, float g) {
+  const float mi = fmaf(A.b1, A.m[i], (1.f - A.b1) * g);
+  const float vi = fmaf(A.b2, A.v[i], (1.f - A.b2) * g * g);
+  A.m[i] = mi;
+  A.v[i] = vi;
+  A.p[i] -= A.lr * (mi / A.bc1) / (sqrtf(vi / A.bc2) + A.eps);
+}
+
 __global__ void __launch_bounds__(kBlock)
 k_chain(const float4 *gc, const float *log_scales, const float *quats, const float *amps,
         const float *rot, const float *shift, Geom G, const int *key, const float *mom,
-        float *g_means, float *g_log_scales, float *g_quats, float *g_amps) {
+        float *g_means, float *g_log_scales, float *g_quats, float *g_amps, AdamDev A) {
   // 64 Gaussians per block; wave w of the four sums the images b = w mod 4
   // (coalesced 64-Gaussian rows of every image, four times the waves of one
   // thread per Gaussian), the partial sums meet in LDS in a fixed order
@@ -474,6 +556,22 @@ k_chain(const float4 *gc, const float *log_scales, const float *quats, const flo
   const float dqz = 2.f * (-2.f * qz * dR[0][0] - qw * dR[0][1] + qx * dR[0][2] + qw * dR[1][0] -
                            2.f * qz * dR[1][1] + qy * dR[1][2] + qx * dR[2][0] + qy * dR[2][1]);
   const float dot = qw * dqw + qx * dqx + qy * dqy + qz * dqz;
+  const float ga = dw_sum * (G.amp_act ? sigmoidf_(amps[n]) : 1.f);
+  const float gq[4] = {(dqw - qw * dot) * iq, (dqx - qx * dot) * iq, (dqy - qy * dot) * iq, (dqz - qz * dot) * iq};
+  if (A.p) {
+    // the optimiser's step on this Gaussian's 11 parameters in place of its
+    // gradient (batch-1 training: one launch and a round trip fewer)
+    const int64_t N = G.N, at = n;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      adam_update(A, 3 * at + k, dmu[k]);
+      adam_update(A, 3 * N + 3 * at + k, ds[k] * dsdl[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) adam_update(A, 6 * N + 4 * at + k, gq[k]);
+    adam_update(A, 10 * N + at, ga);
+    return;
+  }
   if (g_means) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) g_means[3 * n + k] = dmu[k];
@@ -483,15 +581,10 @@ k_chain(const float4 *gc, const float *log_scales, const float *quats, const flo
     for (int k = 0; k < 3; ++k) g_log_scales[3 * n + k] = ds[k] * dsdl[k];
   }
   if (g_quats) {
-    g_quats[4 * n + 0] = (dqw - qw * dot) * iq;
-    g_quats[4 * n + 1] = (dqx - qx * dot) * iq;
-    g_quats[4 * n + 2] = (dqy - qy * dot) * iq;
-    g_quats[4 * n + 3] = (dqz - qz * dot) * iq;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) g_quats[4 * n + k] = gq[k];
   }
-  if (g_amps) {
-    const float a = amps[n];
-    g_amps[n] = dw_sum * (G.amp_act ? sigmoidf_(a) : 1.f);
-  }
+  if (g_amps) g_amps[n] = ga;
 }
 
 // ---------------------------------------------------------------------------
@@ -524,8 +617,9 @@ k_pose_grad_part(const float4 *gc, const float *rot, const float *shift, Geom G,
       g2[j] = gc[3 * n + 2];
     }
   }
-  const int b1 = min(G.B, (int)(blockIdx.y + 1) * kPoseImg);
-  for (int b = blockIdx.y * kPoseImg; b < b1; ++b) {
+  // (up to kPoseImg images per block)
+  const int per = (G.B + gridDim.y - 1) / gridDim.y, b1 = min(G.B, (int)(blockIdx.y + 1) * per);
+  for (int b = blockIdx.y * per; b < b1; ++b) {
     float v[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // t_x, t_y, P_0 (3), P_1 (3)
     float p0[3], p1[3], tx, ty;
     load_pose(rot, shift, b, p0, p1, tx, ty);
@@ -675,18 +769,10 @@ k_pair_count(const float4 *gc, const float *rot, const float *shift, Geom G,
   }
 }
 
-// Adam (Alg. 1 "Adam(grad L)"), bias corrections precomputed on the host.
-__global__ void __launch_bounds__(kBlock)
-k_adam(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1, float b2,
-       float eps, float bc1, float bc2) {
+// Adam (Alg. 1 "Adam(grad L)") over a flat array.
+__global__ void __launch_bounds__(kBlock) k_adam(AdamDev A, const float *g, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+  if (i < n) adam_update(A, i, g[i]);
 }
 
 __global__ void __launch_bounds__(kBlock) k_fill(float *p, int64_t n, float value) {

@@ -147,13 +147,18 @@ int cs_train_sequential(cs_ctx *ctx, float *params, float *adam_m, float *adam_v
       }
       pr.loss = (loss && k + 1 < count) ? loss + k : lossbuf;
     }
-    rc = run_loss(ctx, pr, graph, st);
-    if (rc) return rc;
     const int64_t step = step0 + k + 1;
     const float bc1 = (float)(1.0 - std::pow((double)b1, (double)step));
     const float bc2 = (float)(1.0 - std::pow((double)b2, (double)step));
-    TLAUNCH(k_adam, dim3(cdivt((int64_t)np, kBlock)), dim3(kBlock), 0, st, params, (const float *)g,
-            adam_m, adam_v, (int64_t)np, lr, b1, b2, eps, bc1, bc2);
+    const AdamDev adam{params, adam_m, adam_v, lr, b1, b2, eps, bc1, bc2};
+    // in the chain rule's kernel, but not in a replayed graph, which cannot hold
+    // the step's bias corrections, nor before a check of the gradients
+    const bool apart = graph || ctx->debug_checks;
+    rc = run_loss(ctx, pr, graph, apart ? nullptr : &adam, st);
+    if (rc) return rc;
+    if (apart)
+      TLAUNCH(k_adam, dim3(cdivt((int64_t)np, kBlock)), dim3(kBlock), 0, st, adam, (const float *)g,
+              (int64_t)np);
   }
   if (loss) TLAUNCH(k_train_record, dim3(1), dim3(64), 0, st, (const float *)lossbuf, loss + count - 1);
   return CS_OK;

@@ -56,8 +56,7 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
       G.N = N;
       G.scale_act = g->scale_act;
       G.amp_act = g->amp_act;
-      TLAUNCH(k_build, dim3(cdivv(N, kBlock)), dim3(kBlock), 0, st, g->means, g->log_scales,
-              g->quats, g->amps, G, gc, (int *)nullptr, 0);
+      TLAUNCH(k_build, dim3(cdivv(N, kBlock)), dim3(kBlock), 0, st, gauss_dev(*g), G, gc);
       TLAUNCH(k_vox_prep, dim3(nwp), dim3(256), 0, st, (const float4 *)gc, V, rec,
               (int4 *)(w + o_box), (double *)(w + o_wp));
       TLAUNCH(k_vox_count, dim3(cdivv(N, 4)), dim3(256), 0, st, (const int4 *)(w + o_box), V, cnt);

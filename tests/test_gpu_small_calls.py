@@ -8,11 +8,12 @@ record sums are the same FP32 terms in another order."""
 import numpy as np
 import pytest
 
+from oracle import ctf as o_ctf
 from oracle import model as o_model
 from oracle import objective as o_obj
 from paper_2508_04929_amd import binding, inputs
 
-from gpu_util import announce, dev, host, mixture_args, normwise, per_image_normwise, view_args
+from gpu_util import announce, ctf_arg, dev, host, mixture_args, normwise, per_image_normwise, view_args
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +70,31 @@ def test_limited_workspace_falls_back_to_the_default_tile(monkeypatch):
     monkeypatch.delenv("CS_WORKSPACE_MAX")
     free = host(binding.Library(binding.load_library()).render(**mixture_args(g), **view_args(v)))
     assert per_image_normwise(free, auto) <= 1e-5
+
+
+@pytest.mark.parametrize("n,b,D", [
+    (4096, 6, 108),    # 16 Gaussian blocks: a thread scans a bin's counts
+    (4097, 6, 108),    # 17: a wave does
+    (1000, 16, 128),   # 272 bins of 4 blocks: a thread
+    (4500, 7, 216),    # 350 bins of 18 blocks: a kernel of its own
+    (17000, 1, 64),    # 67 blocks: a wave in two steps
+    (2048, 128, 24),   # 262144 pairs: Gaussians built while counting
+    (2049, 128, 24),   # more: beforehand
+    (50, 32, 36),      # 32 images: losses in one launch
+    (50, 33, 36),      # 33: in two
+])
+def test_binning_and_loss_lines_match_the_oracle(gpu_lib, n, b, D):
+    """Images within 1e-4 normwise and losses within 1e-4, the renderer's bars."""
+    rng = np.random.default_rng(n + b + D)
+    g = inputs.mixture_anisotropic(rng, n, 0.4 * D, scale_mu=np.log(0.7))
+    v = inputs.views(rng, b, D, 1.0)
+    announce(f"binning and loss N={n} B={b} D={D}")
+    ref = o_ctf.apply_ctf(o_model.render_pre_ctf(g.means, g.log_scales, g.quats, g.amps, v.rot, v.shift, v.D,
+                                                 v.pixel, Q_MATCHED), o_ctf.ctf_grid_for(v))
+    Y = (0.5 * ref + ref.std() * rng.standard_normal(ref.shape)).astype(np.float32)
+    loss, _, X = gpu_lib.loss_and_grad(**mixture_args(g), **view_args(v), observed=dev(Y), ctf=ctf_arg(v),
+                                       want_grads=False, want_images=True)
+    assert per_image_normwise(host(X), ref) <= 1e-4
+    per, _ = o_obj.loss_from_images(ref, Y, "sum")
+    np.testing.assert_allclose(host(loss)[:-1], per, rtol=1e-4)
+    np.testing.assert_allclose(host(loss)[-1], per.sum(), rtol=1e-4)
