@@ -26,17 +26,22 @@ constexpr int kDefaultTile = 64;
 constexpr int kDefaultHalo = 16;
 constexpr int kDefaultBudget = 2048;
 constexpr int kMinAutoBudget = 256;
-// Calls of at most this many Gaussian-image pairs give four lanes to a record,
-// and smaller tiles and work items to images of few tiles (see make_geom): such
-// a call lasts as long as one wave's walk over its tallest record.  Loss and
-// gradient, us, default tile and one lane -> this, by pairs:
+// Calls of at most this many Gaussian-image pairs take smaller tiles and work
+// items for images of few tiles (see make_geom): such a call lasts as long as
+// one wave's walk over its tallest record.  Loss and gradient, us, default tile
+// and one lane -> small tile and four lanes per record, by pairs:
 //   one 128 x 128 image   2000: 105 -> 78, 16000: 119 -> 94, 32000: 123 -> 114, 48000: 125 -> 133
 //   16 images of 64 x 64  2000: 106 -> 80, 16000: 118 -> 90, 32000: 122 -> 102, 48000: 125 -> 116
 //   32 images of 128^2    2000: 117 -> 106, 16000: 133 -> 123, 32000: 137 -> 137, 48000: 142 -> 154
 constexpr int64_t kSmallPairs = 32768;
-// ... and up to this many build the Gaussians in the counting pass.
-constexpr int64_t kBuildPairs = 262144;
 constexpr int kSmallTile = 32, kSmallBudget = 64, kSmallTiles = 256;
+// Calls of up to this many pairs, which do not fill the chip, give four lanes to
+// a record of the default tiles too (loss and gradient, us, one lane and four:
+// 8 images of 128 x 128, 40000 pairs: 119 and 105, 320000: 185 and 182; 37 of
+// 64 x 64, 80000: 108 and 103, 320000: 184 and 174; beyond, the four lanes'
+// shares of narrow records run dry: 32 of 128 x 128, 640000: 222 and 226; 256,
+// 5 million: 788 and 856) and build the Gaussians in the counting pass.
+constexpr int64_t kFewPairs = 524288;
 
 // Automatic work-item size: the default budget while N B Gaussian-image
 // pairs fill about a thousand work items, smaller (down to 256) for calls
@@ -325,7 +330,7 @@ Geom make_geom(const cs_gaussians *g, const cs_views *v, const cs_options *opt, 
 // Geometry and workspace of a plan whose problem and passes are set.
 void lay_out(Plan &P, bool small = true) {
   P.G = make_geom(&P.g, &P.v, &P.opt, small);
-  P.rs = (int64_t)P.G.N * P.G.B <= kSmallPairs ? 4 : 1;
+  P.rs = (int64_t)P.G.N * P.G.B <= kFewPairs ? 4 : 1;
   P.L = make_layout(P.G, P.fwd, P.bwd, P.ctf != nullptr);
 }
 
@@ -389,7 +394,7 @@ int launch_binning(cs_ctx *ctx, const Plan &P, bool table, hipStream_t st) {
   // calls that do not fill the chip build the Gaussians in the counting pass
   // (a launch is 4 to 6 of their 40 to 200 us, of larger ones below one percent)
   typedef void (*CountFn)(GaussDev, float4 *, const float *, const float *, Geom, int *, int *, int, CtfTable);
-  const bool build = (int64_t)G.N * G.B <= kBuildPairs;
+  const bool build = (int64_t)G.N * G.B <= kFewPairs;
   const CountFn k_bin_count = build ? &k_bin_count_b<true> : &k_bin_count_b<false>;
   if (!build)
     TLAUNCH(k_build, dim3(bgrid.x), dim3(kBlock), 0, st, gauss_dev(P.g), G, gc);

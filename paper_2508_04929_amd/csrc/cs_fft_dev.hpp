@@ -152,23 +152,35 @@ struct FftVals {
       for (int i = 0; i < R; ++i) f(base + i * Ns, v[m][i]);
     }
   }
-  // twiddles of the earlier passes (tw[k] = exp(-2 pi i k / L)), then the butterflies
-  template <int Ns, bool INV>
-  __device__ __forceinline__ void pass(int t, const float2 *tw) {
+  // twiddles after earlier passes of Ns points (tw[k] = exp(-2 pi i k / L)) ...
+  struct Twiddles {
+    float2 w[kN][R];
+  };
+  template <int Ns>
+  static __device__ __forceinline__ Twiddles twiddles(int t, const float2 *tw) {
+    Twiddles w;
 #pragma unroll
     for (int m = 0; m < kN; ++m) {
       const int j = t + m * P::TS;
-      if (Ns > 1) {
-        const int k = (kJ % P::TS == 0 || j < kJ) ? j % Ns : 0;
+      const int k = (kJ % P::TS == 0 || j < kJ) ? j % Ns : 0;
 #pragma unroll
-        for (int i = 1; i < R; ++i) {
-          float2 w = tw[i * k * (P::L / (Ns * R))];
-          if (INV) w.y = -w.y;
-          v[m][i] = cmul(v[m][i], w);
-        }
-      }
-      dft<R, INV>(v[m]);
+      for (int i = 1; i < R; ++i) w.w[m][i] = tw[i * k * (P::L / (Ns * R))];
     }
+    return w;
+  }
+  template <bool INV>
+  __device__ __forceinline__ void twist(const Twiddles &w) {
+#pragma unroll
+    for (int m = 0; m < kN; ++m)
+#pragma unroll
+      for (int i = 1; i < R; ++i)
+        v[m][i] = cmul(v[m][i], INV ? make_float2(w.w[m][i].x, -w.w[m][i].y) : w.w[m][i]);
+  }
+  // ... and the butterflies
+  template <bool INV>
+  __device__ __forceinline__ void butterflies() {
+#pragma unroll
+    for (int m = 0; m < kN; ++m) dft<R, INV>(v[m]);
   }
 };
 
@@ -195,24 +207,31 @@ struct FftLast {
 template <class P, bool INV, class At>
 __device__ __forceinline__ typename FftLast<P>::Vals fft_run(FftVals<P, P::R0> &a, int t, const float2 *tw,
                                                             At at) {
-  a.template pass<1, INV>(t, tw);
   if constexpr (P::R1 == 1) {
+    a.template butterflies<INV>();
     return a;
   } else {
+    // the twiddles are requested before the barriers that their use follows
+    const auto wb = FftVals<P, P::R1>::template twiddles<P::R0>(t, tw);
+    a.template butterflies<INV>();
     a.template outputs<1>(t, [&](int q, float2 z) { at(q) = z; });
     __syncthreads();
     FftVals<P, P::R1> b;
     b.inputs(t, [&](int q) { return at(q); });
-    b.template pass<P::R0, INV>(t, tw);
+    b.template twist<INV>(wb);
     if constexpr (P::R2 == 1) {
+      b.template butterflies<INV>();
       return b;
     } else {
+      const auto wc = FftVals<P, P::R2>::template twiddles<P::R0 * P::R1>(t, tw);
+      b.template butterflies<INV>();
       __syncthreads();
       b.template outputs<P::R0>(t, [&](int q, float2 z) { at(q) = z; });
       __syncthreads();
       FftVals<P, P::R2> c;
       c.inputs(t, [&](int q) { return at(q); });
-      c.template pass<P::R0 * P::R1, INV>(t, tw);
+      c.template twist<INV>(wc);
+      c.template butterflies<INV>();
       return c;
     }
   }

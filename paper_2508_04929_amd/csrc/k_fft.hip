@@ -144,12 +144,12 @@ k_rows_inv_loss(float2 *spec, const float2 *tw, const float *obs, float *images_
   const size_t row0 = ((size_t)blockIdx.y * L + 2 * w.pr) * L;
   FftVals<P, P::R0> a;
   a.inputs(w.t, [&](int q) { return w.valid ? packed<L>(sa, sa + Dh, q) : make_float2(0.f, 0.f); });
-  auto z = fft_run<P, true>(a, w.t, tw, [&](int q) -> float2 & { return w.template at<P>(q); });
-  // observed values of this thread, requested together
+  // observed values of this thread, requested with the inputs
   typename FftLast<P>::Vals y;
   y.inputs(w.t, [&](int q) {
     return w.valid ? make_float2(obs[row0 + q], obs[row0 + L + q]) : make_float2(0.f, 0.f);
   });
+  auto z = fft_run<P, true>(a, w.t, tw, [&](int q) -> float2 & { return w.template at<P>(q); });
   if (images_out && w.valid)
     z.template outputs<L / FftLast<P>::R>(w.t, [&](int q, float2 v) {
       images_out[row0 + q] = v.x;

@@ -189,31 +189,27 @@ k_bin_blockscan(int *blk, int nbx, int *count) {
   if (threadIdx.x == 0) count[blockIdx.x] = carry;
 }
 
-// Exclusive scan across one block of 1024 threads (16 waves of 64).
-__device__ int block_scan_1024(int val, int *sh, int &total) {
+// Exclusive scans of three values at once across one block of 1024 threads (16
+// waves of 64); tot: their sums.
+__device__ int3 block_scan_1024(int3 val, int3 *sh, int3 &tot) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int x = val;
+  int3 x = val;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
+    const int3 y = make_int3(__shfl_up(x.x, o, 64), __shfl_up(x.y, o, 64), __shfl_up(x.z, o, 64));
+    if (lane >= o) x = make_int3(x.x + y.x, x.y + y.y, x.z + y.z);
   }
   if (lane == 63) sh[wid] = x;
   __syncthreads();
-  if (wid == 0) {
-    int s = lane < 16 ? sh[lane] : 0;
+  int3 pre = make_int3(0, 0, 0);
+  tot = pre;
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      const int y = __shfl_up(s, o, 64);
-      if (lane >= o) s += y;
-    }
-    if (lane < 16) sh[lane] = s;
+  for (int w = 0; w < 16; ++w) {
+    const int3 v = sh[w];
+    if (w < wid) pre = make_int3(pre.x + v.x, pre.y + v.y, pre.z + v.z);
+    tot = make_int3(tot.x + v.x, tot.y + v.y, tot.z + v.z);
   }
-  __syncthreads();
-  const int prefix = wid > 0 ? sh[wid - 1] : 0;
-  total = sh[15];
-  __syncthreads();
-  return prefix + x - val;
+  return make_int3(pre.x + x.x - val.x, pre.y + x.y - val.y, pre.z + x.z - val.z);
 }
 
 // ---------------------------------------------------------------------------
@@ -224,7 +220,8 @@ __device__ int block_scan_1024(int val, int *sh, int &total) {
 __global__ void __launch_bounds__(1024)
 k_scan(int *count, Geom G, int *off, int4 *items, int *item_off, int *n_items,
        int *queues, int *blk, int nbx) {
-  __shared__ int sh[16];
+  __shared__ int3 sh[16];
+  __shared__ int scanned[2048];
   const int total = G.B * G.K;
   if (blk) {
     // few (image, tile) entries: the per-entry scans of k_bin_blockscan, one
@@ -242,7 +239,7 @@ k_scan(int *count, Geom G, int *off, int4 *items, int *item_off, int *n_items,
           if (x < nbx) row[x] = carry;
           carry += v[x];
         }
-        count[e] = carry;
+        count[e] = scanned[e] = carry;
       }
     } else {
       // four entries in flight per wave
@@ -271,7 +268,7 @@ k_scan(int *count, Geom G, int *off, int4 *items, int *item_off, int *n_items,
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (lane == 0 && e0 + 16 * u < total) count[e0 + 16 * u] = carry[u];
+          if (lane == 0 && e0 + 16 * u < total) count[e0 + 16 * u] = scanned[e0 + 16 * u] = carry[u];
       }
     }
     __syncthreads();
@@ -280,17 +277,16 @@ k_scan(int *count, Geom G, int *off, int4 *items, int *item_off, int *n_items,
   const int e0 = min(threadIdx.x * seg, total), e1 = min(e0 + seg, total);
   int s = 0, si = 0, sw = 0;
   for (int e = e0; e < e1; ++e) {
-    const int c = count[e];
+    const int c = blk ? scanned[e] : count[e];
     s += c;
     if (e % G.K < G.ntiles) si += (c + G.budget - 1) / G.budget;
     else sw += c;
   }
-  int tot, itot, wtot;
-  int pre = block_scan_1024(s, sh, tot);
-  int ipre = block_scan_1024(si, sh, itot);
-  block_scan_1024(sw, sh, wtot);
+  int3 tot;
+  const int3 before = block_scan_1024(make_int3(s, si, sw), sh, tot);
+  int pre = before.x, ipre = before.y;
   for (int e = e0; e < e1; ++e) {
-    const int c = count[e];
+    const int c = blk ? scanned[e] : count[e];
     off[e] = pre;
     item_off[e] = ipre;
     const int t = e % G.K;
@@ -303,9 +299,9 @@ k_scan(int *count, Geom G, int *off, int4 *items, int *item_off, int *n_items,
     pre += c;
   }
   if (threadIdx.x == 0) {
-    item_off[total] = itot;
-    n_items[0] = itot;
-    n_items[1] = wtot;  // wide (beyond-halo) records
+    item_off[total] = tot.y;
+    n_items[0] = tot.y;
+    n_items[1] = tot.z;  // wide (beyond-halo) records
     queues[0] = 0;
     queues[1] = 0;
   }
@@ -435,13 +431,16 @@ __device__ __forceinline__ ScreenGrad screen_grad(const Proj &P, const float *m,
 }
 
 // One parameter's Adam step (explicit fused multiply-adds: the kernels that
-// share it give the same bits).
-__device__ __forceinline__ void adam_update(const AdamDev &A, int64_t i, float g) {
-  const float mi = fmaf(A.b1, A.m[i], (1.f - A.b1) * g);
-  const float vi = fmaf(A.b2, A.v[i], (1.f - A.b2) * g * g);
-  A.m[i] = mi;
-  A.v[i] = vi;
-  A.p[i] -= A.lr * (mi / A.bc1) / (sqrtf(vi / A.bc2) + A.eps);
+// share it give the same bits): m and v in place, returns the new parameter.
+__device__ __forceinline__ float adam_step(const AdamDev &A, float p, float &m, float &v, float g) {
+  m = fmaf(A.b1, m, (1.f - A.b1) * g);
+  v = fmaf(A.b2, v, (1.f - A.b2) * g * g);
+  return p - A.lr * (m / A.bc1) / (sqrtf(v / A.bc2) + A.eps);
+}
+
+// Place of parameter k (mean, log-scale, quaternion, amplitude) of Gaussian n.
+__device__ __forceinline__ int64_t param_at(int k, int64_t n, int64_t N) {
+  return k < 3 ? 3 * n + k : k < 6 ? 3 * N + 3 * n + k - 3 : k < 10 ? 6 * N + 4 * n + k - 6 : 10 * N + n;
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -460,6 +459,22 @@ k_chain(const float4 *gc, const float *log_scales, const float *quats, const flo
     g0 = gc[3 * n];
     g1 = gc[3 * n + 1];
     g2 = gc[3 * n + 2];
+  }
+  // what the first wave needs at the end, requested now
+  float raw[8] = {0, 0, 0, 0, 0, 0, 0, 0}, am[11], av[11];
+  if (wv == 0 && live) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) raw[k] = log_scales[3 * n + k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) raw[3 + k] = quats[4 * n + k];
+    raw[7] = amps[n];
+    if (A.p) {
+#pragma unroll
+      for (int k = 0; k < 11; ++k) {
+        am[k] = A.m[param_at(k, n, G.N)];
+        av[k] = A.v[param_at(k, n, G.N)];
+      }
+    }
   }
   float dmu[3] = {0, 0, 0};
   float dS[6] = {0, 0, 0, 0, 0, 0};  // xx xy xz yy yz zz
@@ -513,7 +528,7 @@ k_chain(const float4 *gc, const float *log_scales, const float *quats, const flo
   float s[3], dsdl[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const float l = log_scales[3 * n + k];
+    const float l = raw[k];
     if (G.scale_act) {
       s[k] = softplusf(l);
       dsdl[k] = sigmoidf_(l);
@@ -522,7 +537,7 @@ k_chain(const float4 *gc, const float *log_scales, const float *quats, const flo
       dsdl[k] = s[k];
     }
   }
-  float qw = quats[4 * n + 0], qx = quats[4 * n + 1], qy = quats[4 * n + 2], qz = quats[4 * n + 3];
+  float qw = raw[3], qx = raw[4], qy = raw[5], qz = raw[6];
   const float qn = fmaxf(sqrtf(qw * qw + qx * qx + qy * qy + qz * qz), 1e-12f);
   const float iq = 1.f / qn;
   qw *= iq; qx *= iq; qy *= iq; qz *= iq;
@@ -556,20 +571,21 @@ k_chain(const float4 *gc, const float *log_scales, const float *quats, const flo
   const float dqz = 2.f * (-2.f * qz * dR[0][0] - qw * dR[0][1] + qx * dR[0][2] + qw * dR[1][0] -
                            2.f * qz * dR[1][1] + qy * dR[1][2] + qx * dR[2][0] + qy * dR[2][1]);
   const float dot = qw * dqw + qx * dqx + qy * dqy + qz * dqz;
-  const float ga = dw_sum * (G.amp_act ? sigmoidf_(amps[n]) : 1.f);
+  const float ga = dw_sum * (G.amp_act ? sigmoidf_(raw[7]) : 1.f);
   const float gq[4] = {(dqw - qw * dot) * iq, (dqx - qx * dot) * iq, (dqy - qy * dot) * iq, (dqz - qz * dot) * iq};
   if (A.p) {
     // the optimiser's step on this Gaussian's 11 parameters in place of its
     // gradient (batch-1 training: one launch and a round trip fewer)
-    const int64_t N = G.N, at = n;
+    const float pv[11] = {g0.x, g0.y, g0.z, raw[0], raw[1], raw[2], raw[3], raw[4], raw[5], raw[6], raw[7]};
+    const float pg[11] = {dmu[0], dmu[1], dmu[2], ds[0] * dsdl[0], ds[1] * dsdl[1], ds[2] * dsdl[2],
+                          gq[0], gq[1], gq[2], gq[3], ga};
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      adam_update(A, 3 * at + k, dmu[k]);
-      adam_update(A, 3 * N + 3 * at + k, ds[k] * dsdl[k]);
+    for (int k = 0; k < 11; ++k) {
+      const int64_t at = param_at(k, n, G.N);
+      A.p[at] = adam_step(A, pv[k], am[k], av[k], pg[k]);
+      A.m[at] = am[k];
+      A.v[at] = av[k];
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) adam_update(A, 6 * N + 4 * at + k, gq[k]);
-    adam_update(A, 10 * N + at, ga);
     return;
   }
   if (g_means) {
@@ -772,7 +788,11 @@ k_pair_count(const float4 *gc, const float *rot, const float *shift, Geom G,
 // Adam (Alg. 1 "Adam(grad L)") over a flat array.
 __global__ void __launch_bounds__(kBlock) k_adam(AdamDev A, const float *g, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) adam_update(A, i, g[i]);
+  if (i >= n) return;
+  float m = A.m[i], v = A.v[i];
+  A.p[i] = adam_step(A, A.p[i], m, v, g[i]);
+  A.m[i] = m;
+  A.v[i] = v;
 }
 
 __global__ void __launch_bounds__(kBlock) k_fill(float *p, int64_t n, float value) {

@@ -50,11 +50,28 @@ __device__ __forceinline__ int row_of(int x, float inv_n) {
   return (int)(((float)x + 0.5f) * inv_n);
 }
 
-__device__ __forceinline__ int next_item(int *queue, int *slot) {
-  if (threadIdx.x == 0) *slot = atomicAdd(queue, 1);
-  __syncthreads();
-  return *slot;
-}
+// Work items in turn: the first problem's first gridDim.x items go to the blocks
+// by their index, the rest through the counter.  A block of a small call takes
+// its one item without a round trip to the counter, which every block of the
+// launch would queue up for twice.
+struct ItemQueue {
+  int *counter, *slot;
+  int nitems, first, base;
+  __device__ ItemQueue(int *counter, int *slot, int nitems, int p)
+      : counter(counter), slot(slot), nitems(nitems), first(p == 0 ? (int)blockIdx.x : -1),
+        base(p == 0 ? (int)gridDim.x : 0) {}
+  __device__ int next() {  // nitems or more: none left
+    if (first >= 0) {
+      const int it = first;
+      first = -1;
+      return it;
+    }
+    if (base >= nitems) return nitems;
+    if (threadIdx.x == 0) *slot = base + atomicAdd(counter, 1);
+    __syncthreads();
+    return *slot;
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Dealing records to lanes.  Every lane walks its own Gaussian, so at a step
@@ -235,10 +252,34 @@ __device__ __forceinline__ const unsigned short *order_records(const float4 *lis
   return nullptr;
 }
 
+// A thread's first record in list order, requested with the work item where
+// several lanes share one (small calls, whose items are one pass of the block):
+// its round trip runs beside the item's other loads.
+template <int RS>
+struct FirstRecord {
+  size_t rec;
+  float4 r0, r1;
+  __device__ FirstRecord(const float4 *list, const int4 &itm) {
+    if (RS == 1) return;
+    rec = 2 * ((size_t)itm.z + min((int)threadIdx.x / RS, itm.w - 1));
+    r0 = list[rec];
+    r1 = list[rec + 1];
+  }
+  __device__ void get(const float4 *list, size_t at, float4 &a, float4 &b) {
+    if (RS > 1 && at == rec) {
+      a = r0;
+      b = r1;
+    } else {
+      a = list[at];
+      b = list[at + 1];
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Forward: partial canvas of one work item.  RS adjacent lanes share a record,
 // taking every RS-th of its rows: 1 where there are records enough to fill the
-// chip, 4 for small calls, whose time is one wave's walk over its tallest
+// chip, 4 for smaller calls, whose time is one wave's walk over its tallest
 // footprint (one image of 1000 Gaussians: 24 -> 9.5 us with tiles of 32 beside;
 // eight lanes gave no more).  The sums are integers, so the lanes' order is free.
 // ---------------------------------------------------------------------------
@@ -255,15 +296,16 @@ __global__ void __launch_bounds__(kBlock) k_splat_fwd_rs(MultiProb MP) {
   const float4 *list = MP.p[p].list;
   const int4 *items = MP.p[p].items;
   float *partials = MP.p[p].partials;
-  int *queue = MP.p[p].queue;
   const int nitems = *MP.p[p].n_items;
+  ItemQueue queue(MP.p[p].queue, &slot, nitems, p);
   const int CS = G.C * G.S;
   for (;;) {
-    const int it = next_item(queue, &slot);
+    const int it = queue.next();
     if (it >= nitems) break;
     for (int i = threadIdx.x; i < CS / 4; i += kBlock) smem4[i] = make_int4(0, 0, 0, 0);
     for (int i = (CS & ~3) + threadIdx.x; i < CS; i += kBlock) icanvas[i] = 0;
     const int4 itm = items[it];
+    FirstRecord<RS> fr(list, itm);
     // fixed-point scale: 2^e with 2^e * sum|w| <= 2^30 (the item's |w| are
     // contiguous beside the list, summed in a fixed order)
     const float *wa = MP.p[p].wabs + itm.z;
@@ -301,7 +343,8 @@ __global__ void __launch_bounds__(kBlock) k_splat_fwd_rs(MultiProb MP) {
         order_records(list, (size_t)itm.z + c0, nc, G, R0, C0, rlo, rhi, ol);
     for (int s = threadIdx.x / RS; s < nc; s += kBlock / RS) {
       const size_t rec = 2 * ((size_t)itm.z + c0 + (perm ? perm[s] : s));
-      const float4 r0 = list[rec], r1 = list[rec + 1];
+      float4 r0, r1;
+      fr.get(list, rec, r0, r1);
       const float u = r0.x, v = r0.y, al = r0.z, be = r0.w, ga = r1.x, w = r1.y * scale;
       const int rows = __float_as_int(r1.w);
       const int i0 = max(rows & 0xffff, rlo) + (int)threadIdx.x % RS, i1 = min(rows >> 16, rhi);
@@ -617,12 +660,13 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd_rs(MultiProb MP) {
   const int4 *items = MP.p[p].items;
   const float *GQ = MP.p[p].GQ;
   float *mom = MP.p[p].mom;
-  int *queue = MP.p[p].queue + 1;
   const int nitems = *MP.p[p].n_items;
+  ItemQueue queue(MP.p[p].queue + 1, &slot, nitems, p);
   for (;;) {
-    const int it = next_item(queue, &slot);
+    const int it = queue.next();
     if (it >= nitems) break;
     const int4 itm = items[it];
+    FirstRecord<RS> fr(list, itm);
     const int b = itm.x;
     const int ty = itm.y / G.ntx, tx = itm.y % G.ntx;
     const int R0 = ty * G.T - G.halo, C0 = tx * G.T - G.halo;
@@ -659,7 +703,8 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd_rs(MultiProb MP) {
         order_records(list, (size_t)itm.z + c0, nc, G, R0, C0, rlo, rhi, ol);
     for (int s = threadIdx.x / RS; s < nc; s += kBlock / RS) {
       const size_t rec = 2 * ((size_t)itm.z + c0 + (perm ? perm[s] : s));
-      const float4 r0 = list[rec], r1 = list[rec + 1];
+      float4 r0, r1;
+      fr.get(list, rec, r0, r1);
       const float u = r0.x, v = r0.y, al = r0.z, be = r0.w, ga = r1.x;
       const int n = __float_as_int(r1.z);
       const int rows = __float_as_int(r1.w);

@@ -1,6 +1,6 @@
 """Calls of few Gaussian-image pairs: smaller tiles and work items, and four
 lanes to a record in both splat kernels.  Sizes on both sides of each line (32768
-pairs, 256 default tiles, a halo above the default), ragged images, records
+and 524288 pairs, 256 default tiles, a halo above the default), ragged images, records
 wider than the halo, and options given one by one, against the FP64 oracle.
 
 Images within 1e-4 normwise, gradients within 1e-3, the renderer's bars: the
@@ -35,6 +35,8 @@ Q_MATCHED = 2.0 * np.log(1e6)
     (20, 65, 128, 1.5, {}),                 # 260
     (4096, 8, 32, 0.7, {}),                 # 32768 pairs
     (4097, 8, 32, 0.7, {}),
+    (4096, 128, 24, 0.7, {}),               # 524288 pairs: four lanes
+    (4097, 128, 24, 0.7, {}),               # more: one
 ])
 def test_small_calls_match_the_oracle(gpu_lib, n, b, D, sd, opt):
     rng = np.random.default_rng(n + b + D)
@@ -78,8 +80,8 @@ def test_limited_workspace_falls_back_to_the_default_tile(monkeypatch):
     (1000, 16, 128),   # 272 bins of 4 blocks: a thread
     (4500, 7, 216),    # 350 bins of 18 blocks: a kernel of its own
     (17000, 1, 64),    # 67 blocks: a wave in two steps
-    (2048, 128, 24),   # 262144 pairs: Gaussians built while counting
-    (2049, 128, 24),   # more: beforehand
+    (4096, 128, 24),   # 524288 pairs: Gaussians built while counting
+    (4097, 128, 24),   # more: beforehand
     (50, 32, 36),      # 32 images: losses in one launch
     (50, 33, 36),      # 33: in two
 ])
