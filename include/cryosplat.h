@@ -142,7 +142,8 @@ typedef struct {
                      graph and replay it; the first call with a signature
                      must not itself be inside a caller's stream capture */
   int32_t lane_order; /* 0 = each work item's Gaussians go to lanes in list
-                         order; 1 = dealt so that the lanes of a wave start on
+                         order, or, without a tile either, as 2 in calls
+                         large enough to profit; 1 = dealt so that the lanes of a wave start on
                          distinct LDS banks (pays for wide footprints);
                          2 = sorted by footprint shape (row count, then
                          widest span) so that the lanes of a wave walk

@@ -100,3 +100,20 @@ def test_binning_and_loss_lines_match_the_oracle(gpu_lib, n, b, D):
     per, _ = o_obj.loss_from_images(ref, Y, "sum")
     np.testing.assert_allclose(host(loss)[:-1], per, rtol=1e-4)
     np.testing.assert_allclose(host(loss)[-1], per.sum(), rtol=1e-4)
+
+
+@pytest.mark.parametrize("n,b,D", [(4096, 128, 24), (4097, 128, 24), (70001, 8, 64)])
+def test_automatic_lane_order_keeps_the_bits(gpu_lib, n, b, D):
+    """Untuned calls above 524288 pairs sort their records; with a tile given the
+    order is the caller's (here the list's).  Both sum the same terms."""
+    rng = np.random.default_rng(n)
+    g = inputs.mixture_anisotropic(rng, n, 0.4 * D, scale_mu=np.log(0.8), scale_sd=0.5)
+    v = inputs.views(rng, b, D, 1.0)
+    Y = dev(rng.standard_normal((b, D, D)).astype(np.float32))
+    announce(f"automatic lane order N={n} B={b} D={D}")
+    kw = dict(**mixture_args(g), **view_args(v), observed=Y, want_images=True)
+    auto = gpu_lib.loss_and_grad(**kw)
+    listed = gpu_lib.loss_and_grad(**kw, options=binding.Options(tile=64))
+    assert np.array_equal(host(auto[2]), host(listed[2]))
+    for k in auto[1]:
+        assert np.array_equal(host(auto[1][k]), host(listed[1][k])), k
