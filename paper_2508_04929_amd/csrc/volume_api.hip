@@ -32,13 +32,17 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
   HIPCHK(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   const int N = (int)g->n, nb = D / 8, nbr = nb * nb * nb;
-  VoxGeom V{N, D, D / 2, nb, pixel, q_cut > 0.f ? q_cut : kDefaultQCutVol};
+  const int csh = nb <= 32 ? 1 : 2, nc = (nb + (1 << csh) - 1) >> csh, ncell = nc * nc * nc;
+  // blocks of the counting kernels: at most one per CU, as each adds every cell it met
+  const int per = (int)std::max<int64_t>(128, cdivv(N, 256));
+  const VoxGeom V{N, D, D / 2, nb, csh, nc, per, pixel, q_cut > 0.f ? q_cut : kDefaultQCutVol};
   const size_t o_gc = 0, o_rec = o_gc + al256v((size_t)N * 48 + 16);
   const size_t o_box = o_rec + al256v((size_t)N * 48 + 16);
   const size_t o_cnt = o_box + al256v((size_t)N * 16 + 16);
-  const size_t o_off = o_cnt + al256v((size_t)nbr * 4);
-  const size_t o_cur = o_off + al256v((size_t)(nbr + 1) * 4);
-  const size_t o_scale = o_cur + al256v((size_t)nbr * 4);
+  const size_t o_cur = o_cnt + (size_t)ncell * 8;  // cleared with the counts
+  const size_t o_off = al256v(o_cur + (size_t)ncell * 4);
+  const size_t o_rng = o_off + al256v((size_t)(ncell + 1) * 8);
+  const size_t o_scale = o_rng + al256v((size_t)nbr * 8);
   const int nwp = (int)cdivv(N, 256);  // blocks of k_vox_prep: partial sums of |w|
   const size_t o_wp = o_scale + 256;
   const size_t o_list = o_wp + al256v((size_t)nwp * 8 + 8);
@@ -48,9 +52,7 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
   auto prepare = [&]() -> int {
     char *w = (char *)ctx->vol;
     float4 *gc = (float4 *)(w + o_gc), *rec = (float4 *)(w + o_rec);
-    int *cnt = (int *)(w + o_cnt), *cur = (int *)(w + o_cur);
-    TLAUNCH(k_fill_i32z, dim3(cdivv(nbr, 256)), dim3(256), 0, st, cnt, nbr);
-    TLAUNCH(k_fill_i32z, dim3(cdivv(nbr, 256)), dim3(256), 0, st, cur, nbr);
+    TLAUNCH(k_fill_i32z, dim3(cdivv(3 * ncell, 256)), dim3(256), 0, st, (int *)(w + o_cnt), 3 * ncell);
     if (N > 0) {
       Geom G{};
       G.N = N;
@@ -59,22 +61,23 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
       TLAUNCH(k_build, dim3(cdivv(N, kBlock)), dim3(kBlock), 0, st, gauss_dev(*g), G, gc);
       TLAUNCH(k_vox_prep, dim3(nwp), dim3(256), 0, st, (const float4 *)gc, V, rec,
               (int4 *)(w + o_box), (double *)(w + o_wp));
-      TLAUNCH(k_vox_count, dim3(cdivv(N, 4)), dim3(256), 0, st, (const int4 *)(w + o_box), V, cnt);
+      TLAUNCH(k_vox_count, dim3(cdivv(N, per)), dim3(1024), (size_t)ncell * 8, st,
+              (const int4 *)(w + o_box), V, (int2 *)(w + o_cnt));
     }
-    TLAUNCH(k_vox_scan, dim3(1), dim3(1024), 0, st, (const int *)cnt, nbr,
-            (const double *)(w + o_wp), N > 0 ? nwp : 0, (int *)(w + o_off),
-            (double *)(w + o_scale));
+    TLAUNCH(k_vox_scan, dim3(1), dim3(1024), 0, st, (const int2 *)(w + o_cnt), ncell,
+            (const double *)(w + o_wp), N > 0 ? nwp : 0, (int2 *)(w + o_off), (double *)(w + o_scale));
     return CS_OK;
   };
   rc = prepare();
   if (rc) return rc;
-  // the list length is known only now: read it back (this call synchronises)
-  int total = 0;
-  HIPCHK(hipMemcpyAsync(&total, (char *)ctx->vol + o_off + (size_t)nbr * 4, sizeof(int),
+  // the list lengths are known only now: read them back (this call synchronises)
+  int2 total{0, 0};
+  HIPCHK(hipMemcpyAsync(&total, (char *)ctx->vol + o_off + (size_t)ncell * 8, sizeof(total),
                         hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
-  if (total < 0) return fail(ctx, CS_ERR_UNSUPPORTED, "too many (brick, Gaussian) pairs");
-  const size_t need = o_list + al256v((size_t)total * 4 + 4);
+  if (total.x < 0 || total.y < 0) return fail(ctx, CS_ERR_UNSUPPORTED, "too many (brick, Gaussian) pairs");
+  const size_t o_cells = o_list + al256v((size_t)total.y * 4 + 4);
+  const size_t need = o_cells + al256v((size_t)total.x * 4 + 4);
   if (need > ctx->vol_bytes) {
     // a larger scratch does not keep its contents: prepare again (same values)
     rc = grow(ctx, &ctx->vol, &ctx->vol_bytes, need);
@@ -84,14 +87,19 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
   }
   char *w = (char *)ctx->vol;
   const float4 *rec = (const float4 *)(w + o_rec);
-  const int *off = (const int *)(w + o_off);
+  const int2 *off = (const int2 *)(w + o_off);
   const double *scale = (const double *)(w + o_scale);
-  int *list = (int *)(w + o_list);
-  if (N > 0 && total > 0)
-    TLAUNCH(k_vox_fill, dim3(cdivv(N, 4)), dim3(256), 0, st, (const int4 *)(w + o_box), V, off,
-            (int *)(w + o_cur), list);
+  int *list = (int *)(w + o_list), *cells = (int *)(w + o_cells);
+  int2 *range = (int2 *)(w + o_rng);
+  if (N > 0 && total.x > 0)
+    TLAUNCH(k_vox_fill, dim3(cdivv(N, per)), dim3(1024), (size_t)ncell * 4, st, (const int4 *)(w + o_box), V,
+            off, (int *)(w + o_cur), cells);
+  typedef void (*CellFn)(const int4 *, VoxGeom, const int2 *, const int *, int2 *, int *);
+  const CellFn k_vox_cell = csh == 1 ? &cs::k_vox_cell<1> : &cs::k_vox_cell<2>;
+  TLAUNCH(k_vox_cell, dim3(ncell), dim3(512), 0, st, (const int4 *)(w + o_box), V, off, (const int *)cells,
+          range, list);
   // one 64-lane workgroup per 4^3 sub-cube, eight per brick (XCD-aware order)
-  TLAUNCH(k_vox_eval, dim3(cdivv(nbr, 8) * 64), dim3(64), 0, st, rec, (const int *)list, off, V,
+  TLAUNCH(k_vox_eval, dim3(cdivv(nbr, 8) * 64), dim3(64), 0, st, rec, (const int *)list, (const int2 *)range, V,
           scale, vol);
   return CS_OK;
 }
@@ -133,8 +141,8 @@ int cs_fsc(cs_ctx *ctx, const float *vol_a, const float *vol_b, int32_t D, float
     TLAUNCH(k_fft_axis, rz.grid, rz.block, rz.lds, st, F, tw, D * Dh);        // z
   }
   TLAUNCH(k_fill_u64z, dim3(cdivv(3 * ns, 256)), dim3(256), 0, st, sums, 3 * ns);
-  const unsigned blocks = std::min<unsigned>(2048, cdivv((int64_t)D * D * Dh, 256));
-  TLAUNCH(k_fsc_shells, dim3(blocks), dim3(256), (size_t)3 * ns * 8, st, (const float2 *)fa,
+  const unsigned blocks = std::min<unsigned>(256, cdivv((int64_t)Dh * Dh * Dh, 1024));
+  TLAUNCH(k_fsc_shells, dim3(blocks), dim3(1024), (size_t)3 * ns * 8 * kShellCopies, st, (const float2 *)fa,
           (const float2 *)fb, D, (const double *)scale, sums);
   TLAUNCH(k_fsc_final, dim3(cdivv(ns, 256)), dim3(256), 0, st, (const unsigned long long *)sums, ns,
           (const double *)scale, fsc);
