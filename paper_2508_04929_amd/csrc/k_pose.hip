@@ -247,8 +247,12 @@ __device__ __forceinline__ void row_minimum(unsigned long long key, int lane,
   if ((lane & 15) == 0 && key != ~0ull) atomicMin(best, key);
 }
 
-template <int NWM, int NWN, int TI, int TJ, int MODE>
-__global__ void __launch_bounds__(64 * NWM * NWN, 2) k_pose_mma(PoseGemmArgs a) {
+// S = 2: the loads of the step after the next run while a step's MFMAs do, enough
+// where the blocks of the launch fill the chip.  S > 2: a ring of S steps for the
+// launches that do not, whose time is one block's K steps, each as long as a load
+// takes (0.78 us a step of 128 x 128 parts, 0.4 us of 64 x 64 on a ring of six).
+template <int NWM, int NWN, int TI, int TJ, int S, int MODE>
+__global__ void __launch_bounds__(64 * NWM * NWN, S > 2 ? 1 : 2) k_pose_mma(PoseGemmArgs a) {
   constexpr int kT = 64 * NWM * NWN, BM = NWM * TI * 16, BN = NWN * TJ * 16;
   constexpr int NA = BM * 8 / kT, NB = BN * 8 / kT;  // 16-byte loads per thread and step
   static_assert(NA * kT == BM * 8 && NB * kT == BN * 8, "tile shape");
@@ -256,6 +260,11 @@ __global__ void __launch_bounds__(64 * NWM * NWN, 2) k_pose_mma(PoseGemmArgs a) 
   // buffer need not wait for the loads that fill the other)
   __shared__ __attribute__((aligned(1024))) unsigned short sA0[BM * kMmaK], sA1[BM * kMmaK];
   __shared__ __attribute__((aligned(1024))) unsigned short sB0[BN * kMmaK], sB1[BN * kMmaK];
+  constexpr int kA2 = S > 2 ? BM * kMmaK : 8, kB2 = S > 2 ? BN * kMmaK : 8;
+  constexpr int kA4 = S > 4 ? BM * kMmaK : 8, kB4 = S > 4 ? BN * kMmaK : 8;
+  static_assert(S == 2 || S == 4 || S == 6, "ring arrays");
+  __shared__ __attribute__((aligned(1024))) unsigned short sA2[kA2], sA3[kA2], sA4[kA4], sA5[kA4];
+  __shared__ __attribute__((aligned(1024))) unsigned short sB2[kB2], sB3[kB2], sB4[kB4], sB5[kB4];
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wv / NWN) * TI * 16, wn = (wv % NWN) * TJ * 16;
   // blocks are the BM x BN parts of 256 x 256 tiles a.t0 ...; every XCD runs
@@ -352,15 +361,64 @@ __global__ void __launch_bounds__(64 * NWM * NWN, 2) k_pose_mma(PoseGemmArgs a) 
     mma(1, 1, 1, HI);
     mma_order();
   };
-  stage(0, sA0, sB0);
-  dma_wait();
-  __syncthreads();
-  stage(1, sA1, sB1);
-  frag_a(sA0, 0, 0);
-  frag_b(sB0, 0);
-  for (int kt = 0; kt < nk; kt += 2) {
-    step(kt, sA0, sB0, sA1, sB1);
-    step(kt + 1, sA1, sB1, sA0, sB0);
+  if constexpr (S == 2) {
+    stage(0, sA0, sB0);
+    dma_wait();
+    __syncthreads();
+    stage(1, sA1, sB1);
+    frag_a(sA0, 0, 0);
+    frag_b(sB0, 0);
+    for (int kt = 0; kt < nk; kt += 2) {
+      step(kt, sA0, sB0, sA1, sB1);
+      step(kt + 1, sA1, sB1, sA0, sB0);
+    }
+  } else {
+    unsigned short *const rA[6] = {sA0, sA1, sA2, sA3, sA4, sA5}, *const rB[6] = {sB0, sB1, sB2, sB3, sB4, sB5};
+    constexpr int kLoads = NA + NB;
+    mma_bf16x8 fa[2][2][TI], fb[2][2][TJ];  // [set][k-slice]
+    auto frags = [&](const unsigned short *tA, const unsigned short *tB, int h) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i) fa[h][ks][i] = mma_frag(tA, wm + i * 16 + (lane & 15), ks, lane);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) fb[h][ks][j] = mma_frag(tB, wn + j * 16 + (lane & 15), ks, lane);
+      }
+    };
+    auto slice = [&](int h, int ks) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][ks][i], fb[h][ks][j], acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int u = 0; u < S; ++u) stage(min(u, nk - 1), rA[u], rB[u]);
+    dma_wait_but<(S - 1) * kLoads>();
+    frags(sA0, sB0, 0);
+    constexpr int kUnroll = 3 * S;
+    for (int kt = 0;; kt += kUnroll) {
+      bool more = true;
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        // this step's fragments are in registers, the next step's tile has arrived
+        dma_wait_but<(S - 2) * kLoads>();
+        slice(u & 1, 0);
+        mma_order();
+        stage(min(kt + u + S, nk - 1), rA[u % S], rB[u % S]);  // past the end: the last step again, not read
+        frags(rA[(u + 1) % S], rB[(u + 1) % S], (u & 1) ^ 1);
+        mma_order();
+        slice(u & 1, 1);
+        mma_order();
+        // (a mark of its own per step, so that equal steps are not merged)
+        asm volatile("; step %0" ::"n"(u));
+        if (kt + u + 1 >= nk) {
+          more = false;
+          break;
+        }
+      }
+      if (!more) break;
+    }
   }
   dma_wait();  // no load may land after the block has given its LDS back
   // acc[i][j][r] is C[m0 + wm + 16 i + 4 (lane / 16) + r][n0 + wn + 16 j + lane % 16]
@@ -810,29 +868,46 @@ hipError_t pose_confidence(const unsigned short *bank, int64_t ldb, int64_t boff
 }
 
 // The 256 x 256 tiles t0 .. t1 - 1, in parts of NWM TI 16 x NWN TJ 16.
-template <int NWM, int NWN, int TI, int TJ, int MODE>
+template <int NWM, int NWN, int TI, int TJ, int S, int MODE>
 static void launch_mma(PoseGemmArgs a, int64_t t0, int64_t t1, hipStream_t st) {
   if (t0 == t1) return;
   a.t0 = (int)t0;
   const int64_t parts = (t1 - t0) * (256 / (NWM * TI * 16)) * (256 / (NWN * TJ * 16));
-  hipLaunchKernelGGL((k_pose_mma<NWM, NWN, TI, TJ, MODE>), dim3((unsigned)parts), dim3(64 * NWM * NWN),
+  hipLaunchKernelGGL((k_pose_mma<NWM, NWN, TI, TJ, S, MODE>), dim3((unsigned)parts), dim3(64 * NWM * NWN),
                      0, st, a);
 }
 
+// The tiles in parts of 128 x 128 where these give every CU a block, in smaller
+// ones on a deeper ring otherwise.  Grid searches at K = 16,384, us, 128 x 128 and
+// these: 64 particles x 4,608 rotations 619 and 548, 128 particles 768 and 696, the
+// last 8 tiles of 1,024 particles 199 and 106; at K = 9,216 (energies 4,704) and 300
+// particles 757 and 711.  Few K steps are over before the ring pays (K = 4,096 and
+// 2,112, 16 particles: 144 and 145).
+template <int MODE>
+static void launch_parts(const PoseGemmArgs &a, int64_t t0, int64_t t1, hipStream_t st) {
+  if ((t1 - t0) * 4 >= 256 || a.K < 4608) {
+    launch_mma<2, 2, 4, 4, 2, MODE>(a, t0, t1, st);
+  } else if ((t1 - t0) * 16 > 512) {
+    launch_mma<2, 2, 2, 4, 4, MODE>(a, t0, t1, st);
+  } else {
+    launch_mma<2, 2, 2, 2, 6, MODE>(a, t0, t1, st);
+  }
+}
+
 hipError_t pose_gemm_store(const PoseGemmArgs &a, hipStream_t st) {
-  launch_mma<2, 2, 4, 4, kPoseStore>(a, 0, (int64_t)pcdiv(a.M, 256) * pcdiv(a.N, 256), st);
+  launch_parts<kPoseStore>(a, 0, (int64_t)pcdiv(a.M, 256) * pcdiv(a.N, 256), st);
   return hipGetLastError();
 }
 
 // One 256 x 256 tile occupies a CU: whole rounds of 256 of them (3.0 ms for
 // 25,600 x 4,608 x 16,384 against 3.4 ms as 128 x 128 tiles, whose operands
-// pass through LDS twice as often), what is left as 128 x 128 parts, which
+// pass through LDS twice as often), what is left as smaller parts, which
 // fill the chip with a quarter of the tiles.
 hipError_t pose_gemm_score(const PoseGemmArgs &a, hipStream_t st) {
   const int64_t tiles = (int64_t)pcdiv(a.M, 256) * pcdiv(a.N, 256), rest = tiles % 256;
   const int64_t whole = rest > 128 ? tiles : tiles - rest;
-  launch_mma<2, 4, 8, 4, kPoseScore>(a, 0, whole, st);
-  launch_mma<2, 2, 4, 4, kPoseScore>(a, whole, tiles, st);
+  launch_mma<2, 4, 8, 4, 2, kPoseScore>(a, 0, whole, st);
+  launch_parts<kPoseScore>(a, whole, tiles, st);
   return hipGetLastError();
 }
 
