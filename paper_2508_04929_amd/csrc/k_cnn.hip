@@ -1685,19 +1685,24 @@ hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st) {
 
 // Splits of a weight gradient's pixels: about one block of 128 x 128 outputs
 // per CU (two of 64 x 128), each at least 16 steps of 32 pixels long so that
-// the partials stay a small part of the traffic.
+// the partials stay a small part of the traffic.  wgrad_most is what the rule
+// asks for and never falls as the pixels grow; whole steps per split can leave
+// one of them over, so the plan may take fewer (and, at some sizes, more than it
+// takes for a few more pixels).
 constexpr int kConv1Blocks = 512;  // two per CU
-static int wgrad_plan(int Cin, int Cout, int64_t K, int *kchunk) {
+static int wgrad_most(int Cin, int Cout, int64_t K) {
   const int tiles = (int)(cdiv_(Cout, Cout > 64 ? 128 : 64) * cdiv_(9 * Cin, 128));
   const int want = (Cout > 64 ? 256 : 512) / tiles;
-  int64_t s = std::max<int64_t>(1, std::min<int64_t>(want, K / 512));
-  const int64_t c = (cdiv_(K, s) + 31) / 32 * 32;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(want, K / 512));
+}
+static int wgrad_plan(int Cin, int Cout, int64_t K, int *kchunk) {
+  const int64_t c = (cdiv_(K, wgrad_most(Cin, Cout, K)) + 31) / 32 * 32;
   *kchunk = (int)c;
   return (int)((K + c - 1) / c);
 }
 
-// Values of a partial array: 2^23 at most for one split, or for the first
-// layer's chunks of 256 pixels.
+// Largest weight gradient that is taken, and largest set of 256-pixel chunks of
+// a first layer's: 2^23 values.
 constexpr int64_t kPartMax = (int64_t)1 << 23;
 
 static bool conv1_wgrad_rows(int Wi, int Cout) { return Cout == 32 && Wi % 64 == 0; }
@@ -1706,9 +1711,8 @@ size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool aligned) {
   const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
   if (Cin == 1)
     return (size_t)(aligned && conv1_wgrad_rows(Wi, Cout) ? kConv1Blocks : cdiv_(npix, 256)) * Cout * 10;
-  int kc;
-  // (fewer images never take more splits)
-  return (size_t)wgrad_plan(Cin, Cout, npix, &kc) * Cout * (9 * Cin + 1);
+  // (room for every smaller batch too: a network allocates for its capacity)
+  return (size_t)wgrad_most(Cin, Cout, npix) * Cout * (9 * Cin + 1);
 }
 
 hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout,
