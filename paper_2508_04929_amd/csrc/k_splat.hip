@@ -53,7 +53,9 @@ __device__ __forceinline__ int row_of(int x, float inv_n) {
 // Work items in turn: the first problem's first gridDim.x items go to the blocks
 // by their index, the rest through the counter.  A block of a small call takes
 // its one item without a round trip to the counter, which every block of the
-// launch would queue up for twice.
+// launch would queue up for twice.  A block barrier lies between the last next()
+// of one problem and the first of the next one: only then has every wave read the
+// slot that the first thread is about to overwrite.
 struct ItemQueue {
   int *counter, *slot;
   int nitems, first, base;
@@ -315,6 +317,7 @@ __global__ void __launch_bounds__(kBlock) k_splat_fwd_rs(MultiProb MP) {
   __shared__ OrderLds ol;
   // drain the problems' queues in order: blocks that find one exhausted move on
   for (int p = 0; p < MP.count; ++p) {
+  if (p > 0) __syncthreads();  // the slot has been read
   const Geom G = MP.p[p].G;
   const float4 *list = MP.p[p].list;
   const int4 *items = MP.p[p].items;
@@ -680,6 +683,7 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd_rs(MultiProb MP) {
   __shared__ int slot;
   __shared__ OrderLds ol;
   for (int p = 0; p < MP.count; ++p) {
+  if (p > 0) __syncthreads();  // the slot has been read
   const Geom G = MP.p[p].G;
   const float4 *list = MP.p[p].list;
   const int4 *items = MP.p[p].items;
