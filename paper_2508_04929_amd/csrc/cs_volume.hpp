@@ -18,7 +18,7 @@ struct VoxGeom {
 };
 
 __global__ void k_vox_prep(const float4 *gc, VoxGeom V, float4 *rec, int4 *box, double *wpart);
-__global__ void k_vox_count(const int4 *box, VoxGeom V, int2 *count);
+__global__ void k_vox_count(const int4 *box, VoxGeom V, int2 *count, unsigned long long *total);
 __global__ void k_vox_scan(const int2 *count, int ncell, const double *wpart, int nwp, int2 *off,
                            double *scale);
 __global__ void k_vox_fill(const int4 *box, VoxGeom V, const int2 *off, int *cursor, int *cell_list);

@@ -108,10 +108,14 @@ struct Box {
 // + 21 + 27 us.
 
 // Gaussians and (brick, Gaussian) pairs of every cell; 8 lanes to a Gaussian.
+// The lists are indexed with 32 bits, so the totals are kept in 64: where they do
+// not fit, the counts may have wrapped and nothing may be listed.
 __global__ void __launch_bounds__(1024)
-k_vox_count(const int4 *box, VoxGeom V, int2 *count) {
+k_vox_count(const int4 *box, VoxGeom V, int2 *count, unsigned long long *total) {
   extern __shared__ int2 hist[];  // [nc^3]
+  __shared__ unsigned long long sum[2];
   const int ncell = V.nc * V.nc * V.nc;
+  if (threadIdx.x < 2) sum[threadIdx.x] = 0ull;
   for (int i = threadIdx.x; i < ncell; i += 1024) hist[i] = make_int2(0, 0);
   __syncthreads();
   const int n1 = min(V.N, (int)(blockIdx.x + 1) * V.per);
@@ -126,11 +130,25 @@ k_vox_count(const int4 *box, VoxGeom V, int2 *count) {
     }
   }
   __syncthreads();
+  unsigned long long cells = 0ull, pairs = 0ull;
   for (int i = threadIdx.x; i < ncell; i += 1024)
     if (hist[i].x) {
       atomicAdd(&count[i].x, hist[i].x);
       atomicAdd(&count[i].y, hist[i].y);
+      cells += hist[i].x;
+      pairs += hist[i].y;
     }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    cells += __shfl_xor(cells, o, 64);
+    pairs += __shfl_xor(pairs, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    atomicAdd(&sum[0], cells);
+    atomicAdd(&sum[1], pairs);
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) atomicAdd(&total[threadIdx.x], sum[threadIdx.x]);
 }
 
 // Exclusive scans of the cell counts (one block) and the fixed-point scale of

@@ -38,7 +38,8 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
   const VoxGeom V{N, D, D / 2, nb, csh, nc, per, pixel, q_cut > 0.f ? q_cut : kDefaultQCutVol};
   const size_t o_gc = 0, o_rec = o_gc + al256v((size_t)N * 48 + 16);
   const size_t o_box = o_rec + al256v((size_t)N * 48 + 16);
-  const size_t o_cnt = o_box + al256v((size_t)N * 16 + 16);
+  const size_t o_tot = o_box + al256v((size_t)N * 16 + 16);  // totals and counts, cleared together
+  const size_t o_cnt = o_tot + 16;
   const size_t o_cur = o_cnt + (size_t)ncell * 8;  // cleared with the counts
   const size_t o_off = al256v(o_cur + (size_t)ncell * 4);
   const size_t o_rng = o_off + al256v((size_t)(ncell + 1) * 8);
@@ -52,7 +53,7 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
   auto prepare = [&]() -> int {
     char *w = (char *)ctx->vol;
     float4 *gc = (float4 *)(w + o_gc), *rec = (float4 *)(w + o_rec);
-    TLAUNCH(k_fill_i32z, dim3(cdivv(3 * ncell, 256)), dim3(256), 0, st, (int *)(w + o_cnt), 3 * ncell);
+    TLAUNCH(k_fill_i32z, dim3(cdivv(3 * ncell + 4, 256)), dim3(256), 0, st, (int *)(w + o_tot), 3 * ncell + 4);
     if (N > 0) {
       Geom G{};
       G.N = N;
@@ -62,7 +63,7 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
       TLAUNCH(k_vox_prep, dim3(nwp), dim3(256), 0, st, (const float4 *)gc, V, rec,
               (int4 *)(w + o_box), (double *)(w + o_wp));
       TLAUNCH(k_vox_count, dim3(cdivv(N, per)), dim3(1024), (size_t)ncell * 8, st,
-              (const int4 *)(w + o_box), V, (int2 *)(w + o_cnt));
+              (const int4 *)(w + o_box), V, (int2 *)(w + o_cnt), (unsigned long long *)(w + o_tot));
     }
     TLAUNCH(k_vox_scan, dim3(1), dim3(1024), 0, st, (const int2 *)(w + o_cnt), ncell,
             (const double *)(w + o_wp), N > 0 ? nwp : 0, (int2 *)(w + o_off), (double *)(w + o_scale));
@@ -71,11 +72,13 @@ int cs_voxelize(cs_ctx *ctx, const cs_gaussians *g, int32_t D, float pixel, floa
   rc = prepare();
   if (rc) return rc;
   // the list lengths are known only now: read them back (this call synchronises)
-  int2 total{0, 0};
-  HIPCHK(hipMemcpyAsync(&total, (char *)ctx->vol + o_off + (size_t)ncell * 8, sizeof(total),
-                        hipMemcpyDeviceToHost, st));
+  struct {
+    unsigned long long x, y;
+  } total;
+  HIPCHK(hipMemcpyAsync(&total, (char *)ctx->vol + o_tot, sizeof(total), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
-  if (total.x < 0 || total.y < 0) return fail(ctx, CS_ERR_UNSUPPORTED, "too many (brick, Gaussian) pairs");
+  if (total.x > INT32_MAX || total.y > INT32_MAX)
+    return fail(ctx, CS_ERR_UNSUPPORTED, "too many (brick, Gaussian) pairs");
   const size_t o_cells = o_list + al256v((size_t)total.y * 4 + 4);
   const size_t need = o_cells + al256v((size_t)total.x * 4 + 4);
   if (need > ctx->vol_bytes) {
