@@ -40,7 +40,8 @@ __device__ inline CtfParticle ctf_particle(const CtfDev &c, int b) {
   CtfParticle q;
   q.du = c.defocus_u[b];
   q.dv = c.defocus_v[b];
-  const double a = c.astig ? (double)c.astig[b] : 0.0;
+  // (not read without astigmatism: it may be missing, stored as NaN)
+  const double a = c.astig && q.du != q.dv ? (double)c.astig[b] : 0.0;
   q.ph = c.phase ? (double)c.phase[b] : 0.0;
   float s2f, c2f;
   sincosf((float)(2.0 * a), &s2f, &c2f);
