@@ -357,6 +357,7 @@ int cs_cnn_tensor(cs_cnn *net, int32_t index, int32_t grad, uint16_t *dst, int64
  * bias [Cout] FP32 (may be NULL), padding 1, stride 2; H, W even; Cout a
  * multiple of 8; Cin a multiple of 8, or Cin = 1 (H = W, Cout <= 256) for
  * the first layer.  out_f32 (may be NULL) receives the FP32 values before rounding.
+ * Tensors on 16-byte boundaries take the faster kernels; others are taken too.
  * dgrad: din = conv^T(dout) with wt = w transposed to [Cin][3][3][Cout],
  * zeroed where act_in <= 0 (act_in may be NULL: no mask); Cin % 8 == 0.
  * wgrad: dw [Cout][3][3][Cin] FP32 = sum over batch and pixels (Cin = 1

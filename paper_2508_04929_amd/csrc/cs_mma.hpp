@@ -18,8 +18,8 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float mma_f32x4;
 
 constexpr int kMmaK = 64;  // K staged per step: two v_mfma_f32_16x16x32_bf16
 
-// Operand source of direct loads: 32-bit byte offsets from `base` below
-// `bytes`; a load at or past the end puts zeros into LDS.
+// Operand source of direct loads: 32-bit byte offsets from `base` (on a 16-byte
+// boundary) below `bytes`; a load at or past the end puts zeros into LDS.
 typedef __amdgpu_buffer_rsrc_t DmaSrc;
 constexpr unsigned kDmaMax = 0x7fffff00u;   // longest source
 constexpr unsigned kDmaZero = 0x80000000u;  // an offset past the end of any source

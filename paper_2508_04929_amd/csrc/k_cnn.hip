@@ -412,6 +412,34 @@ struct ConvDgradOp {
   __device__ int64_t ldo() const { return g.Cin; }
 };
 
+// weight gradient: M = Cout, N = 9 Cin (n = tap * Cin + ci), K = B Ho Wo
+// pixels; split-K partials part[z][M][N] (FP32).
+struct ConvWgradOp {
+  static constexpr bool kATrans = true, kBTrans = true;
+  ConvGeom g;
+  const bf16 *dout, *in;
+  float *part;
+  struct Row {};
+  // 8 consecutive output channels of pixel p
+  __device__ const uint4 *ptr_aT(int m, int p, bool &ok) const {
+    ok = true;
+    return (const uint4 *)&dout[(size_t)p * g.Cout + m];
+  }
+  // 8 consecutive (tap, ci) columns of the im2col row of pixel p
+  __device__ const uint4 *ptr_bT(int n, int p, bool &ok) const {
+    const int ox = p % g.Wo, t = p / g.Wo, oy = t % g.Ho, b = t / g.Ho;
+    const int tap = n / g.Cin, ci = n - tap * g.Cin;
+    const int iy = 2 * oy + tap / 3 - 1, ix = 2 * ox + tap % 3 - 1;
+    ok = iy >= 0 && iy < g.Hi && ix >= 0 && ix < g.Wi;
+    return (const uint4 *)(ok ? &in[(((size_t)b * g.Hi + iy) * g.Wi + ix) * g.Cin + ci] : in);
+  }
+  static constexpr bool kStaged = false;
+  __device__ float epi_in(int, int) const { return 0.f; }
+  __device__ void store(int m, int n, float v, int z, float) const {
+    part[((size_t)z * g.Cout + m) * 9 * g.Cin + n] = v;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // The same convolutions and data gradients with operand tiles loaded straight
 // into LDS (channels of a tap a multiple of 32: a K step of 32 stays within
@@ -1568,9 +1596,15 @@ static hipError_t launch_gemm(const Op &op, int M, int N, int K, int splits, hip
   return hipGetLastError();
 }
 
+template <class... T>
+static bool aligned_to(uintptr_t n, const T *...p) {
+  return (((uintptr_t)p | ...) & (n - 1)) == 0;
+}
+
 // The direct-to-LDS kernel takes a multiple of 32 channels per tap, as long as
 // 32-bit byte offsets reach across the images of one tile; other channel
-// counts go to k_gemm.
+// counts go to k_gemm.  So do operands off their 16-byte boundaries (views into
+// a larger buffer): a load into LDS has to be aligned, an ordinary one need not.
 static bool conv_mma_ok(int C, int B, int Hi, int Wi) {
   return C % 32 == 0 && (int64_t)B * Hi * Wi < ((int64_t)1 << 31) &&
          (int64_t)Hi * Wi * C * 2 + 512 * (int64_t)C * 8 < ((int64_t)1 << 30);
@@ -1614,7 +1648,7 @@ hipError_t conv_fwd(const bf16 *in, const bf16 *w, const float *bias, int B, int
                        Cout, relu, out, out32);
     return hipGetLastError();
   }
-  if (conv_mma_ok(Cin, B, Hi, Wi)) {
+  if (conv_mma_ok(Cin, B, Hi, Wi) && aligned_to(16, in, w) && aligned_to(16, out32) && aligned_to(8, out)) {
     ConvMma a{};
     a.src = in; a.w = w; a.bias = bias; a.out = out; a.out32 = out32; a.relu = relu;
     a.Hs = Hi; a.Ws = Wi; a.C = Cin; a.Hm = Hi / 2; a.Wm = Wi / 2; a.N = Cout;
@@ -1639,7 +1673,8 @@ hipError_t conv12_fwd(const bf16 *in0, const bf16 *w1, const float *b1, const bf
 
 hipError_t conv_dgrad(const bf16 *dout, const bf16 *wt, const bf16 *act_in, int B, int Hi, int Wi,
                       int Cin, int Cout, bf16 *din, float *din32, hipStream_t st) {
-  if (conv_mma_ok(Cout, B, Hi, Wi)) {
+  if (conv_mma_ok(Cout, B, Hi, Wi) && aligned_to(16, dout, wt) && aligned_to(16, din32) &&
+      aligned_to(8, act_in, din)) {
     ConvMma a{};
     a.src = dout; a.w = wt; a.mask = act_in; a.out = din; a.out32 = din32;
     a.Hs = a.Hm = Hi / 2; a.Ws = a.Wm = Wi / 2; a.C = Cout; a.N = Cin;
@@ -1705,12 +1740,22 @@ static int wgrad_plan(int Cin, int Cout, int64_t K, int *kchunk) {
 // a first layer's: 2^23 values.
 constexpr int64_t kPartMax = (int64_t)1 << 23;
 
+// Splits of k_gemm, which takes the operands that are not aligned.
+static int wgrad_gemm_plan(int Cin, int Cout, int64_t K) {
+  const int64_t n = (int64_t)Cout * 9 * Cin;
+  int s = wgrad_splits(Cout, 9 * Cin, (int)K);
+  while (s * n > kPartMax && s > 1) --s;
+  const int64_t c = (cdiv_(K, s) + MK - 1) / MK * MK;
+  return (int)cdiv_(K, c);
+}
+
 static bool conv1_wgrad_rows(int Wi, int Cout) { return Cout == 32 && Wi % 64 == 0; }
 
 size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool aligned) {
   const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
   if (Cin == 1)
     return (size_t)(aligned && conv1_wgrad_rows(Wi, Cout) ? kConv1Blocks : cdiv_(npix, 256)) * Cout * 10;
+  if (!aligned) return (size_t)wgrad_gemm_plan(Cin, Cout, npix) * Cout * 9 * Cin;
   // (room for every smaller batch too: a network allocates for its capacity)
   return (size_t)wgrad_most(Cin, Cout, npix) * Cout * (9 * Cin + 1);
 }
@@ -1719,7 +1764,7 @@ hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, i
                       float *part, size_t part_cap, float *dw, float *db, ReduceJob jobs[2],
                       hipStream_t st) {
   const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
-  const bool aligned = (((uintptr_t)dout | (uintptr_t)in) & 15) == 0;
+  const bool aligned = aligned_to(16, dout, in);
   const int64_t least = Cin == 1 ? (int64_t)cdiv_(npix, 256) * Cout * 9 : (int64_t)Cout * 9 * Cin;
   if (least > kPartMax || (Cin == 1 && Cout > 32) || npix >= ((int64_t)1 << 31) - 64 ||
       conv_wgrad_part(B, Hi, Wi, Cin, Cout, aligned) > part_cap)
@@ -1736,6 +1781,15 @@ hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, i
     part_b = part + (size_t)s * Cout * 9;
     hipLaunchKernelGGL(k_conv1_wgrad, dim3(s), dim3(256), 0, st, in, dout, B, Hi, Wi, Cout, 256, part,
                        part_b);
+  } else if (!aligned) {  // (a single layer's call: no bias gradient)
+    if (db) return hipErrorInvalidValue;
+    ConvWgradOp op;
+    op.g = {B, Hi, Wi, Cin, Hi / 2, Wi / 2, Cout};
+    op.dout = dout; op.in = in; op.part = part;
+    s = wgrad_gemm_plan(Cin, Cout, npix);
+    part_b = nullptr;
+    const hipError_t e = launch_gemm(op, Cout, 9 * Cin, (int)npix, s, st);
+    if (e != hipSuccess) return e;
   } else {
     WgradMma a{};
     a.dout = dout; a.in = in;
