@@ -1838,9 +1838,9 @@ hipError_t lin_wgrad(const bf16 *dy, const bf16 *x, int B, int In, int Out, floa
   const int M = Out, N = In, K = B;
   int s = wgrad_splits(M, N, K);
   const int chunks = std::max(1, std::min(1024, B / 32));
-  const size_t cap = part_cap - (db ? (size_t)chunks * Out : 0);
-  while ((size_t)s * M * N > cap && s > 1) --s;
-  if (part_cap < (size_t)chunks * Out || (size_t)s * M * N > cap) return hipErrorInvalidValue;
+  const size_t sums = db ? (size_t)chunks * Out : 0;  // partials of the bias gradient
+  while (s * (size_t)M * N + sums > part_cap && s > 1) --s;
+  if (s * (size_t)M * N + sums > part_cap) return hipErrorInvalidValue;
   int kchunk = (K + s - 1) / s;
   kchunk = (kchunk + MK - 1) / MK * MK;
   s = (K + kchunk - 1) / kchunk;
