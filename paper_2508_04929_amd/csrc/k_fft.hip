@@ -136,7 +136,7 @@ __global__ void __launch_bounds__(256)
 k_rows_inv_loss(float2 *spec, const float2 *tw, const float *obs, float *images_out,
                 float grad_scale, int adjoint, float *loss_part) {
   extern __shared__ float2 lds[];
-  __shared__ float red[256];
+  __shared__ double red[256];
   constexpr int L = P::L, Dh = L / 2 + 1;
   typedef typename P::Reverse Rev;
   const RowTeam<P> w(lds);
@@ -155,20 +155,21 @@ k_rows_inv_loss(float2 *spec, const float2 *tw, const float *obs, float *images_
       images_out[row0 + q] = v.x;
       images_out[row0 + L + q] = v.y;
     });
-  float acc = 0.f;
+  // (squares and sums in FP64: a team's values are one chain of L additions)
+  double acc = 0.0;
 #pragma unroll
   for (int m = 0; m < z.kN; ++m)
 #pragma unroll
     for (int i = 0; i < FftLast<P>::R; ++i) {
       const float ra = z.v[m][i].x - y.v[m][i].x, rb = z.v[m][i].y - y.v[m][i].y;
-      if (z.kJ % P::TS == 0 || w.t + m * P::TS < z.kJ) acc += ra * ra + rb * rb;
+      if (z.kJ % P::TS == 0 || w.t + m * P::TS < z.kJ) acc += (double)ra * ra + (double)rb * rb;
       z.v[m][i] = make_float2(grad_scale * ra, grad_scale * rb);
     }
   red[threadIdx.x] = acc;
   __syncthreads();
   if (w.t == 0 && w.valid) {
     for (int k = 1; k < P::TS; ++k) acc += red[threadIdx.x + k];
-    loss_part[(size_t)blockIdx.y * (L / 2) + w.pr] = acc;
+    loss_part[(size_t)blockIdx.y * (L / 2) + w.pr] = (float)acc;
   }
   if (!adjoint) return;
   FftVals<Rev, Rev::R0> g = fft_turn<P>(z);
