@@ -629,7 +629,9 @@ template __global__ void k_canvas_reduce_s<4>(const float *, const int *, const 
 // per record, per-lane moments over its pixel box, then a fixed-order sum.  A
 // block per record spent its time in the two barriers and the division per
 // pixel (8 images of 128 x 128, 2000 records each: 1.95 ms for loss and
-// gradient, 0.85 ms so and with the split sums of k_canvas_reduce).
+// gradient, 0.85 ms so and with the split sums of k_canvas_reduce).  A lane adds
+// runs of eight pixels before it adds them to its sums, which keeps its chain of
+// additions short in large images at no addition more.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void wide_moments(const float4 *list, int start, int cnt, int part, int parts,
                                              const Geom &G, int b, const float *GQ, float *mom) {
@@ -645,19 +647,38 @@ __device__ __forceinline__ void wide_moments(const float4 *list, int start, int 
       // (row, column) of pixel `lane` and of a step of 64 pixels
       int i = i0 + lane / wdt, j = j0 + lane % wdt;
       const int si = 64 / wdt, sj = 64 % wdt;
-#pragma unroll 4
-      for (int q = lane; q < npx; q += 64) {
+      auto term = [&](float *t) {
         const float dj = (float)j - r0.x, di = (float)i - r0.y;
         const float qq = r0.z * dj * dj + 2.f * r0.w * dj * di + r1.x * di * di;
-        const float t = qq <= G.qk ? img[i * G.D + j] * hexp2(-qq) : 0.f;
-        m[0] += t; m[1] += t * dj; m[2] += t * di;
-        m[3] += t * dj * dj; m[4] += t * dj * di; m[5] += t * di * di;
+        t[0] = qq <= G.qk ? img[i * G.D + j] * hexp2(-qq) : 0.f;
+        t[1] = t[0] * dj; t[2] = t[0] * di;
+        t[3] = t[1] * dj; t[4] = t[1] * di; t[5] = t[2] * di;
         i += si;
         j += sj;
         if (j > j1) {
           j -= wdt;
           ++i;
         }
+      };
+      int q = lane;
+      for (; q + 7 * 64 < npx; q += 8 * 64) {
+        float s[6];
+        term(s);
+#pragma unroll
+        for (int u = 1; u < 8; ++u) {
+          float t[6];
+          term(t);
+#pragma unroll
+          for (int c = 0; c < 6; ++c) s[c] += t[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) m[c] += s[c];
+      }
+      for (; q < npx; q += 64) {
+        float t[6];
+        term(t);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) m[c] += t[c];
       }
     }
 #pragma unroll
