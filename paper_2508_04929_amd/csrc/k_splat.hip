@@ -625,17 +625,22 @@ template __global__ void k_canvas_reduce_s<4>(const float *, const int *, const 
                                               const float4 *, Geom, float *);
 
 // ---------------------------------------------------------------------------
-// Wide records k = part, part + parts, ... of one image in the adjoint: a wave
-// per record, per-lane moments over its pixel box, then a fixed-order sum.  A
-// block per record spent its time in the two barriers and the division per
-// pixel (8 images of 128 x 128, 2000 records each: 1.95 ms for loss and
-// gradient, 0.85 ms so and with the split sums of k_canvas_reduce).  A lane adds
-// runs of eight pixels before it adds them to its sums, which keeps its chain of
-// additions short in large images at no addition more.
+// Wide records k = part, part + parts, ... of one image in the adjoint, W waves
+// to a record (1, or all four of the block): per-lane moments over its pixel box,
+// then a fixed-order sum.  A block per record spends its time in the two barriers
+// where records are small (8 images of 128 x 128, 2000 records each: 1.95 ms for
+// loss and gradient with it and a division per pixel, 0.85 ms with a wave per
+// record and the split sums of k_canvas_reduce), a wave per record leaves waves
+// idle where they are few (50 records over one image of 512 x 512, adjoint: 733 us,
+// with a block each 203).  A lane adds runs of eight pixels before it adds them to its sums, which keeps
+// its chain of additions short in large images at no addition more.
 // ---------------------------------------------------------------------------
+template <int W>
 __device__ __forceinline__ void wide_moments(const float4 *list, int start, int cnt, int part, int parts,
-                                             const Geom &G, int b, const float *GQ, float *mom) {
-  const int lane = threadIdx.x & 63;
+                                             const Geom &G, int b, const float *GQ, float *mom,
+                                             float (*red)[6]) {
+  constexpr int kStep = 64 * W;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, first = threadIdx.x % kStep;
   const float *img = GQ + (size_t)b * G.D * G.D;
   for (int k = part; k < cnt; k += parts) {
     const float4 r0 = list[2 * (size_t)(start + k)], r1 = list[2 * (size_t)(start + k) + 1];
@@ -644,9 +649,9 @@ __device__ __forceinline__ void wide_moments(const float4 *list, int start, int 
     float m[6] = {0, 0, 0, 0, 0, 0};
     if (i1 >= i0 && j1 >= j0) {
       const int wdt = j1 - j0 + 1, npx = (i1 - i0 + 1) * wdt;
-      // (row, column) of pixel `lane` and of a step of 64 pixels
-      int i = i0 + lane / wdt, j = j0 + lane % wdt;
-      const int si = 64 / wdt, sj = 64 % wdt;
+      // (row, column) of this lane's first pixel and of a step of kStep pixels
+      int i = i0 + first / wdt, j = j0 + first % wdt;
+      const int si = kStep / wdt, sj = kStep % wdt;
       auto term = [&](float *t) {
         const float dj = (float)j - r0.x, di = (float)i - r0.y;
         const float qq = r0.z * dj * dj + 2.f * r0.w * dj * di + r1.x * di * di;
@@ -660,8 +665,8 @@ __device__ __forceinline__ void wide_moments(const float4 *list, int start, int 
           ++i;
         }
       };
-      int q = lane;
-      for (; q + 7 * 64 < npx; q += 8 * 64) {
+      int q = first;
+      for (; q + 7 * kStep < npx; q += 8 * kStep) {
         float s[6];
         term(s);
 #pragma unroll
@@ -674,7 +679,7 @@ __device__ __forceinline__ void wide_moments(const float4 *list, int start, int 
 #pragma unroll
         for (int c = 0; c < 6; ++c) m[c] += s[c];
       }
-      for (; q < npx; q += 64) {
+      for (; q < npx; q += kStep) {
         float t[6];
         term(t);
 #pragma unroll
@@ -685,10 +690,23 @@ __device__ __forceinline__ void wide_moments(const float4 *list, int start, int 
     for (int c = 0; c < 6; ++c)
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) m[c] += __shfl_xor(m[c], o, 64);
-    if (lane == 0) {
-      float *o = mom + ((size_t)b * G.N + __float_as_int(r1.z)) * 6;
+    float *o = mom + ((size_t)b * G.N + __float_as_int(r1.z)) * 6;
+    if (W == 1) {
+      if (lane == 0) {
 #pragma unroll
-      for (int c = 0; c < 6; ++c) o[c] = m[c];
+        for (int c = 0; c < 6; ++c) o[c] = m[c];
+      }
+    } else {
+      if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) red[wv][c] = m[c];
+      }
+      __syncthreads();
+      if (threadIdx.x < 6) {
+        const int c = threadIdx.x;
+        o[c] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
+      }
+      __syncthreads();
     }
   }
 }
@@ -702,6 +720,7 @@ template <int RS>
 __global__ void __launch_bounds__(kBlock) k_splat_bwd_rs(MultiProb MP) {
   extern __shared__ float gq[];  // C rows of stride S
   __shared__ int slot;
+  __shared__ float wred[kBlock / 64][6];
   __shared__ OrderLds ol;
   for (int p = 0; p < MP.count; ++p) {
   if (p > 0) __syncthreads();  // the slot has been read
@@ -836,13 +855,17 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd_rs(MultiProb MP) {
     __syncthreads();  // the next chunk rewrites the order
     }
   }
-  // wide records: unit (image, part) after unit, a wave per record of the image
+  // wide records: unit (image, part) after unit; a block to a record where each
+  // part has one at most, else a wave
   if (MP.p[p].n_items[1] > 0) {
-    const int units = G.B * G.wide_parts, wv = threadIdx.x >> 6;
+    const int parts = G.wide_parts, units = G.B * parts;
     for (int un = blockIdx.x; un < units; un += gridDim.x) {
-      const int wb = un / G.wide_parts, e = wb * G.K + G.ntiles;
-      wide_moments(list, MP.p[p].off[e], MP.p[p].count[e], un % G.wide_parts * (kBlock / 64) + wv,
-                   G.wide_parts * (kBlock / 64), G, wb, GQ, mom);
+      const int wb = un / parts, part = un % parts, e = wb * G.K + G.ntiles;
+      const int start = MP.p[p].off[e], cnt = MP.p[p].count[e];
+      if (cnt <= parts)
+        wide_moments<4>(list, start, cnt, part, parts, G, wb, GQ, mom, wred);
+      else
+        wide_moments<1>(list, start, cnt, part * 4 + (threadIdx.x >> 6), parts * 4, G, wb, GQ, mom, wred);
     }
   }
   }
