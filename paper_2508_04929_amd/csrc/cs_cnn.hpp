@@ -27,7 +27,7 @@ struct ReduceJob {
   const float *part;
   float *out, *out2;
   int64_t n;
-  int splits, groups, block0;  // groups, block0: set by reduce_parts
+  int splits, groups, block0;  // log2 of the threads per output, first block: set by reduce_parts
 };
 constexpr int kReduceJobs = 16;
 struct ReduceJobs {
@@ -37,8 +37,8 @@ struct ReduceJobs {
 hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st);
 // Weight gradient dw and (db not null) bias gradient db: writes partials into
 // part (conv_wgrad_part / lin_wgrad_part floats; aligned: both operands on
-// 16-byte boundaries) and returns the two sums that
-// reduce_parts has still to take from them.
+// 16-byte boundaries) and returns the two sums that reduce_parts has still to take
+// from them (dw is written at once where it is one part alone and db is null).
 size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool aligned);
 hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout,
                       float *part, size_t part_cap, float *dw, float *db, ReduceJob jobs[2],

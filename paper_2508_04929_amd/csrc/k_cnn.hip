@@ -1076,31 +1076,34 @@ k_conv1_wgrad_mma(const bf16 *in, const bf16 *dpre, int B, int Hi, int Wi, float
 // out[i] = sum_z part[z n + i].  A block takes 256 / G outputs' columns with G
 // threads each (G grows with the number of partials), whose sums are added in
 // order.  A training step's 16 sums took 309 us in launches of their own, up
-// to 4,096 partials per thread one after the other; together they take 34 us,
-// about 60 MB read.
+// to 4,096 partials per thread one after the other; together they take 25 us,
+// about 60 MB read.  Up to 15 partials stay with one thread: 256 rows of a linear
+// layer of 1,024 to 256 in 8 parts 10.5 us, with four threads per output 12.1.
 __global__ void __launch_bounds__(256) k_reduce_parts(ReduceJobs jobs) {
   __shared__ float red[256];
   int j = 0;
   while (j + 1 < jobs.count && (int)blockIdx.x >= jobs.j[j + 1].block0) ++j;
   const ReduceJob J = jobs.j[j];
-  const int G = J.groups, W = 256 / G;
-  const int c = threadIdx.x % W, gz = threadIdx.x / W;
+  const int G = 1 << J.groups, W = 256 >> J.groups;
+  const int c = threadIdx.x & (W - 1), gz = threadIdx.x >> (8 - J.groups);
   const int64_t i = (int64_t)((int)blockIdx.x - J.block0) * W + c;
   float s = 0.f;
   if (i < J.n) {
-    const int z1 = (int)((int64_t)J.splits * (gz + 1) / G);
-    int z = (int)((int64_t)J.splits * gz / G);
-    for (; z + 8 <= z1; z += 8) {  // eight loads in flight
+    const int z1 = J.splits * (gz + 1) >> J.groups;
+    int z = J.splits * gz >> J.groups;
+    const float *p = J.part + z * J.n + i;
+    for (; z + 8 <= z1; z += 8, p += 8 * J.n) {  // eight loads in flight
       float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = J.part[(size_t)(z + u) * J.n + i];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
+      for (int u = 0; u < 8; ++u) v[u] = p[u * J.n];
+      s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
-    for (; z < z1; ++z) s += J.part[(size_t)z * J.n + i];
+    for (; z < z1; ++z, p += J.n) s += *p;
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
+  if (G > 1) {
+    red[threadIdx.x] = s;
+    __syncthreads();
+  }
   if (gz == 0 && i < J.n) {
     for (int k = 1; k < G; ++k) s += red[k * W + c];
     J.out[i] = s;
@@ -1705,9 +1708,9 @@ hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st) {
     ReduceJob &r = J.j[J.count];
     r = jobs[i];
     if (r.n == 0) continue;
-    r.groups = r.splits >= 64 ? 16 : r.splits >= 8 ? 4 : 1;
+    r.groups = r.splits >= 64 ? 4 : r.splits >= 16 ? 2 : 0;
     r.block0 = block;
-    block += (int)cdiv_(r.n, 256 / r.groups);
+    block += (int)cdiv_(r.n, 256 >> r.groups);
     if (++J.count == kReduceJobs || i + 1 == count) {
       hipLaunchKernelGGL(k_reduce_parts, dim3(block), dim3(256), 0, st, J);
       J = ReduceJobs{};
@@ -1785,8 +1788,8 @@ hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, i
     if (db) return hipErrorInvalidValue;
     ConvWgradOp op;
     op.g = {B, Hi, Wi, Cin, Hi / 2, Wi / 2, Cout};
-    op.dout = dout; op.in = in; op.part = part;
     s = wgrad_gemm_plan(Cin, Cout, npix);
+    op.dout = dout; op.in = in; op.part = s == 1 ? dw : part;
     part_b = nullptr;
     const hipError_t e = launch_gemm(op, Cout, 9 * Cin, (int)npix, s, st);
     if (e != hipSuccess) return e;
@@ -1798,15 +1801,17 @@ hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, i
     a.K = (int)npix;
     s = wgrad_plan(Cin, Cout, npix, &a.kchunk);
     part_b = part + (size_t)s * Cout * 9 * Cin;
-    a.part = part;
+    a.part = s == 1 && !db ? dw : part;
     a.part_b = part_b;
     if (Cout > 64)
       hipLaunchKernelGGL((k_wgrad_mma<4, 4>), dim3(cdiv_(Cout, 128), cdiv_(9 * Cin, 128), s), dim3(256), 0, st, a);
     else
       hipLaunchKernelGGL((k_wgrad_mma<2, 4>), dim3(cdiv_(Cout, 64), cdiv_(9 * Cin, 128), s), dim3(256), 0, st, a);
   }
-  jobs[0] = ReduceJob{part, dw, nullptr, (int64_t)Cout * 9 * Cin, s, 1, 0};
-  jobs[1] = ReduceJob{part_b, db, nullptr, db ? Cout : 0, s, 1, 0};
+  // (one split without a bias gradient: dw has the sums already)
+  const bool direct = s == 1 && !db && Cin > 1;
+  jobs[0] = ReduceJob{part, dw, nullptr, direct ? 0 : (int64_t)Cout * 9 * Cin, s, 0, 0};
+  jobs[1] = ReduceJob{part_b, db, nullptr, db ? Cout : 0, s, 0, 0};
   return hipGetLastError();
 }
 
@@ -1844,15 +1849,17 @@ hipError_t lin_wgrad(const bf16 *dy, const bf16 *x, int B, int In, int Out, floa
   int kchunk = (K + s - 1) / s;
   kchunk = (kchunk + MK - 1) / MK * MK;
   s = (K + kchunk - 1) / kchunk;
+  const bool direct = s == 1 && !db;  // as in conv_wgrad
+  if (direct) op.part = dw;
   hipError_t e = launch_gemm(op, M, N, K, s, st);
   if (e != hipSuccess) return e;
-  jobs[0] = ReduceJob{part, dw, nullptr, (int64_t)M * N, s, 1, 0};
+  jobs[0] = ReduceJob{part, dw, nullptr, direct ? 0 : (int64_t)M * N, s, 0, 0};
   jobs[1] = ReduceJob{};
   if (db) {
     float *pb = part + (size_t)s * M * N;
     hipLaunchKernelGGL(k_colsum, dim3(cdiv_(Out, 256), chunks), dim3(256), 0, st, dy, B, Out,
                        (B + chunks - 1) / chunks, pb);
-    jobs[1] = ReduceJob{pb, db, nullptr, Out, chunks, 1, 0};
+    jobs[1] = ReduceJob{pb, db, nullptr, Out, chunks, 0, 0};
   }
   return hipGetLastError();
 }
