@@ -401,7 +401,8 @@ int cs_bf16_conv3x3s2_wgrad(cs_ctx *ctx, const uint16_t *dout, const uint16_t *i
       (Cin != 1 && Cin % 8) || (Cin == 1 && Cout > 32))
     return fail(ctx, CS_ERR_INVALID_ARG, "bad conv wgrad arguments");
   HIPCHK(hipSetDevice(ctx->device));
-  const size_t cap = conv_wgrad_part(B, H, W, Cin, Cout, (((uintptr_t)dout | (uintptr_t)in) & 15) == 0);
+  const size_t cap = conv_wgrad_part(B, H, W, Cin, Cout,
+                                     conv_wgrad_direct((const bf16 *)dout, (const bf16 *)in, B, H, W, Cin, Cout, false));
   int rc = ensure_aux(ctx, cap * 4);
   if (rc) return rc;
   ReduceJob j[2];

@@ -36,10 +36,11 @@ struct ReduceJobs {
 };
 hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st);
 // Weight gradient dw and (db not null) bias gradient db: writes partials into
-// part (conv_wgrad_part / lin_wgrad_part floats; aligned: both operands on
-// 16-byte boundaries) and returns the two sums that reduce_parts has still to take
-// from them (dw is written at once where it is one part alone and db is null).
-size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool aligned);
+// part (conv_wgrad_part / lin_wgrad_part floats; direct: conv_wgrad_direct, true in
+// a network) and returns the two sums that reduce_parts has still to take from them
+// (dw is written at once where it is one part alone and db is null).
+bool conv_wgrad_direct(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout, bool bias);
+size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool direct);
 hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout,
                       float *part, size_t part_cap, float *dw, float *db, ReduceJob jobs[2],
                       hipStream_t st);

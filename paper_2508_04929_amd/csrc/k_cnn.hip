@@ -8,6 +8,8 @@
 // v_mfma_f32_16x16x32_bf16 (gfx950): a 64x64 block tile, four waves of
 // 32x32, K steps of 32 staged through LDS.  Operand tiles are gathered
 // straight from the activations (implicit im2col), 16 bytes per thread.
+#include <cmath>
+
 #include "cs_cnn.hpp"
 #include "cs_internal.hpp"
 #include "cs_mma.hpp"
@@ -1077,7 +1079,7 @@ k_conv1_wgrad_mma(const bf16 *in, const bf16 *dpre, int B, int Hi, int Wi, float
 // threads each (G grows with the number of partials), whose sums are added in
 // order.  A training step's 16 sums took 309 us in launches of their own, up
 // to 4,096 partials per thread one after the other; together they take 25 us,
-// about 60 MB read.  Up to 15 partials stay with one thread: 256 rows of a linear
+// about 60 MB read.  Up to 31 partials stay with one thread: 256 rows of a linear
 // layer of 1,024 to 256 in 8 parts 10.5 us, with four threads per output 12.1.
 __global__ void __launch_bounds__(256) k_reduce_parts(ReduceJobs jobs) {
   __shared__ float red[256];
@@ -1708,7 +1710,7 @@ hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st) {
     ReduceJob &r = J.j[J.count];
     r = jobs[i];
     if (r.n == 0) continue;
-    r.groups = r.splits >= 64 ? 4 : r.splits >= 16 ? 2 : 0;
+    r.groups = r.splits >= 64 ? 4 : r.splits >= 32 ? 2 : 0;
     r.block0 = block;
     block += (int)cdiv_(r.n, 256 >> r.groups);
     if (++J.count == kReduceJobs || i + 1 == count) {
@@ -1721,17 +1723,23 @@ hipError_t reduce_parts(const ReduceJob *jobs, int count, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Splits of a weight gradient's pixels: about one block of 128 x 128 outputs
-// per CU (two of 64 x 128), each at least 16 steps of 32 pixels long so that
-// the partials stay a small part of the traffic.  wgrad_most is what the rule
-// asks for and never falls as the pixels grow; whole steps per split can leave
-// one of them over, so the plan may take fewer (and, at some sizes, more than it
-// takes for a few more pixels).
+// Splits of a weight gradient's pixels: as many as make a block's walk over its
+// pixels and the reading of all partials about equally long (time a K / s + b s n
+// for n weights), but no more than about one block of 128 x 128 outputs per CU (two
+// of 64 x 128), and two steps of 32 pixels each.  With at least 16 steps per split
+// instead, small products left the chip idle (us, 16 steps -> this): 4 images of
+// 64 x 64, 32 to 64 channels 14.0 -> 9.3; 16 images 14.8 -> 14.3; 64 images of 8 x 8,
+// 256 to 256 19.9 -> 19.1; half and twice the splits 10.9 and 10.0, 14.0 and 15.2,
+// 19.2 and 18.6.
+// wgrad_most is what the rule asks for and never falls as the pixels grow; whole
+// steps per split can leave one of them over, so the plan may take fewer (and, at
+// some sizes, more than it takes for a few more pixels).
 constexpr int kConv1Blocks = 512;  // two per CU
 static int wgrad_most(int Cin, int Cout, int64_t K) {
   const int tiles = (int)(cdiv_(Cout, Cout > 64 ? 128 : 64) * cdiv_(9 * Cin, 128));
-  const int want = (Cout > 64 ? 256 : 512) / tiles;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(want, K / 512));
+  const int64_t want = (Cout > 64 ? 256 : 512) / tiles;
+  const int64_t even = (int64_t)std::sqrt(512.0 * (double)K / ((double)Cin * Cout));
+  return (int)std::max<int64_t>(1, std::min({want, even, K / 64}));
 }
 static int wgrad_plan(int Cin, int Cout, int64_t K, int *kchunk) {
   const int64_t c = (cdiv_(K, wgrad_most(Cin, Cout, K)) + 31) / 32 * 32;
@@ -1742,8 +1750,14 @@ static int wgrad_plan(int Cin, int Cout, int64_t K, int *kchunk) {
 // Largest weight gradient that is taken, and largest set of 256-pixel chunks of
 // a first layer's: 2^23 values.
 constexpr int64_t kPartMax = (int64_t)1 << 23;
+// Products below which k_gemm's smaller tiles take a weight gradient in several
+// splits (us, k_gemm and k_wgrad_mma): 64 channels, 19 million products 7.3 and
+// 8.4, 75 million 11.8 and 9.3; 128, 60 million 9.9 and 11.6, 240 million 16.9 and
+// 14.2.  A single split has no partials to read, and goes to k_wgrad_mma (256 to
+// 256 channels, 64 pixels: 10.2 and 7.0).
+static int64_t wgrad_gemm_products(int Cout) { return (int64_t)1 << (Cout > 64 ? 27 : 26); }
 
-// Splits of k_gemm, which takes the operands that are not aligned.
+// Splits of k_gemm, which takes small products and operands that are not aligned.
 static int wgrad_gemm_plan(int Cin, int Cout, int64_t K) {
   const int64_t n = (int64_t)Cout * 9 * Cin;
   int s = wgrad_splits(Cout, 9 * Cin, (int)K);
@@ -1754,11 +1768,17 @@ static int wgrad_gemm_plan(int Cin, int Cout, int64_t K) {
 
 static bool conv1_wgrad_rows(int Wi, int Cout) { return Cout == 32 && Wi % 64 == 0; }
 
-size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool aligned) {
+bool conv_wgrad_direct(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, int Cin, int Cout, bool bias) {
+  const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
+  return aligned_to(16, dout, in) && (Cin == 1 || bias || wgrad_most(Cin, Cout, npix) == 1 ||
+                                      npix * 9 * Cin * Cout >= wgrad_gemm_products(Cout));
+}
+
+size_t conv_wgrad_part(int B, int Hi, int Wi, int Cin, int Cout, bool direct) {
   const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
   if (Cin == 1)
-    return (size_t)(aligned && conv1_wgrad_rows(Wi, Cout) ? kConv1Blocks : cdiv_(npix, 256)) * Cout * 10;
-  if (!aligned) return (size_t)wgrad_gemm_plan(Cin, Cout, npix) * Cout * 9 * Cin;
+    return (size_t)(direct && conv1_wgrad_rows(Wi, Cout) ? kConv1Blocks : cdiv_(npix, 256)) * Cout * 10;
+  if (!direct) return (size_t)wgrad_gemm_plan(Cin, Cout, npix) * Cout * 9 * Cin;
   // (room for every smaller batch too: a network allocates for its capacity)
   return (size_t)wgrad_most(Cin, Cout, npix) * Cout * (9 * Cin + 1);
 }
@@ -1767,14 +1787,14 @@ hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, i
                       float *part, size_t part_cap, float *dw, float *db, ReduceJob jobs[2],
                       hipStream_t st) {
   const int64_t npix = (int64_t)B * (Hi / 2) * (Wi / 2);
-  const bool aligned = aligned_to(16, dout, in);
+  const bool direct = conv_wgrad_direct(dout, in, B, Hi, Wi, Cin, Cout, db != nullptr);
   const int64_t least = Cin == 1 ? (int64_t)cdiv_(npix, 256) * Cout * 9 : (int64_t)Cout * 9 * Cin;
   if (least > kPartMax || (Cin == 1 && Cout > 32) || npix >= ((int64_t)1 << 31) - 64 ||
-      conv_wgrad_part(B, Hi, Wi, Cin, Cout, aligned) > part_cap)
+      conv_wgrad_part(B, Hi, Wi, Cin, Cout, direct) > part_cap)
     return hipErrorInvalidValue;
   int s;
   float *part_b;
-  if (Cin == 1 && aligned && conv1_wgrad_rows(Wi, Cout)) {
+  if (Cin == 1 && direct && conv1_wgrad_rows(Wi, Cout)) {
     // output rows of whole 32-pixel steps (every network input side)
     s = kConv1Blocks;
     part_b = part + (size_t)s * Cout * 9;
@@ -1784,8 +1804,8 @@ hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, i
     part_b = part + (size_t)s * Cout * 9;
     hipLaunchKernelGGL(k_conv1_wgrad, dim3(s), dim3(256), 0, st, in, dout, B, Hi, Wi, Cout, 256, part,
                        part_b);
-  } else if (!aligned) {  // (a single layer's call: no bias gradient)
-    if (db) return hipErrorInvalidValue;
+  } else if (!direct) {
+    if (db) return hipErrorInvalidValue;  // (a network's tensors are aligned)
     ConvWgradOp op;
     op.g = {B, Hi, Wi, Cin, Hi / 2, Wi / 2, Cout};
     s = wgrad_gemm_plan(Cin, Cout, npix);
@@ -1809,8 +1829,8 @@ hipError_t conv_wgrad(const bf16 *dout, const bf16 *in, int B, int Hi, int Wi, i
       hipLaunchKernelGGL((k_wgrad_mma<2, 4>), dim3(cdiv_(Cout, 64), cdiv_(9 * Cin, 128), s), dim3(256), 0, st, a);
   }
   // (one split without a bias gradient: dw has the sums already)
-  const bool direct = s == 1 && !db && Cin > 1;
-  jobs[0] = ReduceJob{part, dw, nullptr, direct ? 0 : (int64_t)Cout * 9 * Cin, s, 0, 0};
+  const bool whole = s == 1 && !db && Cin > 1;
+  jobs[0] = ReduceJob{part, dw, nullptr, whole ? 0 : (int64_t)Cout * 9 * Cin, s, 0, 0};
   jobs[1] = ReduceJob{part_b, db, nullptr, db ? Cout : 0, s, 0, 0};
   return hipGetLastError();
 }
@@ -1849,11 +1869,11 @@ hipError_t lin_wgrad(const bf16 *dy, const bf16 *x, int B, int In, int Out, floa
   int kchunk = (K + s - 1) / s;
   kchunk = (kchunk + MK - 1) / MK * MK;
   s = (K + kchunk - 1) / kchunk;
-  const bool direct = s == 1 && !db;  // as in conv_wgrad
-  if (direct) op.part = dw;
+  const bool whole = s == 1 && !db;  // as in conv_wgrad
+  if (whole) op.part = dw;
   hipError_t e = launch_gemm(op, M, N, K, s, st);
   if (e != hipSuccess) return e;
-  jobs[0] = ReduceJob{part, dw, nullptr, direct ? 0 : (int64_t)M * N, s, 0, 0};
+  jobs[0] = ReduceJob{part, dw, nullptr, whole ? 0 : (int64_t)M * N, s, 0, 0};
   jobs[1] = ReduceJob{};
   if (db) {
     float *pb = part + (size_t)s * M * N;
