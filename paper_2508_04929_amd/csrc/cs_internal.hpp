@@ -242,7 +242,7 @@ RowsFwdFn fft_rows_fwd(int L);
 RowsInvFn fft_rows_inv(int L);
 RowsInvLossFn fft_rows_inv_loss(int L);
 ColsCtfFn fft_cols_ctf(int L, bool narrow);
-ColsShiftFn fft_cols_shift(int L);
+ColsShiftFn fft_cols_shift(int L, bool narrow);
 AxisFn fft_axis(int L);
 struct FftShape {
   int ts = 0, slots = 0;

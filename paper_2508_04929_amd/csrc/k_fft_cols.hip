@@ -95,23 +95,20 @@ k_cols_shift(float2 *spec, const float2 *tw, const float *shift, float inv_pixel
   const bool even = (L % 2) == 0;
   const int half = L / 2;
   const float norm = 1.f / ((float)L * (float)L);
+  // the cosines of the Nyquist lines, once per thread: a copy of that code per
+  // value kept small launches waiting for instructions (one image of 256 x 256
+  // 20.9 us, now 17.0; 64 images 46.8 and 40.6)
+  const bool nx = even && kx == half;
+  const double amp_x = nx ? cos(M_PI * ac) : 1.0;              // rows but the Nyquist one
+  const double amp_y = cos(nx ? M_PI * (ac + ar) : M_PI * ar);  // the Nyquist row
   w.apply(spec + (size_t)b * L * Dh + kx, Dh, tw, lds, [&](int ky, float2 z) {
-    const bool nx = even && kx == half, ny = even && ky == half;
+    const bool ny = even && ky == half;
     const int fy = ky < (L + 1) / 2 ? ky : ky - L;
-    double turns;
-    double amp = 1.0;
-    if (nx && ny) {
-      turns = 0.0;
-      amp = cos(M_PI * (ac + ar));
-    } else if (nx) {
-      turns = -(double)fy * ar / L;
-      amp = cos(M_PI * ac);
-    } else if (ny) {
-      turns = -(double)kx * ac / L;
-      amp = cos(M_PI * ar);
-    } else {
-      turns = -((double)kx * ac + (double)fy * ar) / L;
-    }
+    const double amp = ny ? amp_y : amp_x;
+    const double turns = nx && ny ? 0.0
+                         : nx     ? -(double)fy * ar / L
+                         : ny     ? -(double)kx * ac / L
+                                  : -((double)kx * ac + (double)fy * ar) / L;
     const float red = (float)((turns - rint(turns)) * (2.0 * M_PI));
     float sn, cs;
     sincosf(red, &sn, &cs);
@@ -147,8 +144,8 @@ ColsCtfFn fft_cols_ctf(int L, bool narrow) {
 }
 #undef X
 #define X(N, A, B, C, T) \
-  case N: return &k_cols_shift<FftRadices<A, B, C, T>, wide_cols(N)>;
-ColsShiftFn fft_cols_shift(int L) {
+  case N: return narrow ? &k_cols_shift<FftRadices<A, B, C, T>, 4> : &k_cols_shift<FftRadices<A, B, C, T>, wide_cols(N)>;
+ColsShiftFn fft_cols_shift(int L, bool narrow) {
   switch (L) { CS_FFT_LENGTHS(X) }
   return nullptr;
 }

@@ -42,12 +42,12 @@ int cs_fourier_shift(cs_ctx *ctx, const float *images, const float *shift, int64
   if (rc) return rc;
   float2 *spec = (float2 *)ctx->aux;
   const RowsFwdFn k_fft_rows_fwd = fft_rows_fwd(D);
-  const ColsShiftFn k_fft_cols_shift = fft_cols_shift(D);
   const RowsInvFn k_fft_rows_inv = fft_rows_inv(D);
   const size_t npix = (size_t)D * D;
   for (int64_t b0 = 0; b0 < B; b0 += chunk) {
     const int nb = (int)std::min<int64_t>(chunk, B - b0);
-    const FftLaunch r = fft_rows_launch(D, nb), c = fft_cols_launch(D, Dh, nb, false);
+    const FftLaunch r = fft_rows_launch(D, nb), c = fft_cols_launch(D, Dh, nb, true);
+    const ColsShiftFn k_fft_cols_shift = fft_cols_shift(D, c.narrow);
     TLAUNCH(k_fft_rows_fwd, r.grid, r.block, r.lds, st, images + b0 * npix, tw, spec);
     TLAUNCH(k_fft_cols_shift, c.grid, c.block, c.lds, st, spec, tw, shift + 2 * b0, 1.f / pixel,
             direction);
