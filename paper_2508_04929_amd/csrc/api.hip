@@ -461,10 +461,11 @@ int launch_one_persistent(cs_ctx *ctx, bool forward, const MultiProb &MP, size_t
   int rc = persistent_grid(ctx, (const void *)(forward ? k_splat_fwd : k_splat_bwd), lds, &grid);
   if (rc) return rc;
   // no more blocks than there can be work items, as the rest would only queue up
-  // at the counter, but in the adjoint two per CU for wide records, which are no
-  // work items (2000 of them over one image of 512 x 512: 1639 us with one per CU,
-  // 842 with two and with four; small calls the same with each)
-  grid = (int)std::min<int64_t>(grid, std::max<int64_t>(items, forward ? 1 : 512));
+  // at the counter, but in the adjoint up to four per CU for wide records, which are
+  // no work items (2000 of them over one image of 512 x 512: half the time with two and
+  // with four of that with one; 1000 in each of 37 of 101 x 101: 688 us with two, 416
+  // with four; small calls without any the same with each)
+  grid = (int)std::min<int64_t>(grid, std::max<int64_t>(items, forward ? 1 : 1024));
   if (forward) {
     TLAUNCH(k_splat_fwd, dim3(grid), dim3(kBlock), lds, st, MP);
   } else {

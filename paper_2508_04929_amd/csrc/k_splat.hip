@@ -632,8 +632,11 @@ template __global__ void k_canvas_reduce_s<4>(const float *, const int *, const 
 // loss and gradient with it and a division per pixel, 0.85 ms with a wave per
 // record and the split sums of k_canvas_reduce), a wave per record leaves waves
 // idle where they are few (50 records over one image of 512 x 512, adjoint: 733 us,
-// with a block each 203).  A lane adds runs of eight pixels before it adds them to its sums, which keeps
-// its chain of additions short in large images at no addition more.
+// with a block each 188).  A lane adds runs of eight pixels before it adds them to
+// its sums, which keeps its chain of additions short in large images, and requests
+// a pixel one step ahead; unrolled loops took more registers than the rest of the
+// kernel leaves at seven waves per SIMD (training step of 64 images of 256 x 256
+// 2,610 us with 88, 2,585 with 69).
 // ---------------------------------------------------------------------------
 template <int W>
 __device__ __forceinline__ void wide_moments(const float4 *list, int start, int cnt, int part, int parts,
@@ -652,39 +655,32 @@ __device__ __forceinline__ void wide_moments(const float4 *list, int start, int 
       // (row, column) of this lane's first pixel and of a step of kStep pixels
       int i = i0 + first / wdt, j = j0 + first % wdt;
       const int si = kStep / wdt, sj = kStep % wdt;
-      auto term = [&](float *t) {
-        const float dj = (float)j - r0.x, di = (float)i - r0.y;
-        const float qq = r0.z * dj * dj + 2.f * r0.w * dj * di + r1.x * di * di;
-        t[0] = qq <= G.qk ? img[i * G.D + j] * hexp2(-qq) : 0.f;
-        t[1] = t[0] * dj; t[2] = t[0] * di;
-        t[3] = t[1] * dj; t[4] = t[1] * di; t[5] = t[2] * di;
+      float s[6] = {0, 0, 0, 0, 0, 0};
+      float g = img[min(i, i1) * G.D + j];
+#pragma unroll 1
+      for (int q = first, k = 1; q < npx; q += kStep, ++k) {
+        const float dj = (float)j - r0.x, di = (float)i - r0.y, now = g;
         i += si;
         j += sj;
         if (j > j1) {
           j -= wdt;
           ++i;
         }
-      };
-      int q = first;
-      for (; q + 7 * kStep < npx; q += 8 * kStep) {
-        float s[6];
-        term(s);
+        g = img[min(i, i1) * G.D + j];  // the next pixel's (past the end: one of the last row, unused)
+        const float qq = r0.z * dj * dj + 2.f * r0.w * dj * di + r1.x * di * di;
+        const float t = qq <= G.qk ? now * hexp2(-qq) : 0.f;
+        s[0] += t; s[1] += t * dj; s[2] += t * di;
+        s[3] += t * dj * dj; s[4] += t * dj * di; s[5] += t * di * di;
+        if (k % 8 == 0) {
 #pragma unroll
-        for (int u = 1; u < 8; ++u) {
-          float t[6];
-          term(t);
-#pragma unroll
-          for (int c = 0; c < 6; ++c) s[c] += t[c];
+          for (int c = 0; c < 6; ++c) {
+            m[c] += s[c];
+            s[c] = 0.f;
+          }
         }
-#pragma unroll
-        for (int c = 0; c < 6; ++c) m[c] += s[c];
       }
-      for (; q < npx; q += kStep) {
-        float t[6];
-        term(t);
 #pragma unroll
-        for (int c = 0; c < 6; ++c) m[c] += t[c];
-      }
+      for (int c = 0; c < 6; ++c) m[c] += s[c];
     }
 #pragma unroll
     for (int c = 0; c < 6; ++c)
@@ -856,13 +852,15 @@ __global__ void __launch_bounds__(kBlock) k_splat_bwd_rs(MultiProb MP) {
     }
   }
   // wide records: unit (image, part) after unit; a block to a record where each
-  // part has one at most, else a wave
+  // part has three at most, else a wave (200 records in each of 4 images of 256 x
+  // 256, 128 parts: 217 us by waves, 107 by blocks; at four of a part's the waves
+  // are all busy)
   if (MP.p[p].n_items[1] > 0) {
     const int parts = G.wide_parts, units = G.B * parts;
     for (int un = blockIdx.x; un < units; un += gridDim.x) {
       const int wb = un / parts, part = un % parts, e = wb * G.K + G.ntiles;
       const int start = MP.p[p].off[e], cnt = MP.p[p].count[e];
-      if (cnt <= parts)
+      if (cnt <= 3 * parts)
         wide_moments<4>(list, start, cnt, part, parts, G, wb, GQ, mom, wred);
       else
         wide_moments<1>(list, start, cnt, part * 4 + (threadIdx.x >> 6), parts * 4, G, wb, GQ, mom, wred);
