@@ -300,8 +300,9 @@ Geom make_geom(const cs_gaussians *g, const cs_views *v, const cs_options *opt, 
   G.qk = qc * kHalfLog2e;
   // Few pairs in few tiles: a quarter of the tile and a smaller work item
   // spread them over more blocks.  With more tiles the default ones fill the
-  // chip, and four times as many canvases only cost (512 images of 64 x 64 with
-  // 128 Gaussians each: 221 us with default tiles, 275 us with small ones).
+  // chip, and four times as many canvases only cost (loss and gradient, us, default
+  // and small tiles: 512 images of 64 x 64 with 64 Gaussians each 152 and 206, 300
+  // images with 32 each 116 and 119, 256 images with 128 each 110 and 108).
   // Never beside a halo above the default, whose canvases would outgrow the
   // tile.
   small = small && (int64_t)G.N * G.B <= kSmallPairs && !(opt && (opt->tile || opt->halo > kDefaultHalo)) &&

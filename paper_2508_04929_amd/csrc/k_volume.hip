@@ -16,7 +16,7 @@
 //
 // FSC: the 3-D real DFT is the renderer's row pass (real rows along x, two
 // per complex transform) over the D slices, then the same Stockham
-// transform along y and along z (k_fft_axis); shell sums of
+// transform along y and along z (k_axis); shell sums of
 // Re(Fa conj Fb), |Fa|^2, |Fb|^2 (weight 2 off the kx = 0 and Nyquist
 // planes) are again exact 64-bit fixed-point sums, scaled by Parseval's
 // bound D^3 max(sum Va^2, sum Vb^2) on every shell sum.
@@ -98,14 +98,12 @@ struct Box {
   }
 };
 
-// The lists are built in two levels: Gaussians under cells of 2^3 bricks (4^3
-// in volumes above 256^3), then
-// each cell's Gaussians under its bricks.  Both levels count in LDS, and a block
-// adds to memory once per cell that it met.  With a memory atomic per (brick,
-// Gaussian) pair the 200000 Gaussians of 14 bricks each in a 256^3 volume took
-// 107 us to count, 57 to scan over 32768 bricks and 98 to list, bound by those
-// atomics; the two levels take 22 + 6
-// + 21 + 27 us.
+// The lists are built in two levels: Gaussians under cells of 2^3 bricks (4^3 in
+// volumes above 256^3), then each cell's Gaussians under its bricks.  Both levels
+// count in LDS, and a block adds to memory once per cell that it met.  With a memory
+// atomic per (brick, Gaussian) pair the 200000 Gaussians of 14 bricks each in a 256^3
+// volume took 107 us to count, 57 to scan over 32768 bricks and 98 to list, bound by
+// those atomics; the two levels take 22 + 6 + 21 + 27 us.
 
 // Gaussians and (brick, Gaussian) pairs of every cell; 8 lanes to a Gaussian.
 // The lists are indexed with 32 bits, so the totals are kept in 64: where they do
