@@ -1615,6 +1615,21 @@ static bool conv_mma_ok(int C, int B, int Hi, int Wi) {
          (int64_t)Hi * Wi * C * 2 + 512 * (int64_t)C * 8 < ((int64_t)1 << 30);
 }
 
+// Forward convolutions that k_gemm does faster (the same bits).  The ring fills its
+// tiles once per block and holds a CU by itself, which short contractions do not pay
+// for once there is more than a round of blocks: C channels in, N out, M pixels, us,
+// k_gemm and ring: 32 to 64, M 65,536 13 and 12, 131,072 19 and 23, 524,288 61 and
+// 73; 64 to 64, 131,072 30 and 31, 524,288 120 and 126; 64 to 128, 65,536 27 and 24,
+// 98,304 32 and 41, 524,288 171 and 189; 96 to 128, 106 and 112 at 1,024 tiles of
+// 256 x 128; 128 to 128, 146 and 136.  Longer ones only lose a half-empty second
+// round: 192 to 128, 72 and 77 at 384 tiles, 100 and 81 at 448.
+static bool conv_fwd_by_gemm(int C, int N, int64_t M) {
+  if (N <= 32) return false;
+  if (N <= 64) return C <= 64 && M > 2048 * C;
+  const int64_t tiles = (int64_t)cdiv_(M, 256) * cdiv_(N, 128);
+  return tiles > 256 && (C <= 64 || (C <= 96 && N <= 128) || (C <= 192 && tiles <= 384));
+}
+
 template <int NWM, int NWN, int TI, int TJ, int S, bool DGRAD>
 static void launch_conv_tile(const ConvMma &a, hipStream_t st) {
   const unsigned tiles = cdiv_(a.M, NWM * TI * 16) * cdiv_(a.N, NWN * TJ * 16) * (DGRAD ? 4 : 1);
@@ -1653,7 +1668,8 @@ hipError_t conv_fwd(const bf16 *in, const bf16 *w, const float *bias, int B, int
                        Cout, relu, out, out32);
     return hipGetLastError();
   }
-  if (conv_mma_ok(Cin, B, Hi, Wi) && aligned_to(16, in, w) && aligned_to(16, out32) && aligned_to(8, out)) {
+  if (conv_mma_ok(Cin, B, Hi, Wi) && !conv_fwd_by_gemm(Cin, Cout, (int64_t)B * (Hi / 2) * (Wi / 2)) &&
+      aligned_to(16, in, w) && aligned_to(16, out32) && aligned_to(8, out)) {
     ConvMma a{};
     a.src = in; a.w = w; a.bias = bias; a.out = out; a.out32 = out32; a.relu = relu;
     a.Hs = Hi; a.Ws = Wi; a.C = Cin; a.Hm = Hi / 2; a.Wm = Wi / 2; a.N = Cout;
