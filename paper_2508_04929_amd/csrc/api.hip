@@ -514,14 +514,33 @@ int launch_forward_finish(cs_ctx *ctx, const Plan &P, float *Q, hipStream_t st) 
   // image of 128 x 128 and 66000 Gaussians takes 142 us for loss and gradient
   // without and 123 us with, batch-1 steps 97 and 90 us; 64 images of 128 x 128
   // (1024 tiles) take 189 us without and 195 us with
+  //
+  // How many records are wide is known on the device only, so calls with enough
+  // pairs to a block of pixels are given the blocks that wide ones need: these cost
+  // the others at most 3 %, and fewer pairs or more images would lose to them.
+  // Rendering Gaussians of sd 3 pixels, 3.5 where one or two images, us:
+  // 4 -> 64 threads, one image of 64 x 64, 30000 Gaussians 836 -> 145 (16: 279);
+  // 4 -> 16, one of 100 x 100, 400000 6441 -> 2093; two of 160 x 160, 50000
+  // 683 -> 339; four of 100 x 100, 60000 1087 -> 463.  (Eight of
+  // 128 x 128 with 20000 of sd 1 pixel take 57 with 4 threads and 60 with 16.)
+  // 1 -> 4, eight of 200 x 200, 20000, whose last tiles are 8 pixels wide
+  // 560 -> 226.  One thread and a tile's pixels in up to four blocks, 37 of
+  // 200 x 200, 20000 2898 -> 1304 (of sd 1 pixel 147 -> 135); below 1024
+  // Gaussians, 64 of 100 x 100 with 500 take 37.8 so and 38.6 in more blocks.
   typedef void (*ReduceFn)(const float *, const int *, const int *, const int *, const int *, const float4 *,
                            Geom, float *);
   const int64_t tiles = (int64_t)G.ntiles * G.B;
   const size_t quads = (size_t)G.T * G.T / 4;
-  const int S = tiles * cdiv(quads, kBlock) < 512 ? 4 : 1;
-  const ReduceFn k_canvas_reduce = S == 1 ? &k_canvas_reduce_s<1> : &k_canvas_reduce_s<4>;
+  const int64_t pairs = (int64_t)G.N * G.B, blocks = cdiv((int64_t)G.B * G.D * G.D, 4 * kBlock);
+  int S = tiles * cdiv(quads, kBlock) < 512 || (blocks <= 384 && pairs >= 256 * blocks) ? 4 : 1;
+  if (G.B <= 4 && blocks <= 80 && pairs >= 256 * blocks) S = blocks < 8 && pairs >= 4096 * blocks ? 64 : 16;
+  const ReduceFn k_canvas_reduce = S == 1    ? &k_canvas_reduce_s<1>
+                                   : S == 4  ? &k_canvas_reduce_s<4>
+                                   : S == 16 ? &k_canvas_reduce_s<16>
+                                             : &k_canvas_reduce_s<64>;
   const int per_tile = (int)cdiv(quads, kBlock / S);
-  const int zsplit = std::max(1, std::min(per_tile, (int)((512 * S + tiles - 1) / tiles)));
+  const int want = S > 1 ? 512 * S : G.N >= 1024 ? 2048 : 512;
+  const int zsplit = std::max(1, std::min(per_tile, (int)((want + tiles - 1) / tiles)));
   TLAUNCH(k_canvas_reduce, dim3(G.ntiles, G.B, zsplit), dim3(kBlock), 0, st,
           (const float *)(ws + P.L.partials), (const int *)(ws + P.L.item_off),
           (const int *)(ws + P.L.n_items), (const int *)(ws + P.L.off), (const int *)(ws + P.L.count),

@@ -454,7 +454,10 @@ __device__ __forceinline__ void wide_box(const float4 r0, const float4 r1, const
 //
 // S threads share a pixel group, each taking every S-th item and record, and
 // their sums are added in order: 1 where the tiles alone fill the chip, 4 for
-// calls of few images, whose time is one thread's walk over its items.
+// calls of few images, whose time is one thread's walk over its items, 16 or 64
+// where those few images have many Gaussians, whose wide records would otherwise
+// be a few blocks' work (one image of 100 x 100, 500000 Gaussians of sd 3.5 pixels:
+// 8.0 ms with 4 threads, 2.6 ms with 16).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float4 f4add(float4 a, float4 b) {
   return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
@@ -623,6 +626,10 @@ template __global__ void k_canvas_reduce_s<1>(const float *, const int *, const 
                                               const float4 *, Geom, float *);
 template __global__ void k_canvas_reduce_s<4>(const float *, const int *, const int *, const int *, const int *,
                                               const float4 *, Geom, float *);
+template __global__ void k_canvas_reduce_s<16>(const float *, const int *, const int *, const int *, const int *,
+                                               const float4 *, Geom, float *);
+template __global__ void k_canvas_reduce_s<64>(const float *, const int *, const int *, const int *, const int *,
+                                               const float4 *, Geom, float *);
 
 // ---------------------------------------------------------------------------
 // Wide records k = part, part + parts, ... of one image in the adjoint, W waves
