@@ -1630,6 +1630,18 @@ static bool conv_fwd_by_gemm(int C, int N, int64_t M) {
   return tiles > 256 && (C <= 64 || (C <= 96 && N <= 128) || (C <= 192 && tiles <= 384));
 }
 
+// Masked data gradients that k_gemm does faster (the same bits): 32 channels are a
+// short contraction per read of the mask, of which k_gemm has more blocks to a CU in
+// flight.  C channels in, N out, M pixels, us, k_gemm and ring: 32 to 64, M 98,304
+// 50 and 51, 262,144 128 and 157; 32 to 128, 65,536 57 and 55, 98,304 79 and 80,
+// 524,288 427 and 460; 32 to 192, 32,768 55 and 55, 65,536 100 and 105, 131,072 205
+// and 227.  Where N leaves columns of its tiles empty it is the slower one: 32 to
+// 56, 262,144 131 and 113; 32 to 72 238 and 203; and with 64 channels at every
+// size: 64 to 64 189 and 181.
+static bool conv_dgrad_by_gemm(int C, int N, int64_t M, bool masked) {
+  return masked && C == 32 && N % 64 == 0 && M >= (N > 128 ? 65536 : 98304);
+}
+
 template <int NWM, int NWN, int TI, int TJ, int S, bool DGRAD>
 static void launch_conv_tile(const ConvMma &a, hipStream_t st) {
   const unsigned tiles = cdiv_(a.M, NWM * TI * 16) * cdiv_(a.N, NWN * TJ * 16) * (DGRAD ? 4 : 1);
@@ -1694,8 +1706,9 @@ hipError_t conv12_fwd(const bf16 *in0, const bf16 *w1, const float *b1, const bf
 
 hipError_t conv_dgrad(const bf16 *dout, const bf16 *wt, const bf16 *act_in, int B, int Hi, int Wi,
                       int Cin, int Cout, bf16 *din, float *din32, hipStream_t st) {
-  if (conv_mma_ok(Cout, B, Hi, Wi) && aligned_to(16, dout, wt) && aligned_to(16, din32) &&
-      aligned_to(8, act_in, din)) {
+  const int64_t pixels = (int64_t)B * (Hi / 2) * (Wi / 2);
+  if (conv_mma_ok(Cout, B, Hi, Wi) && !conv_dgrad_by_gemm(Cout, Cin, pixels, act_in != nullptr) &&
+      aligned_to(16, dout, wt) && aligned_to(16, din32) && aligned_to(8, act_in, din)) {
     ConvMma a{};
     a.src = dout; a.w = wt; a.mask = act_in; a.out = din; a.out32 = din32;
     a.Hs = a.Hm = Hi / 2; a.Ws = a.Wm = Wi / 2; a.C = Cout; a.N = Cin;
