@@ -147,8 +147,10 @@ typedef struct {
                          distinct LDS banks (pays for wide footprints);
                          2 = sorted by footprint shape (row count, then
                          widest span) so that the lanes of a wave walk
-                         similar footprints (pays where sizes spread).  The
-                         results are identical in every order. */
+                         similar footprints (pays where sizes spread; the
+                         forward pass keeps list order where many are as
+                         tall as the image).  The results are identical in
+                         every order. */
 } cs_options;
 
 /* Create a context on HIP device `device`.  *out receives the handle. */
